@@ -31,7 +31,7 @@ namespace stb {
 
 constexpr double kPi = 3.14159265358979323846;
 constexpr double kTwoPi = 6.28318530717958647692;
-constexpr int kMaxBp = 48;        // breakpoints per (apex, panel) pair
+constexpr int kMaxBp = 36;        // breakpoints per (apex, panel) pair: 12 edge events, 6 per face
 constexpr int kMaxNg = 64;        // Gauss nodes per phi piece
 // breakpoint hint tolerances (fractions of |t - tau_min| + panel size)
 constexpr double kTangHint = 0.05;
@@ -158,14 +158,6 @@ STB_HD __forceinline__ void sincos_half_pi(double x, double* s, double* c) {
   pc = fma_keep(pc, x2, 1.0 / 24.0);                         //  1/4!
   pc = fma_keep(pc, x2, -0.5);                               // -1/2!
   *c = fma(x2, pc, 1.0);
-}
-
-STB_HD __forceinline__ double wrap_2pi(double a) {
-  if (a < 0.0) a += kTwoPi;
-  if (a < 0.0) a += kTwoPi;
-  if (a >= kTwoPi) a -= kTwoPi;
-  if (a >= kTwoPi) a -= kTwoPi;
-  return a;
 }
 
 // The apex in the panel's frame (t, p_u, p_v, d), without the C_k.
@@ -581,6 +573,14 @@ STB_HD __forceinline__ double atan2_bp(double y, double x) {
   return mx > 0.0 ? th : 0.0;
 }
 
+// An angle of (-pi, pi] plus or minus up to 3 pi / 2, back in [0, 2 pi): one
+// turn at most.
+STB_HD __forceinline__ double wrap_turn(double a) {
+  a += a < 0.0 ? kTwoPi : 0.0;
+  a -= a >= kTwoPi ? kTwoPi : 0.0;
+  return a;
+}
+
 // acos x = atan2(sqrt((1 - x)(1 + x)), x) for x in [-1, 1].
 STB_HD __forceinline__ double acos_bp(double x) {
   return atan2_bp(sqrt_nn((1.0 - x) * (1.0 + x)), x);
@@ -628,19 +628,22 @@ STB_HD inline void face_angles(const TrialRec& T, FaceAng& F) {
 }
 
 // Breakpoint storage: a plain array, or (the breakpoint kernel) slots in
-// LDS with the rare overflow in private memory.  put/get by slot index.
+// LDS with the rare overflow in private memory.  put/get by slot index;
+// put_edge/get_edge for the 24 slots of the edge events (always in LDS).
 struct BpArray {
   double* a;
   STB_HD __forceinline__ void put(int i, double v) { a[i] = v; }
   STB_HD __forceinline__ double get(int i) const { return a[i]; }
+  STB_HD __forceinline__ void put_edge(int i, double v) { a[i] = v; }
+  STB_HD __forceinline__ double get_edge(int i) const { return a[i]; }
 };
+constexpr int kEdgeSlots = 24;
 
+// Edge events into slots 0..; returns their number (sc: the pair's scale
+// |t - tau_min| + panel size).  Reads the panel's local vertices only.
 template <class BP>
-STB_HD inline int breakpoints_t(const TrialRec& T, const FaceAng& FA, const Apex& A, BP& bp) {
-  int nb = 0;
-  double d2 = A.d * A.d, ad = fabs(A.d);
-  const double rd2 = d2 > 0.0 ? frcp(d2) : 0.0;   // for the tangency test
-  double sc = fabs(A.t - T.tmin) + T.diam;
+STB_HD inline int edge_events(const TrialRec& T, const Apex& A, double sc, BP& bp) {
+  const double d2 = A.d * A.d;
   // cone function at the vertices: an edge with both ends strictly inside
   // the backward cone (a convex set) cannot meet it
   double fv[4];
@@ -672,64 +675,77 @@ STB_HD inline int breakpoints_t(const TrialRec& T, const FaceAng& FA, const Apex
         ok = ok && !(a0 + a1 * l < 0.0);
         double ou = bu + l * du, ov = bv + l * dv;
         ok = ok && !(ou * ou + ov * ov <= 1e-20 * sc * sc);
-        if (ok) {
-          bp.put(nh, ou);
-          bp.put(12 + nh, ov);
-          ++nh;
-        }
+        // written in any case, kept by the count: at most 11 are kept before
+        // the twelfth
+        bp.put_edge(nh, ou);
+        bp.put_edge(12 + nh, ov);
+        nh += ok ? 1 : 0;
       }
     }
-  for (int m = 0; m < nh; ++m) bp.put(m, wrap_2pi(atan2_bp(bp.get(12 + m), bp.get(m))));
-  nb = nh;
+  for (int m = 0; m < nh; ++m) bp.put_edge(m, wrap_turn(atan2_bp(bp.get_edge(12 + m), bp.get_edge(m))));
+  return nh;
+}
+
+// Appends the faces' breakpoints after nb others; returns the new count.
+// Reads the panel's faces only.
+template <class BP>
+STB_HD inline int face_events(const TrialRec& T, const FaceAng& FA, const Apex& A, double sc, BP& bp, int nb) {
+  const double d2 = A.d * A.d, ad = fabs(A.d);
+  const double rd2 = d2 > 0.0 ? frcp(d2) : 0.0;   // for the tangency test
   for (int k = 0; k < 4; ++k) {
     double a = T.fa[k], b = T.fb[k], c = T.fc[k], Ck = A.C[k];
     double beta = FA.beta[k];
     if (!(beta > 1e-12)) continue;
     double phik = FA.phi[k];
-    if (d2 > 0.0) {
-      double rhs = a * a - Ck * Ck * rd2;
-      if (rhs >= 0.0 && rhs <= beta * beta) {
-        const double rb = frcp(beta);
-        double cv = fmin(sqrt_nn(rhs) * rb, 1.0);
-        double g = acos_bp(cv);
-        // candidates phi_k + g, phi_k - g, phi_k + pi - g, phi_k + pi + g;
-        // their directions from (cos, sin) of phi_k = (b, c) / beta and of
-        // g = (cv, sqrt(1 - cv^2)) by the addition theorems
-        const double cp = b * rb, sp = c * rb, sg = sqrt_nn((1.0 - cv) * (1.0 + cv));
-        const double c1 = cp * cv - sp * sg, s1 = sp * cv + cp * sg;   // phi_k + g
-        const double c2 = cp * cv + sp * sg, s2 = sp * cv - cp * sg;   // phi_k - g
-#pragma unroll 1
-        for (int m = 0; m < 4; ++m) {
-          const bool pg = m == 0 || m == 3;             // + g
-          const double sgn = m < 2 ? 1.0 : -1.0;        // + pi: opposite direction
-          const double cs = sgn * (pg ? c1 : c2), sn = sgn * (pg ? s1 : s2);
-          const double cand = (m < 2 ? phik : phik + kPi) + (pg ? g : -g);
-          double e = b * cs + c * sn - a;
-          if (e == 0.0) continue;
-          double wt = Ck * frcp(e);           // double root of Q_k
-          if (!(wt >= ad) || !(wt > 0.0)) continue;
-          const double rw = frcp(wt);
-          double rt = d2 > 0.0 ? 0.5 * (wt + d2 * rw) : 0.5 * wt, st = 0.5 * (wt - d2 * rw);
-          double y0 = A.t - rt, y1 = A.pu + st * cs, y2 = A.pv + st * sn;
-          double worst = -1e300;
+    // Tangencies: D_k = C_k^2 + d^2 (B^2 - a_k^2) = 0 at B = -+ sqrt(rhs), rhs =
+    // a^2 - C^2 / d^2, with the double root w = C / (B - a) of Q_k.  The roots
+    // for the two signs have the product C^2 / (a^2 - rhs) = d^2, so only
+    // the one whose B has the sign of a reaches |d|, and it is positive only
+    // where C has the other sign: w = -(B + a) d^2 / C, d^2 / w = -C / (B + a)
+    // (sums of equal signs).  Its two directions phi_k -+ g (turned by pi for
+    // a < 0) share w, r and s.
+    const double rhs = a * a - Ck * Ck * rd2;
+    if (d2 > 0.0 && rhs >= 0.0 && rhs <= beta * beta && a * Ck < 0.0) {
+      const double rb = frcp(beta), sq = sqrt_nn(rhs);
+      const double cv = fmin(sq * rb, 1.0);
+      const double sg = sqrt_nn((1.0 - cv) * (1.0 + cv));
+      const double g = atan2_bp(sg, cv);
+      const double Ba = copysign(sq, a) + a;
+      const double wt = -(Ba * d2) * frcp(Ck), vt = -Ck * frcp(Ba);   // w, d^2 / w
+      const double rt = 0.5 * (wt + vt), st = 0.5 * (wt - vt);
+      // directions from (cos, sin) of phi_k = (b, c) / beta and (cv, sg) of g
+      const double rs = copysign(rb, a), cp = b * rs, sp = c * rs;
+      const double cc = cp * cv, ss = sp * sg, sc1 = sp * cv, cs1 = cp * sg;
+      double wp = -1e300, wm = -1e300;   // the worst face at + g and at - g
 #pragma unroll
-          for (int m2 = 0; m2 < 4; ++m2)
-            worst = fmax(worst, T.fa[m2] * y0 + T.fb[m2] * y1 + T.fc[m2] * y2 - T.fh[m2]);
-          if (worst <= kTangHint * sc) bp.put(nb++, wrap_2pi(cand));
-        }
+      for (int m2 = 0; m2 < 4; ++m2) {
+        const double h = fma(T.fa[m2], rt, A.C[m2]);   // a_m tau + b_m p_u + c_m p_v - h_m = -h
+        wp = fmax(wp, fma(st, fma(T.fb[m2], cc - ss, T.fc[m2] * (sc1 + cs1)), -h));
+        wm = fmax(wm, fma(st, fma(T.fb[m2], cc + ss, T.fc[m2] * (sc1 - cs1)), -h));
       }
+      const bool reach = wt >= ad && wt > 0.0;
+      const double base = a < 0.0 ? phik + kPi : phik;
+      if (reach && wp <= kTangHint * sc) bp.put(nb++, wrap_turn(base + g));
+      if (reach && wm <= kTangHint * sc) bp.put(nb++, wrap_turn(base - g));
     }
     if (fabs(a * ad + Ck) <= kVtxHint * sc) {
-      bp.put(nb++, wrap_2pi(phik + 0.5 * kPi));
-      bp.put(nb++, wrap_2pi(phik - 0.5 * kPi));
+      bp.put(nb++, wrap_turn(phik + 0.5 * kPi));
+      bp.put(nb++, wrap_turn(phik - 0.5 * kPi));
     }
     if (ad <= kFlatTol * sc && fabs(Ck) <= kFlatTol * sc && fabs(a) <= beta) {
       double g = acos_bp(fmax(-1.0, fmin(1.0, a / beta)));
-      bp.put(nb++, wrap_2pi(phik + g));
-      bp.put(nb++, wrap_2pi(phik - g));
+      bp.put(nb++, wrap_turn(phik + g));
+      bp.put(nb++, wrap_turn(phik - g));
     }
   }
   return nb;
+}
+
+template <class BP>
+STB_HD inline int breakpoints_t(const TrialRec& T, const FaceAng& FA, const Apex& A, BP& bp) {
+  const double sc = fabs(A.t - T.tmin) + T.diam;
+  const int nb = edge_events(T, A, sc, bp);
+  return face_events(T, FA, A, sc, bp, nb);
 }
 
 STB_HD inline int breakpoints(const TrialRec& T, const FaceAng& FA, const Apex& A, double* bp) {
@@ -787,8 +803,7 @@ struct ShadowWedge {
   bool ok;
 };
 
-STB_HD __forceinline__ ShadowWedge shadow_wedge(const TrialRec& T, const Apex& A) {
-  const double sc = fabs(A.t - T.tmin) + T.diam;
+STB_HD __forceinline__ ShadowWedge shadow_wedge(const TrialRec& T, const Apex& A, double sc) {
   double du[4], dv[4], n2[4];
   bool nearp = false;
 #pragma unroll
@@ -843,12 +858,11 @@ STB_HD __forceinline__ bool wedge_misses(const ShadowWedge& W, double a, double 
   return W.ok & (u > 0.0) & (fma(0.5, H, u) < W.len);
 }
 
-// Sorts a[0..n) for n <= M (M a power of 2): into registers (padded with
-// +inf), Batcher's odd-even merge network, back -- independent loads and
-// stores instead of the insertion sort's dependent chain through memory.
+// Loads a[0..n) for n <= M into registers (padded with +inf) and sorts them
+// by Batcher's odd-even merge network: independent loads and compare-exchanges
+// instead of the insertion sort's dependent chain through memory.
 template <int M, class BP>
-STB_HD __forceinline__ void sort_net(BP& a, int n) {
-  double r[M];
+STB_HD __forceinline__ void load_sorted(const BP& a, int n, double (&r)[M]) {
 #pragma unroll
   for (int j = 0; j < M; ++j) r[j] = j < n ? a.get(j) : HUGE_VAL;
 #pragma unroll
@@ -865,6 +879,13 @@ STB_HD __forceinline__ void sort_net(BP& a, int n) {
             r[i + j] = lo;
             r[i + j + k] = hi;
           }
+}
+
+// Sorts a[0..n) for n <= M through load_sorted.
+template <int M, class BP>
+STB_HD __forceinline__ void sort_net(BP& a, int n) {
+  double r[M];
+  load_sorted<M>(a, n, r);
 #pragma unroll
   for (int j = 0; j < M; ++j)
     if (j < n) a.put(j, r[j]);

@@ -103,7 +103,10 @@ struct DlBp {
   __device__ __forceinline__ double get(int i) const {
     return i < kDlBpLds ? lds[i * stride] : spill[i - kDlBpLds];
   }
+  __device__ __forceinline__ void put_edge(int i, double v) { lds[i * stride] = v; }
+  __device__ __forceinline__ double get_edge(int i) const { return lds[i * stride]; }
 };
+static_assert(kDlBpLds >= kEdgeSlots, "the edge events' slots are in LDS");
 
 __global__ __launch_bounds__(256) void k_dl_split(int64_t c0, int64_t n, const int32_t* __restrict__ rowof,
                                                   const int32_t* __restrict__ cols,

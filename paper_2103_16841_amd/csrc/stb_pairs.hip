@@ -375,6 +375,7 @@ __global__ __launch_bounds__(kBlk) void k_emit(Lists L, int64_t nc) {
 // MB, past the L2 caches: keeping the lists there cost most of the kernel's
 // memory traffic.
 constexpr int kBpLds = 24;
+static_assert(kBpLds >= kEdgeSlots, "the edge events' slots are in LDS");
 struct BpLds {
   double* lds;
   int stride;
@@ -386,8 +387,127 @@ struct BpLds {
   __device__ __forceinline__ double get(int i) const {
     return i < kBpLds ? lds[i * stride] : spill[i - kBpLds];
   }
+  __device__ __forceinline__ void put_edge(int i, double v) { lds[i * stride] = v; }
+  __device__ __forceinline__ double get_edge(int i) const { return lds[i * stride]; }
 };
 
+// The same slots for a list known to lie in LDS.
+struct BpLow {
+  const double* lds;
+  int stride;
+  __device__ __forceinline__ double get(int i) const { return lds[i * stride]; }
+};
+
+// The pieces of a combo with 1 <= nb <= M breakpoints, sorted in registers
+// and never written back: bit m of the result is set where the piece that
+// starts at breakpoint m is kept (positive length, not missed by the ray
+// test); r holds the breakpoints.
+template <int M>
+__device__ __forceinline__ uint32_t pieces_in_regs(const BpLow& bp, int nb, const ShadowWedge& W, double (&r)[M],
+                                                   unsigned* nmiss) {
+  load_sorted<M>(bp, nb, r);
+  uint32_t keep = 0;
+  unsigned miss = 0;
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const double e = (m + 1 < M && m + 1 < nb) ? r[m + 1 < M ? m + 1 : 0] : r[0] + kTwoPi;
+    const double H = e - r[m];
+    const bool pos = (m < nb) & (H > 0.0);
+    const bool wm = pos & wedge_misses(W, r[m], H);
+    miss += wm ? 1u : 0u;
+    keep |= (pos & !wm) ? 1u << m : 0u;
+  }
+  *nmiss = miss;
+  return keep;
+}
+
+// Appends those pieces to the piece list from slot s on.
+template <int M>
+__device__ __forceinline__ void store_pieces(const Lists& L, const double (&r)[M], int nb, uint32_t keep,
+                                             unsigned long long s, int32_t k) {
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    if (!((keep >> m) & 1u)) continue;
+    const double e = (m + 1 < M && m + 1 < nb) ? r[m + 1 < M ? m + 1 : 0] : r[0] + kTwoPi;
+    L.pa[s] = r[m];
+    L.ph[s] = e - r[m];
+    L.pc[s] = k;
+    ++s;
+  }
+}
+
+// The breakpoint kernel reads a panel's record in three parts, each into
+// registers at once where its stage begins (read through a reference the
+// loads sink into the branches, each waiting for its own): the frame for the
+// apex, the local vertices for the edge events and again for the ray test,
+// the faces for the C_k and the face events.  Kept in registers across the
+// whole kernel they would spill: the pointer passed through `fresh` makes the
+// later reads loads of their own (cache hits).
+__device__ __forceinline__ const TrialRec* fresh(const TrialRec* p) {
+  asm volatile("" : "+v"(p));
+  return p;
+}
+
+__device__ __forceinline__ void read_frame(const TrialRec* __restrict__ p, TrialRec& T) {
+  const double2* s = reinterpret_cast<const double2*>(p);
+  double2 r[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) r[i] = s[i];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    T.o[c] = (&r[0].x)[c];
+    T.e1[c] = (&r[0].x)[3 + c];
+    T.e2[c] = (&r[0].x)[6 + c];
+    T.n[c] = (&r[0].x)[9 + c];
+  }
+}
+
+__device__ __forceinline__ void read_verts(const TrialRec* __restrict__ p, TrialRec& T) {
+  const double2* s = reinterpret_cast<const double2*>(&p->V[0][0]);
+  double2 r[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) r[i] = s[i];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) T.V[k][c] = (&r[0].x)[3 * k + c];
+}
+
+__device__ __forceinline__ void read_faces(const TrialRec* __restrict__ p, TrialRec& T) {
+  const double2* s = reinterpret_cast<const double2*>(&p->fa[0]);
+  double2 r[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i] = s[i];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    T.fa[k] = (&r[0].x)[k];
+    T.fb[k] = (&r[0].x)[4 + k];
+    T.fc[k] = (&r[0].x)[8 + k];
+    T.fh[k] = (&r[0].x)[12 + k];
+  }
+}
+
+__device__ __forceinline__ FaceAng face_ang(const FaceAng* __restrict__ p) {
+  const double2* s = reinterpret_cast<const double2*>(p);
+  double2 r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = s[i];
+  FaceAng F;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    F.phi[k] = (&r[0].x)[k];
+    F.beta[k] = (&r[0].x)[4 + k];
+  }
+  return F;
+}
+
+// Bound by instruction issue (about 2,240 vector instructions per wave and
+// pass, the vector pipes busy 68%); three waves per SIMD by its LDS slots and
+// registers.  30,720-panel assembly, 3.77e8 combos: 41.2 ms with every panel
+// field behind one reference, both signs of each tangency and the sorted
+// breakpoints written back; 35.5 ms with the record read in parts, the
+// tangencies' one reachable root, and the pieces taken from the sorted
+// registers.  Four waves per SIMD (19 slots, 128 registers): 43.2 ms, spills.
 __global__ __launch_bounds__(kBlk, 3) void k_bp(Geo g, Lists L, int64_t c0, int64_t ncombo_arg) {
   const int B = (int)blockDim.x;
   const int64_t ncombo = list_count(L, ncombo_arg, L.cap_combo, 2);
@@ -396,79 +516,113 @@ __global__ __launch_bounds__(kBlk, 3) void k_bp(Geo g, Lists L, int64_t c0, int6
   unsigned long long nmiss = 0;
   double spill[kMaxBp - kBpLds];
   BpLds bp{s_bp + threadIdx.x, B, spill};
+  const BpLow low{s_bp + threadIdx.x, B};
   for (int64_t base = (int64_t)blockIdx.x * B; base < ncombo; base += (int64_t)gridDim.x * B) {
     const int64_t k = base + threadIdx.x;
     const bool v = k < ncombo;
     int nb = 0;
-    unsigned np = 0;
-    unsigned long long miss = 0;   // pieces (by start breakpoint) found empty by the ray test
+    bool live = false;             // the combo has an admissible range
+    ShadowWedge W{0.0, 0.0, false};
     if (v) {
       const uint32_t key = L.key[k];
       const int64_t cg = c0 + (key >> kKeyShift);
       const int q = (int)(key & kKeyQ);
       const int32_t i = g.rows[cg];
       const int32_t col = g.cols[cg];
-      const TrialRec& T = g.trial[col];
+      const TrialRec* tp = g.trial + col;
+      TrialRec T;
+      read_frame(tp, T);
+      read_faces(tp, T);
+      T.tmin = tp->tmin;
+      T.tmax = tp->tmax;
+      T.diam = tp->diam;
       const double* xq = g.apex + ((int64_t)i * g.maxq + q) * 4;
       double x4[4] = {xq[0], xq[1], xq[2], xq[3]};
       Apex A;
       apex_of(T, x4, A);
+      const double sc = fabs(A.t - T.tmin) + T.diam;
       double wlo = 0.0, whi = 0.0;
-      if (w_range(T, A, wlo, whi)) {
+      live = w_range(T, A, wlo, whi);
+      if (live) {
         ComboL cb;
 #pragma unroll
-        for (int f = 0; f < 4; ++f) {
-          cb.C[f] = A.C[f]; cb.fa[f] = T.fa[f]; cb.fb[f] = T.fb[f]; cb.fc[f] = T.fc[f];
-        }
+        for (int f = 0; f < 4; ++f) cb.C[f] = A.C[f];
         cb.d2 = A.d * A.d; cb.wlo = wlo; cb.whi = whi;
         store_combo(L, k, cb, col);
-        if (g.mixed && apex_far(T, x4, g.eta_far)) L.key[k] = key | kKeyFar;
-        nb = breakpoints_t(T, g.fang[col], A, bp);
-        // the 8-wide network when every lane of the wave has at most 8
-        // breakpoints (about half the waves), the 16-wide one otherwise
-        if (__ballot(nb > 8) == 0) sort_net<8>(bp, nb);
-        else sort_bp_t(bp, nb);
-        if (nb == 0) {
-          np = 2;
-        } else {
-          const ShadowWedge W = shadow_wedge(T, A);
-          for (int m = 0; m < nb; ++m) {
-            const double a = bp.get(m);
-            double e = (m + 1 < nb) ? bp.get(m + 1) : bp.get(0) + kTwoPi;
-            const bool pos = e - a > 0.0;
-            const bool wm = pos & wedge_misses(W, a, e - a);
-            miss |= (uint64_t)wm << m;
-            nmiss += wm ? 1 : 0;
-            np += (pos && !wm) ? 1u : 0u;
-          }
+        if (g.mixed && apex_far(*tp, x4, g.eta_far)) L.key[k] = key | kKeyFar;
+        read_verts(tp, T);
+        nb = edge_events(T, A, sc, bp);
+        tp = fresh(tp);
+        read_faces(tp, T);
+        const FaceAng FA = face_ang(g.fang + col);
+        nb = face_events(T, FA, A, sc, bp, nb);
+        if (nb > 0) {
+          tp = fresh(tp);
+          read_verts(tp, T);
+          W = shadow_wedge(T, A, sc);
         }
       }
     }
+    // the wave sorts in the 8-wide network when all its lanes have at most 8
+    // breakpoints (about half the waves), else in the 16-wide one; beyond 16
+    // (nearly never) through the slots
+    const bool wide = __ballot(nb > 16) != 0, mid = __ballot(nb > 8) != 0;
+    double r[16];
+    unsigned long long keep = 0;   // pieces, by start breakpoint
+    unsigned ms = 0;
+    if (wide) {
+      if (nb > 0) {
+        sort_bp_t(bp, nb);
+        for (int m = 0; m < nb; ++m) {
+          const double a = bp.get(m);
+          const double e = (m + 1 < nb) ? bp.get(m + 1) : bp.get(0) + kTwoPi;
+          const bool pos = e - a > 0.0;
+          const bool wm = pos & wedge_misses(W, a, e - a);
+          ms += wm ? 1u : 0u;
+          keep |= (unsigned long long)(pos & !wm) << m;
+        }
+      }
+    } else if (mid) {
+      if (nb > 0) keep = pieces_in_regs<16>(low, nb, W, r, &ms);
+    } else {
+      double r8[8];
+      if (nb > 0) keep = pieces_in_regs<8>(low, nb, W, r8, &ms);
+#pragma unroll
+      for (int m = 0; m < 8; ++m) r[m] = r8[m];
+    }
+    nmiss += ms;
+    const unsigned np = live ? (nb == 0 ? 2u : (unsigned)__popcll(keep)) : 0u;
     const unsigned long long p0 = block_alloc(L.cnt + CNT_PIECE, np, sh);
     if (v) {
       L.p0[k] = (int32_t)std::min<unsigned long long>(p0, 0x7fffffffull);
       L.np[k] = (int32_t)np;
-      if (np && p0 + np <= (unsigned long long)L.cap_piece) {
-        if (nb == 0) {
-          for (int h = 0; h < 2; ++h) {
-            L.pa[p0 + h] = (double)h;
-            L.ph[p0 + h] = -1.0;
-            L.pc[p0 + h] = (int32_t)k;
-          }
-        } else {
-          unsigned long long s = p0;
-          for (int m = 0; m < nb; ++m) {
-            double a = bp.get(m);
-            double e = (m + 1 < nb) ? bp.get(m + 1) : bp.get(0) + kTwoPi;
-            const bool keep = (e - a > 0.0) && !((miss >> m) & 1ull);
-            if (keep) {
-              L.pa[s] = a;
-              L.ph[s] = e - a;
-              L.pc[s] = (int32_t)k;
-            }
-            s += keep ? 1 : 0;
+    }
+    if (np && p0 + np <= (unsigned long long)L.cap_piece) {
+      if (nb == 0) {
+        for (int h = 0; h < 2; ++h) {
+          L.pa[p0 + h] = (double)h;
+          L.ph[p0 + h] = -1.0;
+          L.pc[p0 + h] = (int32_t)k;
+        }
+      } else if (wide) {
+        unsigned long long s = p0;
+        for (int m = 0; m < nb; ++m) {
+          const double a = bp.get(m);
+          const double e = (m + 1 < nb) ? bp.get(m + 1) : bp.get(0) + kTwoPi;
+          if ((keep >> m) & 1ull) {
+            L.pa[s] = a;
+            L.ph[s] = e - a;
+            L.pc[s] = (int32_t)k;
+            ++s;
           }
         }
+      } else if (mid) {
+        store_pieces<16>(L, r, nb, (uint32_t)keep, p0, (int32_t)k);
+      } else {
+        double r8[8];
+#pragma unroll
+        for (int m = 0; m < 8; ++m) r8[m] = r[m];
+        store_pieces<8>(L, r8, nb, (uint32_t)keep, p0, (int32_t)k);
       }
     }
   }
