@@ -52,8 +52,8 @@ constexpr int kBlk = 256;
 constexpr int kMaxBlocks = 256 * 16;
 
 enum {
-  CNT_COMBO = 0, CNT_DEEP, CNT_PIECE, CNT_JOB, CNT_JOB1X, CNT_JOB2, CNT_JOBF, CNT_JOB32, CNT_REDO, CNT_JOBR, CNT_PAIRS, CNT_CAUSAL, CNT_EVAL_MID,
-  CNT_EVAL_QUARTER, CNT_EVAL_NODES, CNT_EVAL_NODES32, CNT_EVAL_REDO, CNT_MISS, CNT_QZ, CNT_N
+  CNT_COMBO = 0, CNT_DEEP, CNT_PIECE, CNT_JOB, CNT_JOB1X, CNT_JOB2, CNT_JOBF, CNT_JOB32, CNT_QZ, CNT_REDO, CNT_PAIRS,
+  CNT_CAUSAL, CNT_EVAL_MID, CNT_MISS, CNT_N
 };
 
 // Combo key: (candidate in chunk) << kKeyShift | far << 6 | q, q < 64
@@ -64,23 +64,37 @@ constexpr uint32_t kKeyQ = 63u;
 
 // Block-wide list allocation: every thread of the block calls it (n = 0
 // when it has nothing to append), with the same LDS scratch; one atomic per
-// block.  Same-address atomics serialise in the memory system, so they are
-// kept to one per few hundred list entries.  Returns the first slot of this
-// thread's n entries; slots are in thread order within the block.
+// block.  Returns the first slot of this thread's n entries; slots are in
+// thread order within the block.
+//
+// Atomics on one address go through the memory side at about 13 ns each
+// whatever kernel issues them (5.9e6 of them took 77 ms), so a list's
+// counter may be touched only once per several hundred entries: the lit test
+// appends its open apexes for kLitPer candidates per lane at once (the
+// breakpoint kernel's once per 256 combos are hidden behind its arithmetic),
+// a wave of the empty-piece test allocates for up to 1,024 pieces at once,
+// and the counts that only describe the work are summed per block.
 struct AllocLds {
   unsigned wtot[kBlk / 64];
   unsigned long long base;
 };
 
+// Inclusive prefix sum of n over the wavefront.
+template <class T>
+__device__ __forceinline__ T wave_prefix(T n) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const T v = __shfl_up(n, off, 64);
+    if (lane >= off) n += v;
+  }
+  return n;
+}
+
 __device__ __forceinline__ unsigned long long block_alloc(unsigned long long* ctr, unsigned n,
                                                           AllocLds& sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  unsigned incl = n;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    unsigned v = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += v;
-  }
+  const unsigned incl = wave_prefix(n);
   if (lane == 63) sh.wtot[wave] = incl;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -100,10 +114,16 @@ __device__ __forceinline__ unsigned long long block_alloc(unsigned long long* ct
 }
 
 // Sum of a per-lane count over the block, added to *ctr once per block.
-__device__ __forceinline__ void block_count(unsigned long long* ctr, unsigned long long v) {
+// Every thread of the block calls it, outside other uses of sh.
+__device__ __forceinline__ void block_count(unsigned long long* ctr, unsigned long long v, AllocLds& sh) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  if ((threadIdx.x & 63) == 0 && v) atomicAdd(ctr, v);
+  __syncthreads();
+  if (threadIdx.x == 0) sh.base = 0ull;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0 && v) atomicAdd(&sh.base, v);
+  __syncthreads();
+  if (threadIdx.x == 0 && sh.base) atomicAdd(ctr, sh.base);
 }
 
 struct Lists {
@@ -270,45 +290,57 @@ __device__ __forceinline__ TrialRec lit_fields(const TrialRec* __restrict__ p) {
 static_assert(offsetof(TrialRec, tmin) == 24 * sizeof(double) && offsetof(TrialRec, rad) == 30 * sizeof(double),
               "lit_fields layout");
 
+// kLitPer candidates per lane and pass, their open apexes in LDS until the
+// pass's one list allocation.
+constexpr int kLitPer = 4;
+
 __global__ __launch_bounds__(kBlk, 4) void k_lit(Geo g, Lists L, int64_t c0, int64_t nc) {
   const int B = (int)blockDim.x;
   __shared__ AllocLds sh;
+  __shared__ uint64_t s_und[kLitPer][kBlk];
   unsigned long long pairs = 0;
-  for (int64_t base = (int64_t)blockIdx.x * B; base < nc; base += (int64_t)gridDim.x * B) {
-    const int64_t c = base + threadIdx.x;
-    const bool v = c < nc;
-    uint64_t m = 0, und = 0;
-    int nq = 0;
-    if (v) {
-      const int64_t cg = c0 + c;
-      const int32_t i = g.rows[cg];
-      const TrialRec T = lit_fields(g.trial + g.cols[cg]);
-      nq = g.apex_n ? g.apex_n[i] : 1;
-      // (points passed in by a caller are only known to be 8-byte aligned)
-      const double* xr = g.apex + (int64_t)i * g.maxq * 4;
-      // the next apex is loaded while this one is tested
-      double xn[4] = {xr[0], xr[1], xr[2], xr[3]};
-      for (int q = 0; q < nq; ++q) {
-        double x4[4] = {xn[0], xn[1], xn[2], xn[3]};
-        if (q + 1 < nq)
+  for (int64_t base = (int64_t)blockIdx.x * B * kLitPer; base < nc; base += (int64_t)gridDim.x * B * kLitPer) {
+    unsigned n = 0;
+#pragma unroll 1
+    for (int j = 0; j < kLitPer; ++j) {
+      const int64_t c = base + (int64_t)j * B + threadIdx.x;
+      uint64_t m = 0, und = 0;
+      if (c < nc) {
+        const int64_t cg = c0 + c;
+        const int32_t i = g.rows[cg];
+        const TrialRec T = lit_fields(g.trial + g.cols[cg]);
+        const int nq = g.apex_n ? g.apex_n[i] : 1;
+        // (points passed in by a caller are only known to be 8-byte aligned)
+        const double* xr = g.apex + (int64_t)i * g.maxq * 4;
+        // the next apex is loaded while this one is tested
+        double xn[4] = {xr[0], xr[1], xr[2], xr[3]};
+        for (int q = 0; q < nq; ++q) {
+          double x4[4] = {xn[0], xn[1], xn[2], xn[3]};
+          if (q + 1 < nq)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) xn[c] = xr[4 * (q + 1) + c];
-        Apex A;
-        apex_frame(T, x4, A);
-        const int r = lit_quick(T, x4, A);
-        m |= (uint64_t)(r == 1) << q;
-        und |= (uint64_t)(r == 2) << q;
+            for (int c = 0; c < 4; ++c) xn[c] = xr[4 * (q + 1) + c];
+          Apex A;
+          apex_frame(T, x4, A);
+          const int r = lit_quick(T, x4, A);
+          m |= (uint64_t)(r == 1) << q;
+          und |= (uint64_t)(r == 2) << q;
+        }
+        pairs += (unsigned long long)nq;
+        L.mask[c] = m;
       }
-      pairs += (unsigned long long)nq;
-      L.mask[c] = m;
+      s_und[j][threadIdx.x] = und;
+      n += (unsigned)__popcll(und);
     }
-    const unsigned n = (unsigned)__popcll(und);
     unsigned long long k = block_alloc(L.cnt + CNT_DEEP, n, sh);
-    if (v && k + n <= (unsigned long long)L.cap_combo)
-      for (int q = 0; q < nq; ++q)
-        if ((und >> q) & 1ull) L.deep[k++] = ((uint32_t)c << kKeyShift) | (uint32_t)q;
+    if (n && k + n <= (unsigned long long)L.cap_combo)
+#pragma unroll 1
+      for (int j = 0; j < kLitPer; ++j) {
+        const uint32_t c = (uint32_t)(base + (int64_t)j * B + threadIdx.x);
+        for (uint64_t und = s_und[j][threadIdx.x]; und; und &= und - 1)
+          L.deep[k++] = (c << kKeyShift) | (uint32_t)(__ffsll((long long)und) - 1);
+      }
   }
-  block_count(L.cnt + CNT_PAIRS, pairs);
+  block_count(L.cnt + CNT_PAIRS, pairs, sh);
 }
 
 // The second pass's fields: the first pass's and the vertices (t, x, y, z).
@@ -626,15 +658,24 @@ __global__ __launch_bounds__(kBlk, 3) void k_bp(Geo g, Lists L, int64_t c0, int6
       }
     }
   }
-  block_count(L.cnt + CNT_MISS, nmiss);
+  block_count(L.cnt + CNT_MISS, nmiss, sh);
 }
 
-// The empty-piece test, kEmptyPer pieces per lane and pass: a wave takes
-// kEmptyPer runs of 64 consecutive pieces (coalesced reads; the job lists
-// keep piece order), so that one list allocation covers 64 kEmptyPer
+// The empty-piece test, up to kEmptyPer pieces per lane and pass: a wave takes
+// that many runs of 64 consecutive pieces (coalesced reads; the job lists
+// keep piece order), so that one list allocation covers up to 64 kEmptyPer
 // pieces.  L at the midpoint (k_empty); the pieces where it is zero are
-// queued for the quarter points (k_quarter).
-constexpr int kEmptyPer = 8;
+// queued for the quarter points (k_quarter).  On 9.4e8 pieces the two took
+// 51 ms with 4 pieces per lane (one allocation each 13.7 ns), 28.9 with 8,
+// 27.9 with 16; a short list takes fewer, so that it spreads over
+// kEmptyWaves waves (3,840 panels, 3.1e7 pieces: 1.24 -> 1.13 ms).
+constexpr int kEmptyPer = 16;
+constexpr int64_t kEmptyWaves = 2048;
+
+__device__ __forceinline__ int empty_per(int64_t n) {
+  const int64_t per = (n + 64 * kEmptyWaves - 1) / (64 * kEmptyWaves);
+  return (int)(per < 1 ? 1 : per < kEmptyPer ? per : kEmptyPer);
+}
 
 // Job lists the empty-piece test routes a non-empty piece to.
 // One-gap recipes whose two endpoints are both q / e roots (nearly all of
@@ -664,69 +705,70 @@ __device__ __forceinline__ unsigned route_of(const Lists& L, int32_t p, uint32_t
 
 // Job lists of one pass: every lane routes up to kEmptyPer pieces (3 bits
 // of route each in `route`, presence in `has`, piece j from piece_of(j)).
-// Slots are handed out per wave, for the six lists at once: the lane's
-// counts (at most kEmptyPer each) in 10-bit fields of one 64-bit word, one
-// shuffle scan over the wave, and lane f reserves list f's slots with one
-// atomic when the wave has any (no block barriers; the rare lists are
-// rarely touched).  Every lane of the wave must call it.
+// Slots are handed out per wave: the lane's counts of the three frequent
+// lists in 21-bit fields of one 64-bit word, one shuffle scan over the wave,
+// and lane f reserves list f's slots with one atomic when the wave has any
+// (no block barriers); the other three lists, which few waves touch, the
+// same way when the wave has any entry for them.  Every lane of the wave
+// must call it.
 constexpr int JOB_QZ = 5;   // not a job list: the queue for the quarter points
-static_assert(kEmptyPer * 64 < 1024, "per-wave list counts fit 10 bits");
 
 template <class F>
-__device__ __forceinline__ void route_pieces(Lists& L, unsigned has, unsigned route, F piece_of) {
+__device__ __forceinline__ void route_pieces(const Lists& L, unsigned has, uint64_t route, F piece_of) {
   const int lane = threadIdx.x & 63;
-  unsigned long long v = 0;
-  for (int j = 0; j < kEmptyPer; ++j)
-    if ((has >> j) & 1u) v += 1ull << (10 * ((route >> (3 * j)) & 7u));
-  unsigned long long incl = v;
+  auto route_at = [&](int j) { return (unsigned)(route >> (3 * j)) & 7u; };
+  // one word of three lists: counts, and the wave's slots
+  auto reserve = [&](uint64_t v, int c0, int c1, int c2, unsigned long long (&s)[3]) {
+    const uint64_t incl = wave_prefix(v);
+    const uint64_t tot = __shfl(incl, 63, 64);
+    unsigned long long b = 0;
+    if (lane < 3) {
+      const unsigned long long n = (tot >> (21 * lane)) & 0x1fffffull;
+      if (n) b = atomicAdd(L.cnt + (lane == 0 ? c0 : lane == 1 ? c1 : c2), n);
+    }
+    const uint64_t ex = incl - v;
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned long long t = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += t;
-  }
-  const unsigned long long tot = __shfl(incl, 63, 64);
-  unsigned long long b = 0;
-  if (lane < 6) {
-    const int ctr = lane == JOB_R1Q ? CNT_JOB : lane == JOB_R2 ? CNT_JOB2 : lane == JOB_FULL ? CNT_JOBF
-                  : lane == JOB_FP32 ? CNT_JOB32 : lane == JOB_R1X ? CNT_JOB1X : CNT_QZ;
-    const unsigned long long n = (tot >> (10 * lane)) & 1023u;
-    if (n) b = atomicAdd(L.cnt + ctr, n);
-  }
-  const unsigned long long ex = incl - v;
+    for (int f = 0; f < 3; ++f) s[f] = __shfl(b, f, 64) + ((ex >> (21 * f)) & 0x1fffffull);
+    return tot;
+  };
   // the one-gap q/e jobs (nearly every piece) in piece order: item j of
   // every lane before item j + 1, lanes in order within an item, so that
   // neighbouring jobs read neighbouring pieces and combos
-  unsigned long long s0 = __shfl(b, JOB_R1Q, 64);
+  uint64_t vf = 0, vr = 0;
+  unsigned rest = 0;   // items that go to the other lists
+  for (int j = 0; j < kEmptyPer; ++j) {
+    const bool h = (has >> j) & 1u;
+    const unsigned r = route_at(j);
+    vf += !h ? 0ull : r == JOB_R1Q ? 1ull : r == JOB_R1X ? 1ull << 21 : r == JOB_QZ ? 1ull << 42 : 0ull;
+    vr += !h ? 0ull : r == JOB_R2 ? 1ull : r == JOB_FULL ? 1ull << 21 : r == JOB_FP32 ? 1ull << 42 : 0ull;
+    rest |= (h && r != JOB_R1Q) ? 1u << j : 0u;
+  }
+  unsigned long long sf[3], sr[3] = {0ull, 0ull, 0ull};
+  (void)reserve(vf, CNT_JOB, CNT_JOB1X, CNT_QZ, sf);
+  unsigned long long s0 = __shfl(sf[0], 0, 64);   // lane 0 has none before it
   const unsigned long long below = (1ull << lane) - 1ull;
   for (int j = 0; j < kEmptyPer; ++j) {
-    const bool q = ((has >> j) & 1u) && ((route >> (3 * j)) & 7u) == JOB_R1Q;
+    const bool q = ((has >> j) & 1u) && route_at(j) == JOB_R1Q;
     const unsigned long long bal = __ballot(q);
     if (q) L.job[s0 + __popcll(bal & below)] = piece_of(j);
     s0 += __popcll(bal);
   }
-  unsigned long long s1 = __shfl(b, JOB_R2, 64) + ((ex >> 10) & 1023u);
-  unsigned long long s2 = __shfl(b, JOB_FULL, 64) + ((ex >> 20) & 1023u);
-  unsigned long long s3 = __shfl(b, JOB_FP32, 64) + ((ex >> 30) & 1023u);
-  unsigned long long s4 = __shfl(b, JOB_R1X, 64) + ((ex >> 40) & 1023u);
-  unsigned long long s5 = __shfl(b, JOB_QZ, 64) + ((ex >> 50) & 1023u);
   // the other lists: only the lane's items that go there (nearly always
-  // none or one of its kEmptyPer), so the wave runs the slowest lane's few
-  unsigned rare = 0;
-  for (int j = 0; j < kEmptyPer; ++j)
-    rare |= (((has >> j) & 1u) && ((route >> (3 * j)) & 7u) != JOB_R1Q ? 1u : 0u) << j;
-  while (rare) {
-    const int j = __ffs(rare) - 1;
-    rare &= rare - 1u;
-    const unsigned r = (route >> (3 * j)) & 7u;
+  // none or a few of its kEmptyPer), so the wave runs the slowest lane's
+  if (__ballot(vr != 0ull)) (void)reserve(vr, CNT_JOB2, CNT_JOBF, CNT_JOB32, sr);
+  while (rest) {
+    const int j = __ffs(rest) - 1;
+    rest &= rest - 1u;
+    const unsigned r = route_at(j);
     const int32_t p = piece_of(j);
-    int32_t* dst = r == JOB_R2 ? L.job2 + s1 : r == JOB_FULL ? L.jobf + s2 : r == JOB_FP32 ? L.job32 + s3
-                 : r == JOB_R1X ? L.job + (L.cap_piece - 1 - (int64_t)s4) : L.pz + s5;
+    int32_t* dst = r == JOB_R2 ? L.job2 + sr[0] : r == JOB_FULL ? L.jobf + sr[1] : r == JOB_FP32 ? L.job32 + sr[2]
+                 : r == JOB_R1X ? L.job + (L.cap_piece - 1 - (int64_t)sf[1]) : L.pz + sf[2];
     *dst = p;
-    s1 += r == JOB_R2 ? 1 : 0;
-    s2 += r == JOB_FULL ? 1 : 0;
-    s3 += r == JOB_FP32 ? 1 : 0;
-    s4 += r == JOB_R1X ? 1 : 0;
-    s5 += r == JOB_QZ ? 1 : 0;
+    sr[0] += r == JOB_R2 ? 1 : 0;
+    sr[1] += r == JOB_FULL ? 1 : 0;
+    sr[2] += r == JOB_FP32 ? 1 : 0;
+    sf[1] += r == JOB_R1X ? 1 : 0;
+    sf[2] += r == JOB_QZ ? 1 : 0;
   }
 }
 
@@ -738,15 +780,18 @@ __device__ __forceinline__ void route_pieces(Lists& L, unsigned has, unsigned ro
 __global__ __launch_bounds__(kBlk, 4) void k_empty(Lists L, int64_t npiece_arg) {
   const int B = (int)blockDim.x;
   const int64_t npiece = list_count(L, npiece_arg, L.cap_piece, 3);
+  const int per = empty_per(npiece);
+  __shared__ AllocLds sh;
   unsigned long long ev_mid = 0;
-  const int64_t step = (int64_t)gridDim.x * B * kEmptyPer;
-  for (int64_t base = (int64_t)blockIdx.x * B * kEmptyPer; base < npiece; base += step) {
-    unsigned has = 0, route = 0;   // route: 3 bits per item
-    // each wave takes kEmptyPer runs of 64 consecutive pieces
-    const int64_t wbase = base + (int64_t)(threadIdx.x >> 6) * 64 * kEmptyPer + (threadIdx.x & 63);
+  const int64_t step = (int64_t)gridDim.x * B * per;
+  for (int64_t base = (int64_t)blockIdx.x * B * per; base < npiece; base += step) {
+    unsigned has = 0;
+    uint64_t route = 0;   // 3 bits per item
+    // each wave takes `per` runs of 64 consecutive pieces
+    const int64_t wbase = base + (int64_t)(threadIdx.x >> 6) * 64 * per + (threadIdx.x & 63);
     auto piece_of = [&](int j) { return (int32_t)(wbase + (int64_t)j * 64); };
 #pragma unroll 1
-    for (int j = 0; j < kEmptyPer; ++j) {
+    for (int j = 0; j < per; ++j) {
       const int64_t p = wbase + (int64_t)j * 64;
       if (p >= npiece) break;
       const double H = L.ph[p];
@@ -761,11 +806,11 @@ __global__ __launch_bounds__(kBlk, 4) void k_empty(Lists L, int64_t npiece_arg) 
       L.pne[p] = nz ? 1 : 0;
       L.prec[p] = rec;
       has |= 1u << j;
-      route |= (nz ? route_of(L, (int32_t)p, rec) : (unsigned)JOB_QZ) << (3 * j);
+      route |= (uint64_t)(nz ? route_of(L, (int32_t)p, rec) : (unsigned)JOB_QZ) << (3 * j);
     }
     route_pieces(L, has, route, piece_of);
   }
-  block_count(L.cnt + CNT_EVAL_MID, ev_mid);
+  block_count(L.cnt + CNT_EVAL_MID, ev_mid, sh);
 }
 
 // The queued pieces (L zero at the midpoint): L at the quarter points; the
@@ -773,13 +818,14 @@ __global__ __launch_bounds__(kBlk, 4) void k_empty(Lists L, int64_t npiece_arg) 
 __global__ __launch_bounds__(kBlk, 3) void k_quarter(Lists L, int64_t nq_arg) {
   const int B = (int)blockDim.x;
   const int64_t nq = list_count(L, nq_arg, L.cap_piece, 3);
-  unsigned long long ev_quarter = 0;
-  const int64_t step = (int64_t)gridDim.x * B * kEmptyPer;
-  for (int64_t base = (int64_t)blockIdx.x * B * kEmptyPer; base < nq; base += step) {
-    unsigned ne = 0, route = 0;
+  const int per = empty_per(nq);
+  const int64_t step = (int64_t)gridDim.x * B * per;
+  for (int64_t base = (int64_t)blockIdx.x * B * per; base < nq; base += step) {
+    unsigned ne = 0;
+    uint64_t route = 0;
     auto piece_of = [&](int j) { return L.pz[base + (int64_t)j * B + threadIdx.x]; };
 #pragma unroll 1
-    for (int j = 0; j < kEmptyPer; ++j) {
+    for (int j = 0; j < per; ++j) {
       const int64_t e = base + (int64_t)j * B + threadIdx.x;
       if (e >= nq) break;
       const int32_t p = L.pz[e];
@@ -793,20 +839,18 @@ __global__ __launch_bounds__(kBlk, 3) void k_quarter(Lists L, int64_t nq_arg) {
       const double v1 = L_at(cb, a + 0.25 * H), v3 = L_at(cb, a + 0.75 * H);
       const bool nz = v1 != 0.0 || v3 != 0.0;
       const double phq = v1 != 0.0 ? a + 0.25 * H : a + 0.75 * H;
-      ev_quarter += 2;
       if (nz) {
         double sn, cs;
         sincos_small(phq, &sn, &cs);
         (void)L_eval_recipe(cb, cs, sn, &rec);
         L.pne[p] = 1;
         L.prec[p] = rec;
-        route |= route_of(L, p, rec) << (3 * j);
+        route |= (uint64_t)route_of(L, p, rec) << (3 * j);
       }
       ne |= (nz ? 1u : 0u) << j;
     }
     route_pieces(L, ne, route, piece_of);
   }
-  block_count(L.cnt + CNT_EVAL_QUARTER, ev_quarter);
 }
 
 // The n_g nodes of a piece by its recipe (NG gaps): per node only the
@@ -816,9 +860,8 @@ __global__ __launch_bounds__(kBlk, 3) void k_quarter(Lists L, int64_t nq_arg) {
 template <int NG, bool QE>
 __global__ __launch_bounds__(kBlk, 4) void k_nodes_rec(Lists L, const int32_t* __restrict__ jobs_arg,
                                                        int64_t njob_arg, const double* __restrict__ gl,
-                                                       int ng, int ctr) {
+                                                       int ng) {
   const int B = (int)blockDim.x;
-  unsigned long long evals = 0;
   const int64_t njob = list_count(L, njob_arg, L.cap_piece, 3);
   const int32_t* __restrict__ jobs = jobs_arg ? jobs_arg : L.job + (L.cap_piece - njob);
   for (int64_t base = (int64_t)blockIdx.x * B; base < njob; base += (int64_t)gridDim.x * B) {
@@ -897,11 +940,9 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes_rec(Lists L, const int32_t* _
       L_pair(1.0, 0.0, lm, lp);
       acc += (1.5 * gl[kMaxNg + (ng >> 1)]) * lm;
     }
-    evals += (unsigned long long)ng;
     // the weights' common factor H, and the 1/2 the doubled r-measures left
     L.pv[p] = (0.5 * H) * acc;
   }
-  block_count(L.cnt + ctr, evals);
 }
 
 // The n_g nodes of one piece.  Gauss piece [a, a + H]: phi = a + H s(u_g),
@@ -910,9 +951,8 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes_rec(Lists L, const int32_t* _
 // 2 pi / (2 n_g).
 __global__ __launch_bounds__(kBlk, 4) void k_nodes(Lists L, const int32_t* __restrict__ jobs,
                                                    int64_t njob_arg, const double* __restrict__ gl,
-                                                   int ng, int ctr) {
+                                                   int ng) {
   const int B = (int)blockDim.x;
-  unsigned long long evals = 0;
   const int64_t njob = list_count(L, njob_arg, L.cap_piece, 3);
   const double ht = kTwoPi / (2 * ng);
   for (int64_t base = (int64_t)blockIdx.x * B; base < njob; base += (int64_t)gridDim.x * B) {
@@ -931,10 +971,8 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes(Lists L, const int32_t* __res
       const double wt = trap ? ht : (H * ds) * gl[kMaxNg + gi];
       acc += wt * L_at(cb, phi);
     }
-    evals += (unsigned long long)ng;
     L.pv[p] = acc;
   }
-  block_count(L.cnt + ctr, evals);
 }
 
 // The n_g nodes of a far piece in mixed precision: node angle, sin/cos and
@@ -943,7 +981,6 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes(Lists L, const int32_t* __res
 __global__ __launch_bounds__(kBlk, 4) void k_nodes32(Lists L, int64_t njob_arg,
                                                      const double* __restrict__ gl, int ng) {
   const int B = (int)blockDim.x;
-  unsigned long long evals = 0;
   const int64_t njob = list_count(L, njob_arg, L.cap_piece, 3);
   const double ht = kTwoPi / (2 * ng);
   for (int64_t base = (int64_t)blockIdx.x * B; base < njob; base += (int64_t)gridDim.x * B) {
@@ -971,14 +1008,12 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes32(Lists L, int64_t njob_arg,
       comp = (t - acc) - y;
       acc = t;
     }
-    evals += (unsigned long long)ng;
     L.pv[p] = (double)acc;
     // the bound also covers the summation: Kahan leaves O(ulp) of the sum.
     // The piece is non-empty (its FP64 test found L > 0): a sum of zero means
     // FP32 lost the whole lit sliver, so the entry must be recomputed.
     L.pe[p] = acc == 0.0f ? INFINITY : eacc + 1.2e-7f * fabsf(acc);
   }
-  block_count(L.cnt + CNT_EVAL_NODES32, evals);
 }
 
 __global__ __launch_bounds__(kBlk) void k_combine(Lists L, int64_t ncombo_arg) {
@@ -1035,6 +1070,7 @@ __global__ __launch_bounds__(kBlk) void k_store(Geo g, Lists L, int64_t c0, int6
   if (L.cnt[CNT_DEEP] > (unsigned long long)L.cap_combo || L.cnt[CNT_COMBO] > (unsigned long long)L.cap_combo ||
       L.cnt[CNT_PIECE] > (unsigned long long)L.cap_piece)
     return;
+  __shared__ AllocLds shc;
   unsigned long long causal = 0, redo = 0;
   for (int64_t base = (int64_t)blockIdx.x * kBlk; base < nc; base += (int64_t)gridDim.x * kBlk) {
     const int64_t c = base + threadIdx.x;
@@ -1085,8 +1121,8 @@ __global__ __launch_bounds__(kBlk) void k_store(Geo g, Lists L, int64_t c0, int6
       }
     }
   }
-  block_count(L.cnt + CNT_CAUSAL, causal);
-  block_count(L.cnt + CNT_REDO, redo);
+  block_count(L.cnt + CNT_CAUSAL, causal, shc);
+  if (check) block_count(L.cnt + CNT_REDO, redo, shc);
 }
 
 // Mixed precision: the non-empty pieces of the far combos of every flagged
@@ -1325,7 +1361,7 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
     for (auto& u : used) u = false;
     HIPCHK(ctx, hipMemsetAsync(L.cnt, 0, CNT_N * 8, st));
     HIPCHK(ctx, t0(0));
-    hipLaunchKernelGGL(k_lit, dim3(gfor(0, nc)), dim3(ctx->tune_block[0]), 0, st, g, L, c0, nc);
+    hipLaunchKernelGGL(k_lit, dim3(gfor(0, nc, kLitPer)), dim3(ctx->tune_block[0]), 0, st, g, L, c0, nc);
     HIPCHK(ctx, hipGetLastError());
     // the consumers read their counts from the device counters (see
     // list_count); grids for the lists' upper bounds: at most maxq lit
@@ -1346,9 +1382,9 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, t1(1));
     HIPCHK(ctx, t0(2));
-    hipLaunchKernelGGL(k_empty, dim3(gfor(2, ub_piece, kEmptyPer)), dim3(ctx->tune_block[2]), 0, st, L,
+    hipLaunchKernelGGL(k_empty, dim3(gfor(2, ub_piece)), dim3(ctx->tune_block[2]), 0, st, L,
                        dev(CNT_PIECE));
-    hipLaunchKernelGGL(k_quarter, dim3(gfor(2, ub_piece, kEmptyPer)), dim3(ctx->tune_block[2]), 0, st, L,
+    hipLaunchKernelGGL(k_quarter, dim3(gfor(2, ub_piece)), dim3(ctx->tune_block[2]), 0, st, L,
                        dev(CNT_QZ));
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, t1(2));
@@ -1356,13 +1392,13 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
     // two-gap recipes, full evaluations
     HIPCHK(ctx, t0(4));
     hipLaunchKernelGGL((k_nodes_rec<1, true>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L,
-                       L.job, dev(CNT_JOB), job.gl, job.ng, (int)CNT_EVAL_NODES);
+                       L.job, dev(CNT_JOB), job.gl, job.ng);
     hipLaunchKernelGGL((k_nodes_rec<1, false>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st,
-                       L, nullptr, dev(CNT_JOB1X), job.gl, job.ng, (int)CNT_EVAL_NODES);
+                       L, nullptr, dev(CNT_JOB1X), job.gl, job.ng);
     hipLaunchKernelGGL((k_nodes_rec<2, false>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st,
-                       L, L.job2, dev(CNT_JOB2), job.gl, job.ng, (int)CNT_EVAL_NODES);
+                       L, L.job2, dev(CNT_JOB2), job.gl, job.ng);
     hipLaunchKernelGGL(k_nodes, dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L, L.jobf,
-                       dev(CNT_JOBF), job.gl, job.ng, (int)CNT_EVAL_NODES);
+                       dev(CNT_JOBF), job.gl, job.ng);
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, t1(4));
     if (g.mixed) {
@@ -1399,10 +1435,11 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
     }
     const unsigned long long ncombo = hc[CNT_COMBO], npiece = hc[CNT_PIECE];
     const unsigned long long njob = hc[CNT_JOB], njob1x = hc[CNT_JOB1X], njob2 = hc[CNT_JOB2];
+    unsigned long long njr = 0;   // jobs of the recomputed entries
     if (check) {
       // mixed: entries whose FP32 error bound is too large for their size
       // are recomputed with FP64 nodes
-      unsigned long long nredo = hc[CNT_REDO], njr = 0;
+      unsigned long long nredo = hc[CNT_REDO];
       if (nredo) {
         // the FP64 job lists were consumed by the launches above (same stream)
         HIPCHK(ctx, hipMemsetAsync(L.cnt + CNT_JOB, 0, 4 * sizeof(unsigned long long), st));
@@ -1419,17 +1456,16 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
           HIPCHK(ctx, t0(7));
           if (r1)
             hipLaunchKernelGGL((k_nodes_rec<1, true>), dim3(gfor(4, r1)), dim3(ctx->tune_block[4]), 0, st, L,
-                               L.job, (int64_t)r1, job.gl, job.ng, (int)CNT_EVAL_REDO);
+                               L.job, (int64_t)r1, job.gl, job.ng);
           if (r1x)
             hipLaunchKernelGGL((k_nodes_rec<1, false>), dim3(gfor(4, r1x)), dim3(ctx->tune_block[4]), 0, st,
-                               L, L.job + (L.cap_piece - (int64_t)r1x), (int64_t)r1x, job.gl, job.ng,
-                               (int)CNT_EVAL_REDO);
+                               L, L.job + (L.cap_piece - (int64_t)r1x), (int64_t)r1x, job.gl, job.ng);
           if (r2)
             hipLaunchKernelGGL((k_nodes_rec<2, false>), dim3(gfor(4, r2)), dim3(ctx->tune_block[4]), 0, st,
-                               L, L.job2, (int64_t)r2, job.gl, job.ng, (int)CNT_EVAL_REDO);
+                               L, L.job2, (int64_t)r2, job.gl, job.ng);
           if (rf)
             hipLaunchKernelGGL(k_nodes, dim3(gfor(4, rf)), dim3(ctx->tune_block[4]), 0, st, L, L.jobf,
-                               (int64_t)rf, job.gl, job.ng, (int)CNT_EVAL_REDO);
+                               (int64_t)rf, job.gl, job.ng);
           HIPCHK(ctx, hipGetLastError());
           HIPCHK(ctx, t1(7));
         }
@@ -1455,18 +1491,22 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
       ctx->kern_ms[k] += ms;
       ctx->kern_n[k] += 1;
     }
-    const unsigned long long evals = h[CNT_EVAL_MID] + h[CNT_EVAL_QUARTER] + h[CNT_EVAL_NODES] +
-                                     h[CNT_EVAL_NODES32] + h[CNT_EVAL_REDO];
+    // every job evaluates n_g nodes, every queued piece two quarter points
+    const unsigned long long ng = (unsigned long long)job.ng;
+    const unsigned long long ev_test = h[CNT_EVAL_MID] + 2 * hc[CNT_QZ];
+    const unsigned long long ev_full = hc[CNT_JOBF] * ng, ev_nodes = (njob + njob1x + njob2) * ng + ev_full;
+    const unsigned long long ev32 = hc[CNT_JOB32] * ng;
+    const unsigned long long evals = ev_test + ev_nodes + ev32 + njr * ng;
     ctx->kern_units[0] += (int64_t)h[CNT_PAIRS];
     ctx->kern_units[1] += (int64_t)ncombo;
-    ctx->kern_units[2] += (int64_t)(h[CNT_EVAL_MID] + h[CNT_EVAL_QUARTER]);
-    ctx->kern_units[4] += (int64_t)h[CNT_EVAL_NODES];
-    ctx->path_counts[0] += (int64_t)(njob + njob1x) * job.ng;
-    ctx->path_counts[1] += (int64_t)njob2 * job.ng;
-    ctx->path_counts[2] += (int64_t)h[CNT_EVAL_NODES] - (int64_t)(njob + njob1x + njob2) * job.ng;
+    ctx->kern_units[2] += (int64_t)ev_test;
+    ctx->kern_units[4] += (int64_t)ev_nodes;
+    ctx->path_counts[0] += (int64_t)((njob + njob1x) * ng);
+    ctx->path_counts[1] += (int64_t)(njob2 * ng);
+    ctx->path_counts[2] += (int64_t)ev_full;
     ctx->path_counts[3] += (int64_t)h[CNT_MISS];
-    ctx->kern_units[5] += (int64_t)h[CNT_EVAL_NODES32];
-    ctx->kern_units[7] += (int64_t)h[CNT_EVAL_REDO];
+    ctx->kern_units[5] += (int64_t)ev32;
+    ctx->kern_units[7] += (int64_t)(njr * ng);
     ctx->kern_units[3] += (int64_t)h[CNT_REDO];
     ctx->kern_units[6] += (int64_t)nc;
     work[0] += evals;
