@@ -1074,38 +1074,58 @@ STB_HD __forceinline__ void order2i(double& s0, double& e0, int& i0, int& j0, do
 // copy of one of them (fmin, fmax and selects keep the bits), and carrying
 // the ids through every comparison instead costs more selects than the
 // arithmetic itself.
-STB_HD inline double L_eval_recipe(const ComboL& cb, double cs, double sn, uint32_t* recipe) {
-  const double kNone = 1e300;
-  const double d2 = cb.d2;
-  double lo = cb.wlo, hi = cb.whi;
-  bool dead = false;
-  double hs[4], he[4], r1[4], r2[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    double a = cb.fa[k];
-    double B = fma(cb.fb[k], cs, cb.fc[k] * sn);
-    double e = B - a, f = B + a, Ck = cb.C[k];
-    double D = fma(Ck, Ck, d2 * (e * f));
-    bool two = D > 0.0;
-    double q = Ck + copysign(sqrt_disc(D), Ck);
-    double w1 = q * frcp(e);
-    double w2 = -d2 * f * frcp(q);
-    r1[k] = w1;
-    r2[k] = w2;
-    double mn = fmin(w1, w2), mx = fmax(w1, w2);
-    bool pos = e > 0.0, neg = e < 0.0, zer = !(pos || neg);
-    bool cut = pos && two;
-    dead = dead || (pos && !two) || (zer && Ck == 0.0 && !(d2 * f > 0.0));
-    lo = cut ? fmax(lo, mn) : lo;
-    hi = cut ? fmin(hi, mx) : hi;
-    lo = (zer && Ck > 0.0) ? fmax(lo, w2) : lo;
-    hi = (zer && Ck < 0.0) ? fmin(hi, w2) : hi;
-    bool hole = neg && two;
-    hs[k] = hole ? mn : kNone;
-    he[k] = hole ? mx : kNone;
+//
+// One face's roots: both from the reciprocal of e q, q / e = q^2 / (e q) and
+// -d^2 f / q = -d^2 e f / (e q); the linear case e = 0 (exactly) has only the
+// second, taken as a quotient of its own.  A discriminant below 2^-900 has no
+// use here (`two` is false, or C_k = d = 0 and its roots are).
+struct FaceRoots {
+  double w1, w2, e;
+  bool two;
+};
+
+STB_HD __forceinline__ FaceRoots face_roots(double a, double b, double c, double Ck, double d2, double cs,
+                                            double sn) {
+  FaceRoots R;
+  const double B = fma(b, cs, c * sn);
+  const double e = B - a, f = B + a;
+  const double p = d2 * (e * f);
+  const double D = fma(Ck, Ck, p);
+  R.two = D > 0.0;
+  const double x = fmax(D, 0x1p-900);
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = fma(-g, h, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  g = fma(fma(-g, g, x), h, g);
+#else
+  const double g = sqrt(x);
+#endif
+  const double q = Ck + copysign(g, Ck);
+  const double t = frcp(e * q);
+  R.w1 = (q * q) * t;
+  R.w2 = -p * t;
+  R.e = e;
+  if (e == 0.0) {   // nearly never
+    R.w1 = 1e300;   // matches no end
+    R.w2 = -d2 * f * frcp(q);
   }
+  return R;
+}
+
+// The general case of L_eval_recipe, from the faces' roots: holes inside the
+// range, two or more gaps.
+STB_HD inline double L_recipe_general(const ComboL& cb, const FaceRoots (&R)[4], double lo, double hi,
+                                      uint32_t* recipe) {
+  const double kNone = 1e300, d2 = cb.d2;
+  double hs[4], he[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
+    const bool hole = R[k].e < 0.0 && R[k].two;
+    hs[k] = hole ? fmin(R[k].w1, R[k].w2) : kNone;
+    he[k] = hole ? fmax(R[k].w1, R[k].w2) : kNone;
     hs[k] = fmin(fmax(hs[k], lo), hi);
     he[k] = fmax(fmin(he[k], hi), hs[k]);
   }
@@ -1136,8 +1156,8 @@ STB_HD inline double L_eval_recipe(const ComboL& cb, double cs, double sn, uint3
     uint32_t id = 9u;
 #pragma unroll
     for (int k = 3; k >= 0; --k) {
-      id = v == r2[k] ? (uint32_t)(3 + 2 * k) : id;
-      id = v == r1[k] ? (uint32_t)(2 + 2 * k) : id;
+      id = v == R[k].w2 ? (uint32_t)(3 + 2 * k) : id;
+      id = v == R[k].w1 ? (uint32_t)(2 + 2 * k) : id;
     }
     id = v == cb.whi ? 1u : id;
     id = v == cb.wlo ? 0u : id;
@@ -1145,9 +1165,62 @@ STB_HD inline double L_eval_recipe(const ComboL& cb, double cs, double sn, uint3
   };
   const uint32_t rec = (ng >= 1 ? (id_of(gs0) << 4) | id_of(ge0) : 0u) |
                        (ng >= 2 ? ((id_of(gs1) << 4) | id_of(ge1)) << 8 : 0u);
+  *recipe = ng > kRecipeGaps ? 0u : (rec | ((uint32_t)ng << 24));
+  return len;
+}
+
+// The faces that open up cut the range to [lo, hi].  A hole that reaches past
+// an end of [lo, hi] moves that end; when no hole lies strictly inside
+// (nearly always) one gap is left, and its two ends and one r-measure are
+// all there is to compute.  Otherwise the general sweep.
+STB_HD __forceinline__ double L_eval_recipe(const ComboL& cb, double cs, double sn, uint32_t* recipe) {
+  const double d2 = cb.d2;
+  FaceRoots R[4];
+  double lo = cb.wlo, hi = cb.whi;
+  bool dead = false;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    R[k] = face_roots(cb.fa[k], cb.fb[k], cb.fc[k], cb.C[k], d2, cs, sn);
+    const bool pos = R[k].e > 0.0, cut = pos && R[k].two;
+    dead = dead || (pos && !R[k].two);
+    lo = cut ? fmax(lo, fmin(R[k].w1, R[k].w2)) : lo;
+    hi = cut ? fmin(hi, fmax(R[k].w1, R[k].w2)) : hi;
+    if (R[k].e == 0.0) {   // nearly never: a half-line, or all or nothing
+      const double Ck = cb.C[k], f = 2.0 * cb.fa[k];   // B = a
+      dead = dead || (Ck == 0.0 && !(d2 * f > 0.0));
+      lo = Ck > 0.0 ? fmax(lo, R[k].w2) : lo;
+      hi = Ck < 0.0 ? fmin(hi, R[k].w2) : hi;
+    }
+  }
+  *recipe = 0u;
   const bool empty = dead || !(hi > lo);
-  *recipe = (empty || ng > kRecipeGaps) ? 0u : (rec | ((uint32_t)ng << 24));
-  return empty ? 0.0 : len;
+  double l1 = lo, h1 = hi;
+  bool inner = false;   // a hole strictly inside
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double mn = fmin(R[k].w1, R[k].w2), mx = fmax(R[k].w1, R[k].w2);
+    const bool hole = R[k].e < 0.0 && R[k].two;
+    const bool a = hole && mn <= lo, b = hole && mx >= hi;
+    l1 = a ? fmax(l1, mx) : l1;
+    h1 = b ? fmin(h1, mn) : h1;
+    inner = inner || (hole && !(a || b) && mx > lo && mn < hi);
+  }
+  if (inner && !empty) return L_recipe_general(cb, R, lo, hi, recipe);
+  const double kWulp = 8.881784197001252e-16;
+  const double m = rdiff(l1, h1, d2);
+  const bool keep = !empty && h1 > l1 && m > kWulp * h1;
+  uint32_t is = 9u, ie = 9u;
+#pragma unroll
+  for (int k = 3; k >= 0; --k) {
+    is = l1 == R[k].w2 ? (uint32_t)(3 + 2 * k) : is;
+    is = l1 == R[k].w1 ? (uint32_t)(2 + 2 * k) : is;
+    ie = h1 == R[k].w2 ? (uint32_t)(3 + 2 * k) : ie;
+    ie = h1 == R[k].w1 ? (uint32_t)(2 + 2 * k) : ie;
+  }
+  is = l1 == cb.wlo ? 0u : is;
+  ie = h1 == cb.whi ? 1u : ie;
+  if (keep) *recipe = (is << 4) | ie | (1u << 24);
+  return keep ? m : 0.0;
 }
 
 STB_HD __forceinline__ int recipe_gaps(uint32_t r) { return (int)((r >> 24) & 3u); }

@@ -161,6 +161,7 @@ struct Lists {
   unsigned long long* cnt;
   int64_t cap_cand, cap_combo, cap_piece;
   const TrialRec* trial; // panel records of the run
+  int mixed;             // far combos' nodes in FP32
 };
 
 // Item count of a list for a kernel: given by the host (n >= 0), or read
@@ -223,22 +224,27 @@ __device__ __forceinline__ Endpoint endpoint_load(const Lists& L, int64_t c, int
   return E;
 }
 
-__device__ __forceinline__ ComboL load_combo(const Lists& L, int64_t k) {
+__device__ __forceinline__ ComboL load_combo(const Lists& L, int64_t k, int32_t col) {
   const int64_t cap = L.cap_combo;
-  const TrialRec& T = L.trial[L.ccol[k]];
+  const double2* s = reinterpret_cast<const double2*>(&L.trial[col].fa[0]);
+  double2 r[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) r[i] = s[i];
   ComboL cb;
 #pragma unroll
   for (int f = 0; f < 4; ++f) {
     cb.C[f] = L.cb[(kCbC + f) * cap + k];
-    cb.fa[f] = T.fa[f];
-    cb.fb[f] = T.fb[f];
-    cb.fc[f] = T.fc[f];
+    cb.fa[f] = (&r[0].x)[f];
+    cb.fb[f] = (&r[0].x)[4 + f];
+    cb.fc[f] = (&r[0].x)[8 + f];
   }
   cb.d2 = L.cb[kCbD2 * cap + k];
   cb.wlo = L.cb[kCbWlo * cap + k];
   cb.whi = L.cb[kCbWhi * cap + k];
   return cb;
 }
+
+__device__ __forceinline__ ComboL load_combo(const Lists& L, int64_t k) { return load_combo(L, k, L.ccol[k]); }
 
 struct Geo {
   const int32_t* rows;   // row of each candidate (global index)
@@ -687,9 +693,9 @@ enum { JOB_R1Q = 0, JOB_R2 = 1, JOB_FULL = 2, JOB_FP32 = 3, JOB_R1X = 4 };
 // within rounding of the breakpoints, where the structure is ambiguous.
 constexpr double kRecipeMinH = 1e-8;
 
-// Route of a non-empty piece among the FP64 node kernels by its recipe.
-__device__ __forceinline__ unsigned route_fp64(const Lists& L, int32_t p, uint32_t rec) {
-  const double H = L.ph[p];
+// Route of a non-empty piece of length H among the FP64 node kernels by its
+// recipe.
+__device__ __forceinline__ unsigned route_fp64(double H, uint32_t rec) {
   const int ng = recipe_gaps(rec);
   if (rec == 0u || !(H >= kRecipeMinH)) return JOB_FULL;
   if (ng != 1) return JOB_R2;
@@ -698,9 +704,11 @@ __device__ __forceinline__ unsigned route_fp64(const Lists& L, int32_t p, uint32
   return qe ? JOB_R1Q : JOB_R1X;
 }
 
-__device__ __forceinline__ unsigned route_of(const Lists& L, int32_t p, uint32_t rec) {
-  if (L.key[L.pc[p]] & kKeyFar) return JOB_FP32;
-  return route_fp64(L, p, rec);
+// The same for any piece of combo k: far combos (mixed precision only) go to
+// the FP32 nodes.
+__device__ __forceinline__ unsigned route_of(const Lists& L, int32_t k, double H, uint32_t rec) {
+  if (L.mixed && (L.key[k] & kKeyFar)) return JOB_FP32;
+  return route_fp64(H, rec);
 }
 
 // Job lists of one pass: every lane routes up to kEmptyPer pieces (3 bits
@@ -776,7 +784,12 @@ __device__ __forceinline__ void route_pieces(const Lists& L, unsigned has, uint6
 // non-empty pieces go to the job lists, the others to the queue of pieces
 // whose quarter points decide (k_quarter).  The quarter-point path has a
 // kernel of its own so that this one, run on every piece, needs fewer
-// registers and keeps more waves resident.
+// registers and keeps more waves resident.  Half of a wave's time went into
+// the chain piece -> combo -> panel and a second look-up of the combo's key
+// for the route: with the first two loads taken ahead, no key outside mixed
+// precision and the one-gap evaluation of L the stage takes 22.1 instead of
+// 27.9 ms (9.4e8 pieces); a whole piece's data ahead at three waves per SIMD
+// is no faster (21.9 ms).
 __global__ __launch_bounds__(kBlk, 4) void k_empty(Lists L, int64_t npiece_arg) {
   const int B = (int)blockDim.x;
   const int64_t npiece = list_count(L, npiece_arg, L.cap_piece, 3);
@@ -790,23 +803,34 @@ __global__ __launch_bounds__(kBlk, 4) void k_empty(Lists L, int64_t npiece_arg) 
     // each wave takes `per` runs of 64 consecutive pieces
     const int64_t wbase = base + (int64_t)(threadIdx.x >> 6) * 64 * per + (threadIdx.x & 63);
     auto piece_of = [&](int j) { return (int32_t)(wbase + (int64_t)j * 64); };
+    // a piece's combo, that combo's panel and the data of both are a chain of
+    // three loads: the first two are taken one and two pieces ahead (past the
+    // list's end, those of its last piece)
+    auto at = [&](int j) { return std::min(wbase + (int64_t)j * 64, npiece - 1); };
+    int32_t k0 = L.pc[at(0)], k1 = L.pc[at(1)];
+    int32_t col0 = L.ccol[k0];
 #pragma unroll 1
     for (int j = 0; j < per; ++j) {
       const int64_t p = wbase + (int64_t)j * 64;
       if (p >= npiece) break;
-      const double H = L.ph[p];
+      const double H = L.ph[p], a = L.pa[p];
+      const int32_t k = k0;
+      const ComboL cb = load_combo(L, k, col0);
+      k0 = k1;
+      k1 = L.pc[at(j + 2)];
+      col0 = L.ccol[k0];
       bool nz = true;   // trapezoid half (H < 0): always evaluated
       uint32_t rec = 0u;
       if (!(H < 0.0)) {
         double sn, cs;
-        sincos_small(L.pa[p] + 0.5 * H, &sn, &cs);
-        nz = L_eval_recipe(load_combo(L, L.pc[p]), cs, sn, &rec) != 0.0;
+        sincos_small(a + 0.5 * H, &sn, &cs);
+        nz = L_eval_recipe(cb, cs, sn, &rec) != 0.0;
         ++ev_mid;
       }
       L.pne[p] = nz ? 1 : 0;
       L.prec[p] = rec;
       has |= 1u << j;
-      route |= (uint64_t)(nz ? route_of(L, (int32_t)p, rec) : (unsigned)JOB_QZ) << (3 * j);
+      route |= (uint64_t)(nz ? route_of(L, k, H, rec) : (unsigned)JOB_QZ) << (3 * j);
     }
     route_pieces(L, has, route, piece_of);
   }
@@ -829,7 +853,8 @@ __global__ __launch_bounds__(kBlk, 3) void k_quarter(Lists L, int64_t nq_arg) {
       const int64_t e = base + (int64_t)j * B + threadIdx.x;
       if (e >= nq) break;
       const int32_t p = L.pz[e];
-      const ComboL cb = load_combo(L, L.pc[p]);
+      const int32_t k = L.pc[p];
+      const ComboL cb = load_combo(L, k);
       const double a = L.pa[p], H = L.ph[p];
       // the test in plain arithmetic; the recipe only for the (few) pieces
       // it finds non-empty, at the point that decided
@@ -845,7 +870,7 @@ __global__ __launch_bounds__(kBlk, 3) void k_quarter(Lists L, int64_t nq_arg) {
         (void)L_eval_recipe(cb, cs, sn, &rec);
         L.pne[p] = 1;
         L.prec[p] = rec;
-        route |= (uint64_t)route_of(L, p, rec) << (3 * j);
+        route |= (uint64_t)route_of(L, k, H, rec) << (3 * j);
       }
       ne |= (nz ? 1u : 0u) << j;
     }
@@ -1143,7 +1168,7 @@ __global__ __launch_bounds__(kBlk) void k_redo(Geo g, Lists L, int64_t nc) {
       for (int32_t k = k0; k < k0 + nk; ++k) {
         if (!(L.key[k] & kKeyFar)) continue;
         for (int32_t p = L.p0[k]; p < L.p0[k] + L.np[k]; ++p)
-          if (L.pne[p]) ++cnt[route_fp64(L, p, L.prec[p])];
+          if (L.pne[p]) ++cnt[route_fp64(L.ph[p], L.prec[p])];
       }
     }
     unsigned long long sl[5];
@@ -1156,7 +1181,7 @@ __global__ __launch_bounds__(kBlk) void k_redo(Geo g, Lists L, int64_t nc) {
         if (!(L.key[k] & kKeyFar)) continue;
         for (int32_t p = L.p0[k]; p < L.p0[k] + L.np[k]; ++p) {
           if (!L.pne[p]) continue;
-          const unsigned r = route_fp64(L, p, L.prec[p]);
+          const unsigned r = route_fp64(L.ph[p], L.prec[p]);
           if (r == JOB_R1X) L.job[L.cap_piece - 1 - (int64_t)(sl[r]++)] = p;
           else if (r == JOB_R1Q) L.job[sl[r]++] = p;
           else if (r == JOB_R2) L.job2[sl[r]++] = p;
@@ -1324,6 +1349,7 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
   if (ctx->list_limit[1]) L.cap_combo = std::min(L.cap_combo, ctx->list_limit[1]);
   if (ctx->list_limit[2]) L.cap_piece = std::min(L.cap_piece, ctx->list_limit[2]);
   L.trial = job.trial;
+  L.mixed = job.mixed ? 1 : 0;
   Geo g;
   g.rows = job.rows; g.cols = job.cols; g.trial = job.trial; g.fang = job.fang;
   g.lit_out = job.lit_out;
