@@ -42,7 +42,7 @@ struct stb_ctx {
   int tune_per_cu[8] = {kDefaultPerCu[0], kDefaultPerCu[1], kDefaultPerCu[2], kDefaultPerCu[3],
                         kDefaultPerCu[4], kDefaultPerCu[5], kDefaultPerCu[6], kDefaultPerCu[7]};
   bool tuned = false;
-  int ncu = 0;
+  int ncu = 1;   // compute units of the device
   // caller's upper limits on the pair lists' lengths: candidates, lit
   // combos, pieces per chunk (0: none; stb_set_pair_lists)
   int64_t list_limit[3] = {0, 0, 0};
@@ -54,7 +54,11 @@ struct stb_ctx {
   // free ones hold kept_bytes <= kKeptMaxBytes
   std::vector<std::pair<void*, size_t>> kept, lent;
   size_t kept_bytes = 0;
+  // small pinned host block that kernels write results to (kPinDoubles, made
+  // on first use)
+  double* h_pin = nullptr;
 };
+constexpr int kPinDoubles = 2048;
 
 struct stb_mesh {
   stb_ctx* ctx = nullptr;
@@ -101,6 +105,11 @@ struct stb_mat {
   int32_t* d_cols = nullptr;
   double* d_vals = nullptr;
   float* d_vals32 = nullptr;     // lazily made for the 16-RHS product
+  // column parts of the product with x in LDS (0: the store is too small
+  // for it): nparts parts of `part` columns, and per row the entries where
+  // one part ends and the next begins
+  int nparts = 0, part = 0;
+  int64_t* d_split = nullptr;    // [n][nparts - 1]
   // host mirror for stb_mat_get / to_dense
   std::vector<int64_t> h_rowptr;
   std::vector<int32_t> h_cols;

@@ -323,6 +323,82 @@ __global__ __launch_bounds__(256) void k_spmv(int64_t n, const int64_t* __restri
   }
 }
 
+// The same product with x in LDS: workgroups of 16 wavefronts, as many as
+// are resident at once, go through the columns in `nparts` parts of P (x's
+// part staged once per workgroup) and, within a part, over the rows, one
+// wavefront per row with 256 entries in flight.  `split` holds, per row, where
+// its entries pass from one part to the next.  What k_spmv loses is the gather
+// of x through the caches: a row's columns come in runs of about seven, so every
+// 64 entries touch nine cache lines or more.  6e7 entries over 30,720 rows
+// (724 MB): k_spmv 196 us, this 155 us = 4.7 TB/s, the same loads without any
+// gather 146 us (a plain read streams at 5.0 TB/s).
+constexpr int kSpmvThreads = 1024;
+constexpr int kSpmvPartMax = 19200;   // doubles of x in LDS (150 KiB)
+__global__ __launch_bounds__(kSpmvThreads) void k_spmv_lds(int64_t n, int nparts, int P, int64_t ncols,
+                                                           const int64_t* __restrict__ rowptr,
+                                                           const int64_t* __restrict__ split,
+                                                           const int32_t* __restrict__ cols,
+                                                           const double* __restrict__ vals,
+                                                           const double* __restrict__ w, int nrhs, int col,
+                                                           double* __restrict__ y) {
+  extern __shared__ double sx[];
+  const int lane = threadIdx.x & 63;
+  const int64_t first = ((int64_t)blockIdx.x * kSpmvThreads + threadIdx.x) >> 6;
+  const int64_t step = (int64_t)gridDim.x * (kSpmvThreads / 64);
+  for (int p = 0; p < nparts; ++p) {
+    const int c0 = p * P, cn = (int)std::min<int64_t>(P, ncols - c0);
+    if (p > 0) __syncthreads();   // the rows of the last part are done with sx
+    for (int i = threadIdx.x; i < cn; i += kSpmvThreads) sx[i] = w[(int64_t)(c0 + i) * nrhs + col];
+    __syncthreads();
+    for (int64_t row = first; row < n; row += step) {
+      const int64_t b = p == 0 ? rowptr[row] : split[row * (nparts - 1) + p - 1];
+      const int64_t e = p == nparts - 1 ? rowptr[row + 1] : split[row * (nparts - 1) + p];
+      int64_t k = b + lane;
+      double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+      for (; k + 192 < e; k += 256) {
+        const int32_t i0 = cols[k], i1 = cols[k + 64], i2 = cols[k + 128], i3 = cols[k + 192];
+        const double v0 = vals[k], v1 = vals[k + 64], v2 = vals[k + 128], v3 = vals[k + 192];
+        s0 = fma(v0, sx[i0 - c0], s0);
+        s1 = fma(v1, sx[i1 - c0], s1);
+        s2 = fma(v2, sx[i2 - c0], s2);
+        s3 = fma(v3, sx[i3 - c0], s3);
+      }
+      // the rest (fewer than 256 entries, this lane's at most 4) at once
+      if (k < e) {
+        const int64_t k1 = k + 64 < e ? k + 64 : k, k2 = k + 128 < e ? k + 128 : k, k3 = k + 192 < e ? k + 192 : k;
+        const int32_t i0 = cols[k], i1 = cols[k1], i2 = cols[k2], i3 = cols[k3];
+        const double v0 = vals[k], v1 = vals[k1], v2 = vals[k2], v3 = vals[k3];
+        s0 = fma(v0, sx[i0 - c0], s0);
+        s1 = k + 64 < e ? fma(v1, sx[i1 - c0], s1) : s1;
+        s2 = k + 128 < e ? fma(v2, sx[i2 - c0], s2) : s2;
+        s3 = k + 192 < e ? fma(v3, sx[i3 - c0], s3) : s3;
+      }
+      double s = (s0 + s1) + (s2 + s3);
+      for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+      if (lane == 0) {
+        double* o = y + row * nrhs + col;
+        *o = p == 0 ? s : *o + s;
+      }
+    }
+  }
+}
+
+// split[row][p]: the row's first entry with a column of part p + 1 or later.
+__global__ void k_spmv_split(int64_t n, int nparts, int P, const int64_t* __restrict__ rowptr,
+                             const int32_t* __restrict__ cols, int64_t* __restrict__ split) {
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= n * (nparts - 1)) return;
+  const int64_t row = g / (nparts - 1);
+  const int64_t target = (g % (nparts - 1) + 1) * P;
+  int64_t lo = rowptr[row], hi = rowptr[row + 1];
+  while (lo < hi) {
+    const int64_t mid = lo + ((hi - lo) >> 1);
+    if (cols[mid] < target) lo = mid + 1;
+    else hi = mid;
+  }
+  split[g] = lo;
+}
+
 // Compaction of a store to its causal entries: one wavefront per row counts
 // the row's flags; after the scan of the counts, one wavefront per row
 // copies the flagged entries in order (ballot + mbcnt give each lane its
@@ -569,6 +645,35 @@ stb_status stb_cull_points(stb_ctx* ctx, stb_mesh* m, const stb_quad_params& p, 
   return s;
 }
 
+// Stores from this many entries on take the product with x in LDS
+// (k_spmv_lds): 15,360 panels (2.1e7 entries) 76 -> 55 us, 30,720 panels
+// (7.2e7) 208 -> 176 us; below, filling the LDS costs what it saves (11,520
+// panels, 1.6e7 entries: 33.0 and 33.6 us; 7,680 panels: 17.9 and 18.8 us).
+constexpr int64_t kSpmvLdsMin = (int64_t)1 << 24;
+
+// The column parts of a large store and where each row crosses them, made with
+// the store so that a product allocates nothing.
+static stb_status spmv_plan(stb_ctx* ctx, stb_mat* M, hipStream_t st) {
+  dfree(M->d_split);
+  M->d_split = nullptr;
+  M->nparts = 0;
+  if (M->nnz < kSpmvLdsMin) return STB_OK;
+  const int64_t nc = mat_ncols(M);
+  const int np = (int)((nc + kSpmvPartMax - 1) / kSpmvPartMax);
+  const int P = (int)((nc + np - 1) / np);
+  if (np > 1) {
+    const int64_t m = M->n * (np - 1);
+    if (dalloc(&M->d_split, (size_t)m) != hipSuccess) return fail(ctx, STB_E_NO_MEMORY, "product plan");
+    hipLaunchKernelGGL(k_spmv_split, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, M->n, np, P, M->d_rowptr,
+                       M->d_cols, M->d_split);
+    HIPCHK(ctx, hipGetLastError());
+    HIPCHK(ctx, hipStreamSynchronize(st));
+  }
+  M->nparts = np;
+  M->part = P;
+  return STB_OK;
+}
+
 stb_status stb_keep_causal(stb_ctx* ctx, stb_mat* M, const uint8_t* d_flag, hipStream_t st) {
   const int64_t n = M->n;
   int64_t *cnt = nullptr, *rp = nullptr;
@@ -609,7 +714,7 @@ stb_status stb_keep_causal(stb_ctx* ctx, stb_mat* M, const uint8_t* d_flag, hipS
   M->d_vals = vals;
   M->nnz = nk;
   M->host_valid = false;
-  return STB_OK;
+  return spmv_plan(ctx, M, st);
 }
 
 // Host copy of a matrix store (for stb_mat_get / stb_mat_to_dense).
@@ -743,6 +848,13 @@ stb_status stb_ctx_create(int32_t device, stb_ctx** out) {
       delete c;
       return fail(nullptr, STB_E_DEVICE, "hipEventCreate failed");
     }
+  if (hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || c->ncu < 1)
+    c->ncu = 1;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_spmv_lds), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)sizeof(double) * kSpmvPartMax) != hipSuccess) {
+    stb_ctx_destroy(c);
+    return fail(nullptr, STB_E_DEVICE, "LDS size of the product");
+  }
   // this device's address of the allocation-free product's scratch array
   if (stb_noalloc_setup(c) != STB_OK) {
     std::string m = c->err;
@@ -762,6 +874,7 @@ void stb_ctx_destroy(stb_ctx* ctx) {
   ctx_drop_kept(ctx);
   for (auto& e : ctx->ev) if (e) (void)hipEventDestroy(e);
   for (auto& e : ctx->kev) if (e) (void)hipEventDestroy(e);
+  if (ctx->h_pin) (void)hipHostFree(ctx->h_pin);
   if (ctx->stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;
 }
@@ -960,6 +1073,7 @@ stb_status stb_assemble_V(stb_ctx* ctx, const stb_mesh* mesh_c, const stb_quad_p
 void stb_mat_destroy(stb_mat* M) {
   if (!M) return;
   dfree(M->d_rowptr); dfree(M->d_cols); dfree(M->d_vals); dfree(M->d_vals32);
+  dfree(M->d_split);
   stb_free_blocked(M);
   delete M;
 }
@@ -1046,7 +1160,15 @@ stb_status stb_apply_dev(stb_ctx* ctx, const stb_mat* M, int32_t nrhs, const dou
   if (nrhs == 16) return stb_apply16_dev(ctx, const_cast<stb_mat*>(M), w, y, st);
   int64_t threads = M->n * 64;
   for (int c = 0; c < nrhs; ++c) {
-    if (M->n > 0) {
+    if (M->n > 0 && M->nparts > 0) {
+      // as many workgroups as are resident: two per CU where x's part takes at
+      // most half the LDS
+      const int64_t blocks = std::min<int64_t>((M->n + kSpmvThreads / 64 - 1) / (kSpmvThreads / 64),
+                                               (int64_t)ctx->ncu * (M->part <= 9600 ? 2 : 1));
+      hipLaunchKernelGGL(k_spmv_lds, dim3((unsigned)blocks), dim3(kSpmvThreads), sizeof(double) * M->part, st, M->n,
+                         M->nparts, M->part, mat_ncols(M), M->d_rowptr, M->d_split, M->d_cols, M->d_vals, w, nrhs, c, y);
+      HIPCHK(ctx, hipGetLastError());
+    } else if (M->n > 0) {
       hipLaunchKernelGGL(k_spmv, dim3((unsigned)std::min<int64_t>((threads + 255) / 256, 1 << 20)), dim3(256), 0, st, M->n,
                          M->d_rowptr, M->d_cols, M->d_vals, w, nrhs, c, y);
       HIPCHK(ctx, hipGetLastError());

@@ -1372,10 +1372,6 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
   // brackets a launch of kernel kind k with events (per chunk, read after
   // the chunk's synchronisation)
   auto t0 = [&](int k) { used[k] = true; return hipEventRecord(ctx->kev[2 * k], st); };
-  if (!ctx->ncu) {
-    HIPCHK(ctx, hipDeviceGetAttribute(&ctx->ncu, hipDeviceAttributeMultiprocessorCount, ctx->device));
-    if (ctx->ncu < 1) ctx->ncu = 1;
-  }
   // grid of stage k: enough blocks for n items (per items per thread), at
   // most the stage's blocks per CU times the CU count
   auto gfor = [&](int k, unsigned long long n, int per = 1) {

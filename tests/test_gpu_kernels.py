@@ -1,0 +1,56 @@
+"""Small tests of single kernels at the sizes where they can go wrong: edges of
+tiles and parts, remainders, the smallest and largest of a dispatch's range.
+References are plain numpy on the library's own exported values, or the oracle."""
+import numpy as np
+import pytest
+
+from paper_2103_16841_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -53
+
+
+@pytest.fixture(scope="module")
+def stb():
+    import torch
+    torch.cuda.init()
+    from paper_2103_16841_amd import stb as s
+    s.load()
+    return s
+
+
+@pytest.fixture(scope="module")
+def ctx(stb):
+    c = stb.Context(0)
+    yield c
+    c.close()
+
+
+def _rows_of(A, rows):
+    """Dense rows of a matrix through stb_mat_get."""
+    cols = np.tile(np.arange(A.n, dtype=np.int32), len(rows))
+    return A.get(np.repeat(np.asarray(rows, dtype=np.int32), A.n), cols).reshape(len(rows), A.n)
+
+
+# one column part (15,360 panels), two (30,720) and three (40,320, the last part's
+# rows mostly empty before the late slabs); 11,520 panels stay below the limit
+@pytest.mark.parametrize("level,slabs", [(1, 48), (2, 16), (2, 32), (2, 42)])
+def test_product_with_column_parts(stb, ctx, level, slabs):
+    mesh = inputs.icosphere_mesh(level, slabs)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    A = stb.assemble_V(ctx, M, stb.default_params(m_q=1, n_g=2))
+    rng = np.random.default_rng(0)
+    # the first rows (nearly empty), the last, both sides of the workgroups' strides
+    rows = np.unique(np.concatenate([[0, 1, 15, 16, 4095, 4096, A.n - 1], rng.integers(0, A.n, 9)]))
+    D = _rows_of(A, rows)
+    for nrhs in (1, 3):
+        W = rng.standard_normal((A.n, nrhs) if nrhs > 1 else A.n)
+        Y = A.apply(W)
+        ref = D @ W
+        # any order of summation: at most (terms) eps of the terms' size
+        bound = (D != 0).sum(1) * EPS * 2
+        scale = np.abs(D) @ np.abs(W)
+        assert np.all(np.abs(Y[rows] - ref) <= (bound[:, None] * scale if nrhs > 1 else bound * scale))
+    A.close()
+    M.close()
