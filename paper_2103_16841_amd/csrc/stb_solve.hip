@@ -1,12 +1,15 @@
 // stb_solve.hip -- the discrete indirect system (eq. df_ind): restarted
-// GMRES over the assembled energetic single-layer matrix, on the device.
+// GMRES over the assembled energetic single-layer matrix, on the device, and
+// marching-on-in-time for slab-structured meshes.
 //
-// Every Krylov step is one FP64 product with the stored matrix (k_spmv)
-// plus classical Gram-Schmidt against the basis, done twice for
-// orthogonality (CGS2): two batched dot products and two batched updates.
-// The small Hessenberg problem (Givens rotations, back substitution) stays
-// on the host.  Dot products are fixed-order block reductions, so results
-// do not depend on the schedule.
+// Every Krylov step is one FP64 product with the stored matrix plus
+// classical Gram-Schmidt against the basis, done twice for orthogonality
+// (CGS2): partial dot products of every basis vector per chunk of n, then one
+// kernel that sums a vector's chunks in order and subtracts.  The small
+// Hessenberg problem (Givens rotations, back substitution) stays on the host;
+// a step's coefficients reach it through pinned memory while the next step's
+// product is already running.  Every sum has a fixed order, so results do not
+// depend on the schedule.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -20,38 +23,140 @@ namespace {
 
 constexpr int kSolveThreads = 256;
 
-// out[b] = <V_b, w> for b < k (V row-major, k rows of ld doubles).
-__global__ __launch_bounds__(kSolveThreads) void k_dots(int64_t n, const double* __restrict__ V,
-                                                        int64_t ld, const double* __restrict__ w,
-                                                        double* __restrict__ out) {
-  const double* v = V + (int64_t)blockIdx.x * ld;
+// part[b * nch + c] = <V_b, w> over chunk c of kGsChunk elements, for b < k (V
+// row-major, rows of n doubles): one wavefront per vector and chunk.  (One
+// workgroup per vector took 37 us at n = 30,720: 120 dependent loads a lane,
+// and one busy CU for the few vectors of the first steps.)
+constexpr int64_t kGsChunk = 1024;
+__global__ __launch_bounds__(kSolveThreads) void k_gs_dots(int64_t n, int k, const double* __restrict__ V,
+                                                           const double* __restrict__ w,
+                                                           double* __restrict__ part) {
+  const int lane = threadIdx.x & 63;
+  const int b = (int)blockIdx.y * (kSolveThreads / 64) + (int)(threadIdx.x >> 6);
+  if (b >= k) return;
+  const double* v = V + (int64_t)b * n;
+  const int64_t i0 = (int64_t)blockIdx.x * kGsChunk, i1 = std::min<int64_t>(i0 + kGsChunk, n);
   double s = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += kSolveThreads) s += v[i] * w[i];
+  if (i1 - i0 == kGsChunk) {
+    double p[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < (int)(kGsChunk / 64); ++u) p[u & 3] = fma(v[i0 + 64 * u + lane], w[i0 + 64 * u + lane], p[u & 3]);
+    s = (p[0] + p[1]) + (p[2] + p[3]);
+  } else {
+    for (int64_t i = i0 + lane; i < i1; i += 64) s = fma(v[i], w[i], s);
+  }
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+  if (lane == 0) part[(int64_t)b * gridDim.x + blockIdx.x] = s;
+}
+
+// h[b] = the sum of b's nch chunks (in order), w -= sum_{b < k} h[b] V_b; block 0
+// writes h to hout.  npart (optional): per block the sum of its new w_i^2.
+constexpr int kMaxBasis = 513;
+__global__ __launch_bounds__(kSolveThreads) void k_gs_sub(int64_t n, int k, int64_t nch, const double* __restrict__ V,
+                                                          const double* __restrict__ part, double* __restrict__ w,
+                                                          double* __restrict__ hout, double* __restrict__ npart) {
+  __shared__ double h[kMaxBasis];
+  for (int b = threadIdx.x; b < k; b += kSolveThreads) {
+    double s = 0.0;
+    for (int64_t c = 0; c < nch; ++c) s += part[(int64_t)b * nch + c];
+    h[b] = s;
+    if (blockIdx.x == 0) hout[b] = s;
+  }
+  __syncthreads();
+  const int64_t i = (int64_t)blockIdx.x * kSolveThreads + threadIdx.x;
+  double s = 0.0;
+  if (i < n) {
+    s = w[i];
+    int b = 0;
+    for (; b + 8 <= k; b += 8) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = V[(int64_t)(b + u) * n + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s = fma(-h[b + u], v[u], s);
+    }
+    for (; b < k; ++b) s = fma(-h[b], V[(int64_t)b * n + i], s);
+    w[i] = s;
+  }
+  if (!npart) return;
+  double q = s * s;
+  for (int off = 32; off > 0; off >>= 1) q += __shfl_down(q, off, 64);
+  __shared__ double red[kSolveThreads / 64];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = q;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = red[0];
+    for (int v = 1; v < kSolveThreads / 64; ++v) t += red[v];
+    npart[blockIdx.x] = t;
+  }
+}
+
+// Sum of m partial sums in a fixed order, by a whole block.
+__device__ __forceinline__ double block_sum(const double* __restrict__ part, int64_t m) {
   __shared__ double red[kSolveThreads];
+  double s = 0.0;
+  for (int64_t c = threadIdx.x; c < m; c += kSolveThreads) s += part[c];
   red[threadIdx.x] = s;
   __syncthreads();
   for (int off = kSolveThreads / 2; off > 0; off >>= 1) {
     if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+  return red[0];
 }
 
-// w -= sum_{b < k} h[b] V_b (b ascending).
-__global__ void k_subtract(int64_t n, int k, const double* __restrict__ V, int64_t ld,
-                           const double* __restrict__ h, double* __restrict__ w) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double s = w[i];
-  for (int b = 0; b < k; ++b) s -= h[b] * V[(int64_t)b * ld + i];
-  w[i] = s;
+// out = w / |w| (0 for |w| = 0) from the m partial sums of |w|^2; block 0
+// writes |w|^2 and, with k > 0, the k + k coefficients of the two Gram-Schmidt
+// passes to `host` (pinned host memory): [0] |w|^2, [1 ...] first, then
+// second pass.
+__global__ __launch_bounds__(kSolveThreads) void k_gs_scale(int64_t n, int64_t m, const double* __restrict__ npart,
+                                                            const double* w, double* out, int k,
+                                                            const double* __restrict__ h1,
+                                                            const double* __restrict__ h2, double* __restrict__ host) {
+  const double q = block_sum(npart, m);
+  const double f = q > 0.0 ? 1.0 / sqrt(q) : 0.0;
+  const int64_t i = (int64_t)blockIdx.x * kSolveThreads + threadIdx.x;
+  if (i < n) out[i] = f * w[i];
+  if (blockIdx.x != 0) return;
+  if (threadIdx.x == 0) host[0] = q;
+  for (int b = threadIdx.x; b < k; b += kSolveThreads) {
+    host[1 + b] = h1[b];
+    host[1 + k + b] = h2[b];
+  }
 }
 
-// y = a x (+ y when acc).
-__global__ void k_axpy(int64_t n, double a, const double* x, double* y, int acc) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Per block the sum of its a_i^2.
+__global__ __launch_bounds__(kSolveThreads) void k_norm2(int64_t n, const double* __restrict__ a,
+                                                         double* __restrict__ npart) {
+  const int64_t i = (int64_t)blockIdx.x * kSolveThreads + threadIdx.x;
+  double q = i < n ? a[i] * a[i] : 0.0;
+  for (int off = 32; off > 0; off >>= 1) q += __shfl_down(q, off, 64);
+  __shared__ double red[kSolveThreads / 64];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = q;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = red[0];
+    for (int v = 1; v < kSolveThreads / 64; ++v) t += red[v];
+    npart[blockIdx.x] = t;
+  }
+}
+
+// x += sum_{b < k} y[b] V_b (b ascending).
+__global__ __launch_bounds__(kSolveThreads) void k_combine(int64_t n, int k, const double* __restrict__ V,
+                                                           const double* __restrict__ y, double* __restrict__ x) {
+  const int64_t i = (int64_t)blockIdx.x * kSolveThreads + threadIdx.x;
   if (i >= n) return;
-  y[i] = acc ? fma(a, x[i], y[i]) : a * x[i];
+  double s = x[i];
+  int b = 0;
+  for (; b + 8 <= k; b += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = V[(int64_t)(b + u) * n + i];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s = fma(y[b + u], v[u], s);
+  }
+  for (; b < k; ++b) s = fma(y[b], V[(int64_t)b * n + i], s);
+  x[i] = s;
 }
 
 // r = b - r (r holds A x).
@@ -289,35 +394,44 @@ stb_status stb_solve_gmres(stb_ctx* ctx, const stb_mat* A, const double* b_host,
   if (iters) *iters = 0;
   if (relres) *relres = 0.0;
   if (n == 0) return STB_OK;
-  double *V = nullptr, *w = nullptr, *b = nullptr, *x = nullptr, *h = nullptr, *h2 = nullptr;
-  auto cleanup = [&]() { dfree(V); dfree(w); dfree(b); dfree(x); dfree(h); dfree(h2); };
-  if (dalloc(&V, (size_t)(m + 1) * n) != hipSuccess || dalloc(&w, (size_t)n) != hipSuccess ||
-      dalloc(&b, (size_t)n) != hipSuccess || dalloc(&x, (size_t)n) != hipSuccess ||
-      dalloc(&h, (size_t)m + 1) != hipSuccess || dalloc(&h2, (size_t)m + 1) != hipSuccess) {
+  // the basis is a block lent by the context; the rest is one allocation
+  const unsigned g = (unsigned)((n + kSolveThreads - 1) / kSolveThreads);
+  const int64_t nch = (n + kGsChunk - 1) / kGsChunk;
+  const size_t need = (size_t)(3 * n + (m + 1) * nch + g + 3 * (m + 1));
+  double *V = nullptr, *buf = nullptr;
+  auto cleanup = [&]() { ctx_keep(ctx, V); ctx_keep(ctx, buf); };
+  if (kalloc(ctx, &V, (size_t)(m + 1) * n) != hipSuccess || kalloc(ctx, &buf, need) != hipSuccess) {
     cleanup();
     return stb_fail(ctx, STB_E_NO_MEMORY, "GMRES basis of %d vectors of %lld", m + 1, (long long)n);
   }
-  const unsigned g = (unsigned)((n + 255) / 256);
+  double *w = buf, *b = w + n, *x = b + n, *part = x + n, *npart = part + (m + 1) * nch, *h1 = npart + g,
+         *h2 = h1 + (m + 1), *yd = h2 + (m + 1);
   stb_status s = STB_OK;
-  hipError_t e = hipMemcpyAsync(b, b_host, sizeof(double) * n, hipMemcpyHostToDevice, st);
+  hipError_t e = hipSuccess;
+  if (!ctx->h_pin) e = hipHostMalloc((void**)&ctx->h_pin, sizeof(double) * kPinDoubles);
+  double* host = ctx->h_pin;
+  static_assert(kPinDoubles >= 1 + 2 * kMaxBasis, "a step's coefficients fit the pinned block");
+  if (e == hipSuccess) e = hipMemcpyAsync(b, b_host, sizeof(double) * n, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(x, x_host, sizeof(double) * n, hipMemcpyHostToDevice, st);
   if (e != hipSuccess) { cleanup(); return stb_fail(ctx, STB_E_DEVICE, "GMRES copy: %s", hipGetErrorString(e)); }
-  // one device scalar read back per reduction
-  auto dot = [&](const double* u, const double* v, double* out) -> stb_status {
-    hipLaunchKernelGGL(k_dots, dim3(1), dim3(kSolveThreads), 0, st, n, u, n, v, h2);
-    hipError_t ee = hipMemcpyAsync(out, h2, sizeof(double), hipMemcpyDeviceToHost, st);
+  // |u|^2 to the host and u / |u| to `out`
+  auto normalise = [&](const double* u, double* out, double* n2) -> stb_status {
+    hipLaunchKernelGGL(k_norm2, dim3(g), dim3(kSolveThreads), 0, st, n, u, npart);
+    hipLaunchKernelGGL(k_gs_scale, dim3(g), dim3(kSolveThreads), 0, st, n, (int64_t)g, npart, u, out, 0, h1, h2, host);
+    hipError_t ee = hipGetLastError();
     if (ee == hipSuccess) ee = hipStreamSynchronize(st);
-    return ee == hipSuccess ? STB_OK : stb_fail(ctx, STB_E_DEVICE, "GMRES dot: %s", hipGetErrorString(ee));
+    *n2 = host[0];
+    return ee == hipSuccess ? STB_OK : stb_fail(ctx, STB_E_DEVICE, "GMRES norm: %s", hipGetErrorString(ee));
   };
   double bnorm2 = 0.0;
-  if ((s = dot(b, b, &bnorm2))) { cleanup(); return s; }
+  if ((s = normalise(b, V, &bnorm2))) { cleanup(); return s; }
   const double bnorm = std::sqrt(bnorm2);
   if (bnorm == 0.0) {
     for (int64_t i = 0; i < n; ++i) x_host[i] = 0.0;
     cleanup();
     return STB_OK;
   }
-  std::vector<double> H((size_t)(m + 1) * m, 0.0), cs(m), sn(m), gv(m + 1), y(m), hh(m + 1), hh2(m + 1);
+  std::vector<double> H((size_t)(m + 1) * m, 0.0), cs(m), sn(m), gv(m + 1), y(m);
   int total = 0;
   double res = 0.0;
   for (;;) {
@@ -325,32 +439,39 @@ stb_status stb_solve_gmres(stb_ctx* ctx, const stb_mat* A, const double* b_host,
     if ((s = stb_apply_dev(ctx, A, 1, x, w, st))) break;
     hipLaunchKernelGGL(k_residual, dim3(g), dim3(256), 0, st, n, b, w);
     double rn2 = 0.0;
-    if ((s = dot(w, w, &rn2))) break;
+    if ((s = normalise(w, V, &rn2))) break;
     const double rn = std::sqrt(rn2);
     res = rn / bnorm;
     if (res <= rtol || total >= maxit) break;
-    hipLaunchKernelGGL(k_axpy, dim3(g), dim3(256), 0, st, n, 1.0 / rn, w, V, 0);
     std::fill(gv.begin(), gv.end(), 0.0);
     gv[0] = rn;
     int j = 0;
+    bool ahead = false;   // the product A V_j is already enqueued
     for (; j < m && total < maxit; ++j, ++total) {
       double* vj1 = V + (int64_t)(j + 1) * n;
-      if ((s = stb_apply_dev(ctx, A, 1, V + (int64_t)j * n, vj1, st))) break;
-      // classical Gram-Schmidt, twice
-      for (int pass = 0; pass < 2 && s == STB_OK; ++pass) {
-        hipLaunchKernelGGL(k_dots, dim3((unsigned)(j + 1)), dim3(kSolveThreads), 0, st, n, V, n, vj1, h);
-        hipLaunchKernelGGL(k_subtract, dim3(g), dim3(256), 0, st, n, j + 1, V, n, h, vj1);
-        e = hipMemcpyAsync(pass == 0 ? hh.data() : hh2.data(), h, sizeof(double) * (j + 1),
-                           hipMemcpyDeviceToHost, st);
-        if (e != hipSuccess) s = stb_fail(ctx, STB_E_DEVICE, "GMRES: %s", hipGetErrorString(e));
+      if (!ahead && (s = stb_apply_dev(ctx, A, 1, V + (int64_t)j * n, vj1, st))) break;
+      // classical Gram-Schmidt, twice, then the norm and V_{j+1}
+      const int k = j + 1;
+      const dim3 gd((unsigned)nch, (unsigned)((k + kSolveThreads / 64 - 1) / (kSolveThreads / 64)));
+      for (int pass = 0; pass < 2; ++pass) {
+        hipLaunchKernelGGL(k_gs_dots, gd, dim3(kSolveThreads), 0, st, n, k, V, vj1, part);
+        hipLaunchKernelGGL(k_gs_sub, dim3(g), dim3(kSolveThreads), 0, st, n, k, nch, V, part, vj1,
+                           pass == 0 ? h1 : h2, pass == 0 ? nullptr : npart);
       }
+      hipLaunchKernelGGL(k_gs_scale, dim3(g), dim3(kSolveThreads), 0, st, n, (int64_t)g, npart, vj1, vj1, k, h1, h2,
+                         host);
+      if ((e = hipGetLastError()) == hipSuccess) e = hipEventRecord(ctx->ev[4], st);
+      // the next product runs while the host waits for this step's
+      // coefficients (unused if the step turns out to be the last)
+      ahead = j + 1 < m && total + 1 < maxit;
+      if (e == hipSuccess && ahead) s = stb_apply_dev(ctx, A, 1, vj1, vj1 + n, st);
+      if (e == hipSuccess) e = hipEventSynchronize(ctx->ev[4]);
+      if (e != hipSuccess) s = stb_fail(ctx, STB_E_DEVICE, "GMRES step: %s", hipGetErrorString(e));
       if (s) break;
-      double hn2 = 0.0;
-      if ((s = dot(vj1, vj1, &hn2))) break;   // synchronises: hh, hh2 are on the host now
-      for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = hh[i] + hh2[i];
+      const double hn2 = host[0];
+      for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = host[1 + i] + host[1 + k + i];
       const double hn = std::sqrt(hn2);
       H[(size_t)(j + 1) * m + j] = hn;
-      if (hn > 0.0) hipLaunchKernelGGL(k_axpy, dim3(g), dim3(256), 0, st, n, 1.0 / hn, vj1, vj1, 0);
       // apply the previous rotations, then a new one for row j + 1
       for (int i = 0; i < j; ++i) {
         const double a = H[(size_t)i * m + j], c = H[(size_t)(i + 1) * m + j];
@@ -374,15 +495,19 @@ stb_status stb_solve_gmres(stb_ctx* ctx, const stb_mat* A, const double* b_host,
       for (int k = i + 1; k < j; ++k) t -= H[(size_t)i * m + k] * y[k];
       y[i] = H[(size_t)i * m + i] != 0.0 ? t / H[(size_t)i * m + i] : 0.0;
     }
-    for (int i = 0; i < j; ++i)
-      hipLaunchKernelGGL(k_axpy, dim3(g), dim3(256), 0, st, n, y[i], V + (int64_t)i * n, x, 1);
-    e = hipGetLastError();
+    e = hipMemcpyAsync(yd, y.data(), sizeof(double) * j, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) {
+      hipLaunchKernelGGL(k_combine, dim3(g), dim3(kSolveThreads), 0, st, n, j, V, yd, x);
+      e = hipGetLastError();
+    }
     if (e != hipSuccess) { s = stb_fail(ctx, STB_E_DEVICE, "GMRES: %s", hipGetErrorString(e)); break; }
   }
   if (s == STB_OK) {
     e = hipMemcpyAsync(x_host, x, sizeof(double) * n, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) s = stb_fail(ctx, STB_E_DEVICE, "GMRES copy: %s", hipGetErrorString(e));
+  } else {
+    (void)hipStreamSynchronize(st);   // nothing enqueued may outlive the buffers
   }
   cleanup();
   if (s) return s;

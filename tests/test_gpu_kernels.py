@@ -54,3 +54,39 @@ def test_product_with_column_parts(stb, ctx, level, slabs):
         assert np.all(np.abs(Y[rows] - ref) <= (bound[:, None] * scale if nrhs > 1 else bound * scale))
     A.close()
     M.close()
+
+
+# fewer unknowns than a chunk of the dot products, a remainder chunk, restarts
+# shorter and longer than the vectors subtracted at once
+@pytest.mark.parametrize("slabs,restart", [(1, 1), (6, 5), (6, 100), (18, 8), (18, 9), (18, 100)])
+def test_gmres_restarts(stb, ctx, slabs, restart):
+    mesh = inputs.icosphere_mesh(0, slabs, T=2.0)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    A = stb.assemble_V(ctx, M)
+    D = A.to_dense()
+    b = D @ np.random.default_rng(slabs).standard_normal(A.n)
+    x, its, rel = stb.solve_gmres(ctx, A, b, restart=restart, maxit=40, rtol=1e-10)
+    assert its <= 40
+    # the reported residual is the true one: the product's rounding error aside
+    true = np.linalg.norm(b - D @ x) / np.linalg.norm(b)
+    slack = A.n * EPS * 2 * np.linalg.norm(np.abs(D) @ np.abs(x)) / np.linalg.norm(b)
+    assert abs(true - rel) <= slack + 1e-12 * rel
+    # no more work than asked: one more product than steps at most, and a longer
+    # search never ends with a larger residual
+    x2, its2, rel2 = stb.solve_gmres(ctx, A, b, restart=restart, maxit=39, rtol=1e-10)
+    assert its2 <= 39 and rel <= rel2 * (1 + 1e-9) + slack
+    if restart == 100 and slabs <= 6:
+        # the minimal residual over the Krylov space itself
+        k = min(its, 20)
+        x3, its3, rel3 = stb.solve_gmres(ctx, A, b, restart=restart, maxit=k, rtol=1e-14)
+        Q = np.zeros((A.n, k))
+        v = b / np.linalg.norm(b)
+        for i in range(k):
+            Q[:, i] = v
+            v = D @ v
+            for _ in range(2):
+                v -= Q[:, :i + 1] @ (Q[:, :i + 1].T @ v)
+            v /= np.linalg.norm(v)
+        z, *_ = np.linalg.lstsq(D @ Q, b, rcond=None)
+        best = np.linalg.norm(b - D @ (Q @ z)) / np.linalg.norm(b)
+        assert abs(rel3 - best) <= 1e-8 * best + slack
