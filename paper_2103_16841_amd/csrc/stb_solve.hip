@@ -186,120 +186,276 @@ __global__ void k_mot_block(int64_t K, const int32_t* __restrict__ rows0, const 
                             const int32_t* __restrict__ cols, const double* __restrict__ vals,
                             const int32_t* __restrict__ slab, const int32_t* __restrict__ loc,
                             double* __restrict__ D) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;   // one wavefront per row
   if (k >= K) return;
   const int32_t i = rows0[k];
-  for (int64_t e = rowptr[i]; e < rowptr[i + 1]; ++e) {
+  for (int64_t e = rowptr[i] + (threadIdx.x & 63); e < rowptr[i + 1]; e += 64) {
     const int32_t j = cols[e];
     if (slab[j] == 0) D[k * K + loc[j]] = vals[e];
   }
 }
 
 // Every stored entry (i, j) has slab[j] <= slab[i] (block lower triangular
-// in time); bad[0] counts the entries that do not.
-__global__ void k_mot_lower(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ cols,
-                            const int32_t* __restrict__ slab, unsigned long long* __restrict__ bad) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// in time); bad[0] counts the entries that do not.  One wavefront per row.
+__global__ __launch_bounds__(256) void k_mot_lower(int64_t n, const int64_t* __restrict__ rowptr,
+                                                   const int32_t* __restrict__ cols,
+                                                   const int32_t* __restrict__ slab,
+                                                   unsigned long long* __restrict__ bad) {
+  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (i >= n) return;
-  unsigned long long c = 0;
-  for (int64_t e = rowptr[i]; e < rowptr[i + 1]; ++e) c += slab[cols[e]] > slab[i] ? 1ull : 0ull;
-  if (c) atomicAdd(bad, c);
+  const int lane = threadIdx.x & 63;
+  const int32_t own = slab[i];
+  const int64_t e = rowptr[i + 1];
+  unsigned c = 0;
+  int64_t k = rowptr[i] + lane;
+  for (; k + 192 < e; k += 256) {
+    const int32_t j0 = cols[k], j1 = cols[k + 64], j2 = cols[k + 128], j3 = cols[k + 192];
+    c += (slab[j0] > own ? 1u : 0u) + (slab[j1] > own ? 1u : 0u) + (slab[j2] > own ? 1u : 0u) +
+         (slab[j3] > own ? 1u : 0u);
+  }
+  for (; k < e; k += 64) c += slab[cols[k]] > own ? 1u : 0u;
+  for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off, 64);
+  if (lane == 0 && c) atomicAdd(bad, (unsigned long long)c);
 }
 
-// Gauss-Jordan inversion of D (K x K, row-major) in place, pivot step k,
-// part 1 (one workgroup): partial pivot (largest |D[i][k]|, i >= k, first
-// such i), row swap, scaling of the pivot row, the column's multipliers
-// into f (f[k] = 0) and column k cleared outside the pivot row.
-constexpr int kGjThreads = 1024;
-__global__ __launch_bounds__(kGjThreads) void k_gj_pivot(int64_t K, int64_t k, double* __restrict__ D,
-                                                         int32_t* __restrict__ perm, double* __restrict__ f,
-                                                         int* __restrict__ singular) {
-  __shared__ double sv[kGjThreads];
-  __shared__ int64_t si[kGjThreads];
-  double best = -1.0;
-  int64_t bi = k;
-  for (int64_t i = k + threadIdx.x; i < K; i += kGjThreads) {
-    const double v = fabs(D[i * K + k]);
-    if (v > best) { best = v; bi = i; }
-  }
-  sv[threadIdx.x] = best;
-  si[threadIdx.x] = bi;
-  __syncthreads();
-  for (int off = kGjThreads / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      const double a = sv[threadIdx.x], b = sv[threadIdx.x + off];
-      const int64_t ia = si[threadIdx.x], ib = si[threadIdx.x + off];
-      if (b > a || (b == a && ib < ia)) { sv[threadIdx.x] = b; si[threadIdx.x] = ib; }
+// Gauss-Jordan inversion of D (K x K, row-major) in place, NB columns at a
+// time, with partial pivoting and no row interchanges: pivot k sits in a row
+// p_k not used before, and the array ends as B[p_k][j] = (P D)^-1[k][j], so
+// D^-1[k][p_j] = B[p_k][j] (k_gj_permute).
+//
+// Panel step (one workgroup): the NB columns from k0 on, the thread's RPT rows
+// in registers; per column the pivot search over the unused rows and one
+// elimination of the panel's columns, the pivot row passed through LDS.  Then
+// the pivot rows' other columns, as they were, go to rbuf.  The step is a
+// serial chain, so it runs on as few wavefronts as hold the rows (one per
+// SIMD up to K = 1024), and pivots are compared by the upper halves of |D|
+// (20 bits of mantissa) with one DPP maximum over the wave: a pivot within 1e-6 of
+// the largest is as stable as the largest.  K = 960: eliminating the whole
+// matrix column by column took two launches a column, 6.2 + 3.8 us; this
+// panel with 16 waves and exact (value, row) shuffles 4.5 us a column, as it
+// stands 2.5 us.
+//
+// Maximum over the wavefront of a non-negative key (DPP row shifts, then the
+// two row broadcasts; lane 63 holds it).
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  auto step = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
+  v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));   // row_shr:1
+  v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));   // row_shr:2
+  v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));   // row_shr:4
+  v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));   // row_shr:8
+  v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast:15
+  v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));   // row_bcast:31
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+template <int T, int RPT, int NB>
+__global__ __launch_bounds__(T) void k_gj_panel(int64_t K, int64_t k0, double* __restrict__ D,
+                                                int32_t* __restrict__ piv, uint8_t* __restrict__ used,
+                                                double* __restrict__ rbuf, int* __restrict__ singular) {
+  constexpr int kWaves = T / 64;
+  const int nb = (int)(K - k0 < NB ? K - k0 : NB);
+  const bool wide = nb == NB && (K & 1) == 0;   // whole panel, rows 16-byte aligned
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ uint32_t s_key[kWaves];
+  __shared__ int32_t s_idx[kWaves], s_piv[NB];
+  __shared__ double s_row[NB];
+  double A[RPT][NB];
+  bool free_row[RPT];
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    const int64_t i = threadIdx.x + (int64_t)r * T;
+    free_row[r] = i < K && !used[i];
+    if (i < K && wide) {
+      const double2* d = reinterpret_cast<const double2*>(D + i * K + k0);
+#pragma unroll
+      for (int c = 0; c < NB; c += 2) {
+        const double2 v = d[c / 2];
+        A[r][c] = v.x;
+        A[r][c + 1] = v.y;
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < NB; ++c) A[r][c] = i < K && c < nb ? D[i * K + k0 + c] : 0.0;
     }
-    __syncthreads();
   }
-  const int64_t p = si[0];
-  if (threadIdx.x == 0) {
-    perm[k] = (int32_t)p;
-    if (!(sv[0] > 0.0)) *singular = 1;
-  }
-  if (p != k)
-    for (int64_t j = threadIdx.x; j < K; j += kGjThreads) {
-      const double t = D[k * K + j];
-      D[k * K + j] = D[p * K + j];
-      D[p * K + j] = t;
+#pragma unroll
+  for (int c = 0; c < NB; ++c)
+    if (c < nb) {
+      // key of an unused row: 1 + the upper half of |entry| (1 for a NaN or an
+      // infinity, so that there always is a pivot); 0 for the others
+      uint32_t best = 0;
+      int32_t bi = 0;
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        const uint32_t h = (uint32_t)__double2hiint(A[r][c]) & 0x7fffffffu;
+        const uint32_t key = free_row[r] ? (h < 0x7ff00000u ? h : 0u) + 1u : 0u;
+        bi = key > best ? (int32_t)(threadIdx.x + r * T) : bi;
+        best = key > best ? key : best;
+      }
+      const uint32_t top = wave_max(best);
+      const uint64_t at = __ballot(best == top);
+      if (lane == __ffsll((long long)at) - 1) {
+        s_key[wave] = top;
+        s_idx[wave] = bi;
+      }
+      __syncthreads();
+      best = s_key[0];
+      bi = s_idx[0];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) {
+        const uint32_t k = s_key[w];
+        bi = k > best ? s_idx[w] : bi;
+        best = k > best ? k : best;
+      }
+      // the pivot row's owner scales it and passes it on
+#pragma unroll
+      for (int r = 0; r < RPT; ++r)
+        if (threadIdx.x + r * T == (unsigned)bi) {
+          const double inv = A[r][c] != 0.0 ? stb::frcp(A[r][c]) : 0.0;
+          if (A[r][c] == 0.0) *singular = 1;
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            A[r][j] = (j == c ? 1.0 : A[r][j]) * inv;
+            s_row[j] = A[r][j];
+          }
+          free_row[r] = false;
+          used[bi] = 1;
+          s_piv[c] = bi;
+          piv[k0 + c] = bi;
+        }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < RPT; ++r)
+        if (threadIdx.x + r * T != (unsigned)bi) {
+          const double f = A[r][c];
+#pragma unroll
+          for (int j = 0; j < NB; ++j) A[r][j] = j == c ? -f * s_row[j] : fma(-f, s_row[j], A[r][j]);
+        }
     }
-  __syncthreads();
-  const double piv = D[k * K + k];
-  const double inv = sv[0] > 0.0 ? 1.0 / piv : 0.0;
-  __syncthreads();
-  for (int64_t j = threadIdx.x; j < K; j += kGjThreads) {
-    const double v = j == k ? 1.0 : D[k * K + j];
-    D[k * K + j] = v * inv;
+  for (int64_t j = threadIdx.x; j < K; j += T) {
+    double v[NB];
+#pragma unroll
+    for (int c = 0; c < NB; ++c) v[c] = c < nb ? D[(int64_t)s_piv[c] * K + j] : 0.0;
+#pragma unroll
+    for (int c = 0; c < NB; ++c)
+      if (c < nb) rbuf[(int64_t)c * K + j] = v[c];
   }
-  for (int64_t i = threadIdx.x; i < K; i += kGjThreads) {
-    if (i == k) { f[i] = 0.0; continue; }
-    f[i] = D[i * K + k];
-    D[i * K + k] = 0.0;
+  __syncthreads();   // (the panel's own columns of rbuf are not used)
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    const int64_t i = threadIdx.x + (int64_t)r * T;
+    if (i < K && wide) {
+      double2* d = reinterpret_cast<double2*>(D + i * K + k0);
+#pragma unroll
+      for (int c = 0; c < NB; c += 2) d[c / 2] = make_double2(A[r][c], A[r][c + 1]);
+    } else if (i < K) {
+#pragma unroll
+      for (int c = 0; c < NB; ++c)
+        if (c < nb) D[i * K + k0 + c] = A[r][c];
+    }
   }
 }
 
-// Part 2: D[i][j] -= f[i] D[k][j] for every row i != k (row k is read only).
-__global__ void k_gj_update(int64_t K, int64_t k, double* __restrict__ D, const double* __restrict__ f) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= K * K) return;
-  const int64_t i = e / K, j = e - i * K;
-  const double fi = f[i];
-  if (fi != 0.0) D[e] = fma(-fi, D[k * K + j], D[e]);
-}
-
-// Undo the row interchanges on the inverse: its columns k and perm[k] swap,
-// k from K - 1 down to 0 (one lane per row).
-__global__ void k_gj_unswap(int64_t K, double* __restrict__ D, const int32_t* __restrict__ perm) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= K) return;
-  for (int64_t k = K - 1; k >= 0; --k) {
-    const int64_t p = perm[k];
-    if (p != k) {
-      const double t = D[i * K + k];
-      D[i * K + k] = D[i * K + p];
-      D[i * K + p] = t;
-    }
+// The other columns: D[i][j] = D[i][j] + sum_c panel[i][c] rbuf[c][j], without
+// the old D[i][j] in the panel's pivot rows.  Tiles of kGjRows rows by 256
+// columns, the rows' panel entries in LDS.
+constexpr int kGjRows = 8;
+template <int NB>
+__global__ __launch_bounds__(256) void k_gj_update(int64_t K, int64_t k0, double* __restrict__ D,
+                                                   const double* __restrict__ rbuf, const int32_t* __restrict__ piv) {
+  const int nb = (int)(K - k0 < NB ? K - k0 : NB);
+  const int64_t i0 = (int64_t)blockIdx.y * kGjRows, j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  __shared__ double s_p[kGjRows][NB];
+  __shared__ int s_piv[kGjRows];
+  for (int g = threadIdx.x; g < kGjRows * NB; g += 256) {
+    const int r = g / NB, c = g - r * NB;
+    s_p[r][c] = i0 + r < K && c < nb ? D[(i0 + r) * K + k0 + c] : 0.0;
+  }
+  if (threadIdx.x < kGjRows) {
+    int is = 0;
+    for (int c = 0; c < nb; ++c) is |= piv[k0 + c] == (int32_t)(i0 + threadIdx.x) ? 1 : 0;
+    s_piv[threadIdx.x] = is;
+  }
+  __syncthreads();
+  if (j >= K || (j >= k0 && j < k0 + nb)) return;
+  double b[NB];
+#pragma unroll
+  for (int c = 0; c < NB; ++c) b[c] = c < nb ? rbuf[(int64_t)c * K + j] : 0.0;
+#pragma unroll 4
+  for (int r = 0; r < kGjRows; ++r) {
+    if (i0 + r >= K) break;
+    double s = s_piv[r] ? 0.0 : D[(i0 + r) * K + j];
+#pragma unroll
+    for (int c = 0; c < NB; ++c) s = fma(s_p[r][c], b[c], s);
+    D[(i0 + r) * K + j] = s;
   }
 }
+
+// out[k][p_j] = B[p_k][j].
+__global__ __launch_bounds__(256) void k_gj_permute(int64_t K, const double* __restrict__ B,
+                                                    const int32_t* __restrict__ piv, double* __restrict__ out) {
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x, k = blockIdx.y;
+  if (j < K) out[k * K + piv[j]] = B[(int64_t)piv[k] * K + j];
+}
+
+template <int T, int RPT, int NB>
+hipError_t gj_steps(int64_t K, double* D, int32_t* piv, uint8_t* used, double* rbuf, int* sing, hipStream_t st) {
+  const dim3 gu((unsigned)((K + 255) / 256), (unsigned)((K + kGjRows - 1) / kGjRows));
+  for (int64_t k0 = 0; k0 < K; k0 += NB) {
+    hipLaunchKernelGGL((k_gj_panel<T, RPT, NB>), dim3(1), dim3(T), 0, st, K, k0, D, piv, used, rbuf, sing);
+    if (K > NB) hipLaunchKernelGGL((k_gj_update<NB>), gu, dim3(256), 0, st, K, k0, D, rbuf, piv);
+  }
+  return hipGetLastError();
+}
+
+// Enqueues out = D^-1 (D is overwritten); used: K zeros, rbuf: 16 K doubles.  A
+// panel's rows stay in one workgroup's registers, so the panels narrow as K
+// grows.
+hipError_t gj_invert(int64_t K, double* D, double* out, int32_t* piv, uint8_t* used, double* rbuf, int* sing,
+                     hipStream_t st) {
+  hipError_t e = K <= 1024   ? gj_steps<256, 4, 16>(K, D, piv, used, rbuf, sing, st)
+                 : K <= 2048 ? gj_steps<512, 4, 16>(K, D, piv, used, rbuf, sing, st)
+                 : K <= 4096 ? gj_steps<1024, 4, 8>(K, D, piv, used, rbuf, sing, st)
+                 : K <= 8192 ? gj_steps<1024, 8, 4>(K, D, piv, used, rbuf, sing, st)
+                             : gj_steps<1024, 16, 2>(K, D, piv, used, rbuf, sing, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_gj_permute, dim3((unsigned)((K + 255) / 256), (unsigned)K), dim3(256), 0, st, K, D, piv, out);
+  return hipGetLastError();
+}
+constexpr int64_t kMotMaxPanels = 16 * 1024;
 
 // Time step n, part 1: r[k] = b[i] - sum_j A[i][j] x[j] for the rows i =
 // rows[k] of the slab (x is zero on this and later slabs, so this is
-// b_n - sum_{m<n} A_nm x_m); one wavefront per row, fixed-order reduction.
+// b_n - sum_{m<n} A_nm x_m); one workgroup per row (a slab has few rows, so
+// one wavefront each left the chip idle: 26 us a step at K = 960), fixed-order
+// reduction.
 __global__ __launch_bounds__(256) void k_mot_rhs(int64_t K, const int32_t* __restrict__ rows,
                                                  const int64_t* __restrict__ rowptr,
                                                  const int32_t* __restrict__ cols,
                                                  const double* __restrict__ vals,
                                                  const double* __restrict__ x, const double* __restrict__ b,
                                                  double* __restrict__ r) {
-  const int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (k >= K) return;
+  const int64_t k = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int32_t i = rows[k];
-  double s = 0.0;
-  for (int64_t e = rowptr[i] + lane; e < rowptr[i + 1]; e += 64) s += vals[e] * x[cols[e]];
+  const int64_t e = rowptr[i + 1];
+  int64_t q = rowptr[i] + threadIdx.x;
+  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+  for (; q + 768 < e; q += 1024) {
+    const int32_t c0 = cols[q], c1 = cols[q + 256], c2 = cols[q + 512], c3 = cols[q + 768];
+    const double v0 = vals[q], v1 = vals[q + 256], v2 = vals[q + 512], v3 = vals[q + 768];
+    s0 = fma(v0, x[c0], s0);
+    s1 = fma(v1, x[c1], s1);
+    s2 = fma(v2, x[c2], s2);
+    s3 = fma(v3, x[c3], s3);
+  }
+  for (; q < e; q += 256) s0 = fma(vals[q], x[cols[q]], s0);
+  double s = (s0 + s1) + (s2 + s3);
   for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  if (lane == 0) r[k] = b[i] - s;
+  __shared__ double red[4];
+  if (lane == 0) red[wave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) r[k] = b[i] - ((red[0] + red[1]) + (red[2] + red[3]));
 }
 
 // Part 2: x[rows[k]] = sum_l Dinv[k][l] r[l]; one wavefront per row.
@@ -309,8 +465,17 @@ __global__ __launch_bounds__(256) void k_mot_apply(int64_t K, const int32_t* __r
   const int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   if (k >= K) return;
-  double s = 0.0;
-  for (int64_t l = lane; l < K; l += 64) s += Dinv[k * K + l] * r[l];
+  const double* d = Dinv + k * K;
+  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+  int64_t l = lane;
+  for (; l + 192 < K; l += 256) {
+    s0 = fma(d[l], r[l], s0);
+    s1 = fma(d[l + 64], r[l + 64], s1);
+    s2 = fma(d[l + 128], r[l + 128], s2);
+    s3 = fma(d[l + 192], r[l + 192], s3);
+  }
+  for (; l < K; l += 64) s0 = fma(d[l], r[l], s0);
+  double s = (s0 + s1) + (s2 + s3);
   for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
   if (lane == 0) x[rows[k]] = s;
 }
@@ -579,7 +744,8 @@ stb_status stb_solve_mot(stb_ctx* ctx, const stb_mesh* mesh, const stb_mat* A, c
     if ((int64_t)rows[(size_t)n].size() != K)
       return stb_fail(ctx, STB_E_INVALID_ARG, "slab %lld has %lld panels, slab 0 has %lld: use GMRES",
                       (long long)n, (long long)rows[(size_t)n].size(), (long long)K);
-  if (K > 16384) return stb_fail(ctx, STB_E_INVALID_ARG, "%lld panels per slab (at most 16384)", (long long)K);
+  static_assert(kMotMaxPanels == 16384, "the limit the interface states");
+  if (K > kMotMaxPanels) return stb_fail(ctx, STB_E_INVALID_ARG, "%lld panels per slab (at most 16384)", (long long)K);
   // slab n must be slab 0 moved by (lev_n - lev_0) in time, panel by panel
   for (int64_t n = 1; n < S; ++n) {
     const double shift = lev[(size_t)n] - lev[0];
@@ -601,17 +767,19 @@ stb_status stb_solve_mot(stb_ctx* ctx, const stb_mesh* mesh, const stb_mat* A, c
   std::vector<int32_t> rflat((size_t)(S * K));
   for (int64_t n = 0; n < S; ++n)
     std::copy(rows[(size_t)n].begin(), rows[(size_t)n].end(), rflat.begin() + n * K);
-  int32_t *d_slab = nullptr, *d_loc = nullptr, *d_rows = nullptr, *d_perm = nullptr;
-  double *D = nullptr, *f = nullptr, *x = nullptr, *b = nullptr, *r = nullptr;
+  int32_t *d_slab = nullptr, *d_loc = nullptr, *d_rows = nullptr, *d_piv = nullptr;
+  uint8_t* d_used = nullptr;
+  double *D = nullptr, *Dinv = nullptr, *rbuf = nullptr, *x = nullptr, *b = nullptr, *r = nullptr;
   unsigned long long* d_bad = nullptr;
   int* d_sing = nullptr;
   auto cleanup = [&]() {
-    dfree(d_slab); dfree(d_loc); dfree(d_rows); dfree(d_perm); dfree(D); dfree(f); dfree(x); dfree(b);
-    dfree(r); dfree(d_bad); dfree(d_sing);
+    dfree(d_slab); dfree(d_loc); dfree(d_rows); dfree(d_piv); dfree(d_used); ctx_keep(ctx, D); ctx_keep(ctx, Dinv);
+    dfree(rbuf); dfree(x); dfree(b); dfree(r); dfree(d_bad); dfree(d_sing);
   };
   if (dalloc(&d_slab, (size_t)nt) != hipSuccess || dalloc(&d_loc, (size_t)nt) != hipSuccess ||
-      dalloc(&d_rows, (size_t)(S * K)) != hipSuccess || dalloc(&d_perm, (size_t)K) != hipSuccess ||
-      dalloc(&D, (size_t)(K * K)) != hipSuccess || dalloc(&f, (size_t)K) != hipSuccess ||
+      dalloc(&d_rows, (size_t)(S * K)) != hipSuccess || dalloc(&d_piv, (size_t)K) != hipSuccess ||
+      dalloc(&d_used, (size_t)K) != hipSuccess || kalloc(ctx, &D, (size_t)(K * K)) != hipSuccess ||
+      kalloc(ctx, &Dinv, (size_t)(K * K)) != hipSuccess || dalloc(&rbuf, (size_t)(16 * K)) != hipSuccess ||
       dalloc(&x, (size_t)nt) != hipSuccess || dalloc(&b, (size_t)nt) != hipSuccess ||
       dalloc(&r, (size_t)K) != hipSuccess || dalloc(&d_bad, 1) != hipSuccess || dalloc(&d_sing, 1) != hipSuccess) {
     cleanup();
@@ -624,11 +792,12 @@ stb_status stb_solve_mot(stb_ctx* ctx, const stb_mesh* mesh, const stb_mat* A, c
   if (e == hipSuccess) e = hipMemsetAsync(d_bad, 0, 8, st);
   if (e == hipSuccess) e = hipMemsetAsync(d_sing, 0, sizeof(int), st);
   if (e == hipSuccess) e = hipMemsetAsync(D, 0, 8 * K * K, st);
+  if (e == hipSuccess) e = hipMemsetAsync(d_used, 0, K, st);
   if (e == hipSuccess) e = hipMemsetAsync(x, 0, 8 * nt, st);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_mot_lower, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, nt, A->d_rowptr,
+    hipLaunchKernelGGL(k_mot_lower, dim3((unsigned)((nt * 64 + 255) / 256)), dim3(256), 0, st, nt, A->d_rowptr,
                        A->d_cols, d_slab, d_bad);
-    hipLaunchKernelGGL(k_mot_block, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, K, d_rows,
+    hipLaunchKernelGGL(k_mot_block, dim3((unsigned)((K * 64 + 255) / 256)), dim3(256), 0, st, K, d_rows,
                        A->d_rowptr, A->d_cols, A->d_vals, d_slab, d_loc, D);
     e = hipGetLastError();
   }
@@ -643,16 +812,7 @@ stb_status stb_solve_mot(stb_ctx* ctx, const stb_mesh* mesh, const stb_mat* A, c
                     bad);
   }
   const auto c0 = std::chrono::steady_clock::now();
-  const unsigned gu = (unsigned)((K * K + 255) / 256);
-  for (int64_t k = 0; k < K && e == hipSuccess; ++k) {
-    hipLaunchKernelGGL(k_gj_pivot, dim3(1), dim3(kGjThreads), 0, st, K, k, D, d_perm, f, d_sing);
-    hipLaunchKernelGGL(k_gj_update, dim3(gu), dim3(256), 0, st, K, k, D, f);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_gj_unswap, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, K, D, d_perm);
-    e = hipGetLastError();
-  }
+  e = gj_invert(K, D, Dinv, d_piv, d_used, rbuf, d_sing, st);
   int sing = 0;
   if (e == hipSuccess) e = hipMemcpyAsync(&sing, d_sing, sizeof(int), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -660,9 +820,9 @@ stb_status stb_solve_mot(stb_ctx* ctx, const stb_mesh* mesh, const stb_mat* A, c
   if (e == hipSuccess && !sing) {
     const unsigned gw = (unsigned)((K * 64 + 255) / 256);
     for (int64_t n = 0; n < S && e == hipSuccess; ++n) {
-      hipLaunchKernelGGL(k_mot_rhs, dim3(gw), dim3(256), 0, st, K, d_rows + n * K, A->d_rowptr, A->d_cols,
+      hipLaunchKernelGGL(k_mot_rhs, dim3((unsigned)K), dim3(256), 0, st, K, d_rows + n * K, A->d_rowptr, A->d_cols,
                          A->d_vals, x, b, r);
-      hipLaunchKernelGGL(k_mot_apply, dim3(gw), dim3(256), 0, st, K, d_rows + n * K, D, r, x);
+      hipLaunchKernelGGL(k_mot_apply, dim3(gw), dim3(256), 0, st, K, d_rows + n * K, Dinv, r, x);
       e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(x_host, x, 8 * nt, hipMemcpyDeviceToHost, st);

@@ -90,3 +90,35 @@ def test_gmres_restarts(stb, ctx, slabs, restart):
         z, *_ = np.linalg.lstsq(D @ Q, b, rcond=None)
         best = np.linalg.norm(b - D @ (Q @ z)) / np.linalg.norm(b)
         assert abs(rel3 - best) <= 1e-8 * best + slack
+
+
+# K = 60 (fewer rows than a panel step's workgroup, a last panel of 12 columns), 12 and
+# 960 by the slabs' triangles; 1,280 and 5,120 take two and eight rows per lane
+@pytest.mark.parametrize("level,slabs", [(-1, 3), (0, 5), (2, 3), (3, 2)])
+def test_marching_equals_dense_solve(stb, ctx, level, slabs):
+    if level < 0:
+        mesh = inputs.cube_mesh(S=slabs, T=1.0)
+    else:
+        pts, tris = inputs.icosphere(level)
+        mesh = inputs.extrude(pts, tris, slabs, 0.5 * slabs)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    A = stb.assemble_V(ctx, M, stb.default_params(m_q=2, n_g=8))
+    rng = np.random.default_rng(level + 5)
+    b = A.apply(rng.standard_normal(A.n))
+    x, info = stb.solve_mot(ctx, M, A, b)
+    K = A.n // slabs
+    assert info["slabs"] == slabs and info["panels_per_slab"] == K
+    # the same marching in numpy: slab 0's diagonal block on every slab
+    lo = mesh.tet_coords()[:, :, 0].min(1)
+    idx = [np.where(np.isclose(lo, n * mesh.T / slabs))[0] for n in range(slabs)]
+    block = lambda i, j: A.get(np.repeat(i, len(j)).astype(np.int32), np.tile(j, len(i)).astype(np.int32)).reshape(len(i), -1)
+    D = block(idx[0], idx[0])
+    ref = np.zeros(A.n)
+    for n in range(slabs):
+        r = b[idx[n]].copy()
+        for m in range(n):
+            r -= block(idx[n], idx[m]) @ ref[idx[m]]
+        ref[idx[n]] = np.linalg.solve(D, r)
+    # a solve by an explicit inverse: a few K eps cond(D) of the block's size
+    cond = np.linalg.cond(D)
+    assert np.linalg.norm(x - ref) <= 8 * K * EPS * cond ** 2 * np.linalg.norm(ref)
