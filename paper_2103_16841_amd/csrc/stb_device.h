@@ -1304,6 +1304,35 @@ STB_HD __forceinline__ double rdiff2_node(double w0, double w1, double d2) {
   return (w1 - w0) * g;
 }
 
+// The double layer's r-integrals over one gap [w0, w1] (w1 >= w0 >= |d| > 0) at a
+// node, node-stage arithmetic: with n = w^2 + d^2 (1 / r = 2 w / n) and one
+// reciprocal of n0 n1,
+//   sa = 1/r0 - 1/r1 = 2 (w1 - w0) (w0 w1 - d^2) / (n0 n1),
+//   sh = ln(w1 / w0) + 2 d^2 (1/n1 - 1/n0)
+//      = ln(w1 / w0) - 2 d^2 (w1 - w0) (w1 + w0) / (n0 n1),
+// products where dl_eval has differences.  ln(w1 / w0) = 2 artanh(x), x = (w1 -
+// w0) / (w1 + w0), by its series to x^21 up to x = 1/6 (remainder below 2e-18),
+// else by the library.
+STB_HD __forceinline__ void dl_gap_node(double w0, double w1, double d2, double& sa, double& sh) {
+  const double dw = w1 - w0, sw = w1 + w0;
+  const double t = (2.0 * dw) * frcp_node(fma(w0, w0, d2) * fma(w1, w1, d2));
+  sa += t * fma(w0, w1, -d2);
+  const double x = dw * frcp_node(sw), y = x * x;
+  double p = 1.0 / 21.0;
+  p = fma_keep(p, y, 1.0 / 19.0);
+  p = fma_keep(p, y, 1.0 / 17.0);
+  p = fma_keep(p, y, 1.0 / 15.0);
+  p = fma_keep(p, y, 1.0 / 13.0);
+  p = fma_keep(p, y, 1.0 / 11.0);
+  p = fma_keep(p, y, 1.0 / 9.0);
+  p = fma_keep(p, y, 1.0 / 7.0);
+  p = fma_keep(p, y, 1.0 / 5.0);
+  p = fma_keep(p, y, 1.0 / 3.0);
+  double ln = 2.0 * fma(x * y, p, x);
+  if (x > 1.0 / 6.0) ln = log(w1 * frcp(w0));
+  sh += fma(-(d2 * sw), t, ln);
+}
+
 STB_HD __forceinline__ double endpoint_value_node(const Endpoint& E, double d2, double wlo, double whi,
                                                   double cs, double sn) {
   const double B = fma(E.fb, cs, E.fc * sn);

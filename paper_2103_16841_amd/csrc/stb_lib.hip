@@ -636,7 +636,7 @@ stb_status stb_cull_points(stb_ctx* ctx, stb_mesh* m, const stb_quad_params& p, 
   if (dalloc(&d_box, (size_t)std::max<int64_t>(np, 1)) != hipSuccess)
     return fail(ctx, STB_E_NO_MEMORY, "point boxes");
   stb_point_boxes(ctx, np, d_pts, d_box);
-  stb_status s = stb_cull(ctx, np, d_box, m, d_rowptr, d_cols, d_rowof, nnz);
+  stb_status s = stb_cull(ctx, np, d_box, m, d_rowptr, d_cols, d_rowof, nnz, true);
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   dfree(d_box);
   ctx->lit_search[0] = 0;
@@ -775,7 +775,7 @@ void ctx_keep(stb_ctx* ctx, void* p) {
   for (size_t k = 0; k < ctx->lent.size(); ++k)
     if (ctx->lent[k].first == p) {
       const size_t n = ctx->lent[k].second;
-      if (ctx->kept_bytes + n <= kKeptMaxBytes) {
+      if (ctx->kept_bytes + n <= ctx->kept_max) {
         ctx->kept.push_back(ctx->lent[k]);
         ctx->kept_bytes += n;
       } else {
@@ -1210,7 +1210,7 @@ stb_status stb_potential_core(stb_ctx* ctx, stb_mesh* mesh, const stb_quad_param
   int64_t* d_rowptr = nullptr;
   int32_t *d_cols = nullptr, *d_rowof = nullptr;
   auto cleanup = [&]() {
-    dfree(d_I); dfree(d_rowptr); dfree(d_cols); dfree(d_rowof);
+    ctx_keep(ctx, d_I); dfree(d_rowptr); ctx_keep(ctx, d_cols); ctx_keep(ctx, d_rowof);
   };
   HIPCHK(ctx, hipEventRecord(ctx->ev[0], ctx->stream));
   HIPCHK(ctx, hipEventRecord(ctx->ev[1], ctx->stream));
@@ -1218,7 +1218,7 @@ stb_status stb_potential_core(stb_ctx* ctx, stb_mesh* mesh, const stb_quad_param
   s = stb_cull_points(ctx, mesh, p, np, d_pts, &d_rowptr, &d_cols, &d_rowof, &nnz);
   if (s) { cleanup(); return s; }
   HIPCHK(ctx, hipEventRecord(ctx->ev[2], ctx->stream));
-  if (dalloc(&d_I, (size_t)nnz) != hipSuccess) { cleanup(); return fail(ctx, STB_E_NO_MEMORY, "candidates"); }
+  if (kalloc(ctx, &d_I, (size_t)nnz) != hipSuccess) { cleanup(); return fail(ctx, STB_E_NO_MEMORY, "candidates"); }
   PairJob J;
   J.nnz = nnz;
   J.rows = d_rowof;

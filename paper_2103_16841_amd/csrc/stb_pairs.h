@@ -18,6 +18,9 @@ struct PairJob {
   bool mixed = false;                // far combos' Gauss nodes in FP32
   double eta_far = 2.0;              // far: apex farther than eta_far radii from the panel's ball
   double* out = nullptr;             // [nnz] matrix entry or inner integral
+  // double layer (single apex per row, FP64): per panel kDlCoef doubles of the
+  // density (see stb_dl.hip); out[c] = D v_panel (point).  nullptr: single layer
+  const double* dl_coef = nullptr;
   uint8_t* lit_out = nullptr;        // optional [nnz]: 1 where some apex is lit
   unsigned long long* n_causal = nullptr;   // host: += candidates with a lit apex
   // optional segments of the candidate range (batches of meshes): candidate
@@ -26,6 +29,11 @@ struct PairJob {
   const int64_t* seg_off = nullptr;
   unsigned long long* seg_causal = nullptr;
 };
+
+// A panel's linear density v = sum_m v_m lambda_m, lambda_m = C_m / D_m in the
+// frame of a point: [0..3] v_m / D_m, [4], [5] its in-plane gradient
+// -sum v_m (b_m, c_m) / D_m, [6] the sign of the outward normal, [7] 0.
+constexpr int kDlCoef = 8;
 
 // Runs the pipeline; work[0..3] receive L evaluations, lit combos, apexes
 // tested and pieces.  Synchronises the context stream.

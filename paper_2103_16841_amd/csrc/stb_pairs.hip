@@ -28,6 +28,11 @@
 //   k_store   one lane per candidate: matrix entry = ordered sum over the
 //             apexes of w_q I_q (eq. int_bform); potential: I itself.
 //
+// The double layer (eq. dlp) takes the same stages up to the node kernels: its
+// breakpoints, pieces and recipes are the single layer's.  k_nodes_dl sums
+// three integrals per piece instead of one, and k_store_dl forms the panel's
+// potential from them.
+//
 // Every list position is handed out by atomics, but every sum runs in a
 // fixed order (nodes, pieces in phi order, apexes in q order), so results do
 // not depend on the schedule.  The candidate range is processed in chunks
@@ -148,6 +153,8 @@ struct Lists {
   double* ph;            // length (trapezoid half: -1)
   int32_t* pc;           // owning combo
   double* pv;            // ordered node sum
+  double* pv2;           // double layer: the other two sums (pv2, pv3: [cap_piece])
+  double* pv3;
   int32_t* pz;           // pieces whose quarter points decide (shares pv's memory: the
                          // node sums are written only after k_quarter has read the queue)
   float* pe;             // FP32 rounding bound of the node sum (far pieces, mixed)
@@ -257,6 +264,7 @@ struct Geo {
   const int32_t* apex_n; // [rows] or nullptr (one apex)
   int maxq;
   int mixed;             // far combos' nodes in FP32
+  int skip_flat;         // double layer: an apex in the panel's plane contributes nothing
   double eta_far;
 };
 
@@ -327,7 +335,7 @@ __global__ __launch_bounds__(kBlk, 4) void k_lit(Geo g, Lists L, int64_t c0, int
             for (int c = 0; c < 4; ++c) xn[c] = xr[4 * (q + 1) + c];
           Apex A;
           apex_frame(T, x4, A);
-          const int r = lit_quick(T, x4, A);
+          const int r = g.skip_flat && A.d == 0.0 ? 0 : lit_quick(T, x4, A);
           m |= (uint64_t)(r == 1) << q;
           und |= (uint64_t)(r == 2) << q;
         }
@@ -1000,6 +1008,149 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes(Lists L, const int32_t* __res
   }
 }
 
+// The double layer's nodes of a piece by its recipe: as k_nodes_rec, with the
+// three sums of wt sa, wt sh cos phi and wt sh sin phi.  For the mirror nodes m
+// -+ delta the last two follow from cos m, sin m and the sums of sh cos delta and
+// of its difference times sin delta.  Bound by instruction issue: 4.2e7 pieces of
+// 1.4e5 surface points on 15,360 panels took 87 ms with one kernel for the
+// test and four endpoint formulas indexed in private memory, a library
+// logarithm and two quotients per gap and node; the node kernels take 24 ms and
+// the tests 11 ms here.
+template <int NG, bool QE>
+__global__ __launch_bounds__(kBlk, 4) void k_nodes_dl(Lists L, const int32_t* __restrict__ jobs_arg,
+                                                      int64_t njob_arg, const double* __restrict__ gl, int ng) {
+  const int B = (int)blockDim.x;
+  const int64_t njob = list_count(L, njob_arg, L.cap_piece, 3);
+  const int32_t* __restrict__ jobs = jobs_arg ? jobs_arg : L.job + (L.cap_piece - njob);
+  for (int64_t base = (int64_t)blockIdx.x * B; base < njob; base += (int64_t)gridDim.x * B) {
+    const int64_t k = base + threadIdx.x;
+    if (k >= njob) continue;
+    const int32_t p = jobs[k];
+    const double H = L.ph[p], a = L.pa[p];
+    const uint32_t rec = L.prec[p];
+    const int64_t c = L.pc[p];
+    const int64_t cap = L.cap_combo;
+    const double d2 = L.cb[kCbD2 * cap + c], wlo = L.cb[kCbWlo * cap + c],
+                 whi = L.cb[kCbWhi * cap + c];
+    Endpoint E[2 * NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      E[2 * g] = endpoint_load(L, c, (rec >> (8 * g + 4)) & 15u, wlo, whi);
+      E[2 * g + 1] = endpoint_load(L, c, (rec >> (8 * g)) & 15u, wlo, whi);
+    }
+    const double m = a + 0.5 * H;
+    double sm, cm;
+    sincos_small(m, &sm, &cm);
+    double P[2 * NG], Q[2 * NG], CC[2 * NG], SG[2 * NG];
+#pragma unroll
+    for (int e = 0; e < 2 * NG; ++e) {
+      P[e] = fma(E[e].fb, cm, E[e].fc * sm);
+      Q[e] = fma(E[e].fb, sm, -(E[e].fc * cm));
+      CC[e] = E[e].C * E[e].C;
+      SG[e] = copysign(1.0, E[e].C);
+    }
+    double ia = 0.0, s1 = 0.0, s2 = 0.0;
+    // one mirror pair with weight factor wf (the midpoint itself: half of it)
+    auto pair = [&](double cd, double sd, double wf) {
+      double am = 0.0, hm = 0.0, ap = 0.0, hp = 0.0;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        double vm[2], vp[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int e = 2 * g + t;
+          endpoint_pair_node<QE>(E[e], P[e], Q[e], CC[e], SG[e], d2, wlo, whi, cd, sd, vm[t], vp[t]);
+        }
+        dl_gap_node(vm[0], fmax(vm[1], vm[0]), d2, am, hm);
+        dl_gap_node(vp[0], fmax(vp[1], vp[0]), d2, ap, hp);
+      }
+      ia = fma(wf, am + ap, ia);
+      s1 = fma(wf * cd, hm + hp, s1);
+      s2 = fma(wf * sd, hm - hp, s2);
+    };
+    const bool short_piece = H <= kPi;
+    for (int gi = 0; gi < (ng >> 1); ++gi) {
+      double sd, cd;
+      if (short_piece) sincos_half_pi(H * gl[2 * kMaxNg + gi], &sd, &cd);
+      else sincos_small(H * gl[2 * kMaxNg + gi], &sd, &cd);
+      pair(cd, sd, gl[3 * kMaxNg + gi]);
+    }
+    if (ng & 1) pair(1.0, 0.0, 0.5 * (1.5 * gl[kMaxNg + (ng >> 1)]));
+    // phi = m - delta: cos phi = cm cd + sm sd, sin phi = sm cd - cm sd
+    L.pv[p] = H * ia;
+    L.pv2[p] = H * fma(cm, s1, sm * s2);
+    L.pv3[p] = H * fma(sm, s1, -(cm * s2));
+  }
+}
+
+// The double layer's nodes of the other pieces: full evaluation.
+__global__ __launch_bounds__(kBlk, 4) void k_nodes_dl_full(Lists L, const int32_t* __restrict__ jobs,
+                                                           int64_t njob_arg, const double* __restrict__ gl, int ng) {
+  const int B = (int)blockDim.x;
+  const int64_t njob = list_count(L, njob_arg, L.cap_piece, 3);
+  const double ht = kTwoPi / (2 * ng);
+  for (int64_t k = (int64_t)blockIdx.x * B + threadIdx.x; k < njob; k += (int64_t)gridDim.x * B) {
+    const int32_t p = jobs[k];
+    const double H = L.ph[p], a = L.pa[p];
+    const ComboL cb = load_combo(L, L.pc[p]);
+    FaceSet F;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) { F.fa[f] = cb.fa[f]; F.fb[f] = cb.fb[f]; F.fc[f] = cb.fc[f]; }
+    const bool trap = H < 0.0;
+    double ia = 0.0, ic = 0.0, is = 0.0;
+    for (int gi = 0; gi < ng; ++gi) {
+      const double u = gl[gi];
+      const double phi = trap ? (a * ng + gi) * ht : a + H * (u * u * (3.0 - 2.0 * u));
+      const double wt = trap ? ht : (H * (6.0 * u * (1.0 - u))) * gl[kMaxNg + gi];
+      double sn, cs, sa, sh;
+      sincos_small(phi, &sn, &cs);
+      dl_eval(F, cb.C, cb.d2, cb.wlo, cb.whi, cs, sn, sa, sh);
+      ia += wt * sa;
+      ic += (wt * sh) * cs;
+      is += (wt * sh) * sn;
+    }
+    L.pv[p] = ia;
+    L.pv2[p] = ic;
+    L.pv3[p] = is;
+  }
+}
+
+// out[c] = D v (x) of candidate c's panel for its linear density (coef, see
+// PairJob): (d_n / 4 pi) (v(t, p) ia + g_u ic + g_v is), d_n the distance along
+// the outward normal.  One apex per candidate, so its combo is its row's point.
+__global__ __launch_bounds__(kBlk) void k_store_dl(Geo g, Lists L, int64_t c0, int64_t nc,
+                                                   const double* __restrict__ coef, double* __restrict__ out) {
+  if (L.cnt[CNT_DEEP] > (unsigned long long)L.cap_combo || L.cnt[CNT_COMBO] > (unsigned long long)L.cap_combo ||
+      L.cnt[CNT_PIECE] > (unsigned long long)L.cap_piece)
+    return;   // redone by the host (see k_store)
+  const int64_t cap = L.cap_combo;
+  for (int64_t c = (int64_t)blockIdx.x * kBlk + threadIdx.x; c < nc; c += (int64_t)gridDim.x * kBlk) {
+    double r = 0.0;
+    if (L.mask[c]) {
+      const int32_t k = L.combo0[c], p0 = L.p0[k], np = L.np[k];
+      double ia = 0.0, ic = 0.0, is = 0.0;
+      for (int s = 0; s < np; ++s) {
+        if (!L.pne[p0 + s]) continue;
+        ia += L.pv[p0 + s];
+        ic += L.pv2[p0 + s];
+        is += L.pv3[p0 + s];
+      }
+      if (np > 0) {
+        const int32_t j = g.cols[c0 + c];
+        const TrialRec& T = g.trial[j];
+        const double* x = g.apex + (int64_t)g.rows[c0 + c] * 4;
+        const double* w = coef + (int64_t)kDlCoef * j;
+        const double d = (x[1] - T.o[0]) * T.n[0] + (x[2] - T.o[1]) * T.n[1] + (x[3] - T.o[2]) * T.n[2];
+        double al = 0.0;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) al += w[f] * L.cb[(kCbC + f) * cap + k];
+        r = (w[6] * d / (4.0 * kPi)) * (al * ia + w[4] * ic + w[5] * is);
+      }
+    }
+    out[c0 + c] = r;
+  }
+}
+
 // The n_g nodes of a far piece in mixed precision: node angle, sin/cos and
 // the per-face coefficients in FP64, root solves and interval measure in
 // FP32 (L_eval_far), node sum in FP32 with Kahan compensation.
@@ -1204,12 +1355,14 @@ unsigned grid_for(int64_t n, int per = 1, int block = kBlk, int64_t max_blocks =
 struct PairWorkspace {
   int64_t cap_cand = 0, cap_combo = 0, cap_piece = 0;
   void* base = nullptr;
+  double* dl = nullptr;   // [2 cap_piece], made by the first double-layer run
   Lists L{};
 };
 
 void stb_free_workspace(stb_ctx* ctx) {
   if (!ctx->ws) return;
   dfree(ctx->ws->base);
+  dfree(ctx->ws->dl);
   delete ctx->ws;
   ctx->ws = nullptr;
 }
@@ -1245,7 +1398,7 @@ static void ws_want(int64_t nnz, int maxq, int64_t* cc, int64_t* cb, int64_t* cp
 
 int64_t stb_pairs_ws_held(const stb_ctx* ctx) {
   const PairWorkspace* w = ctx->ws;
-  return w ? (int64_t)ws_bytes(w->cap_cand, w->cap_combo, w->cap_piece) : 0;
+  return w ? (int64_t)ws_bytes(w->cap_cand, w->cap_combo, w->cap_piece) + (w->dl ? 16 * w->cap_piece : 0) : 0;
 }
 
 int64_t stb_pairs_ws_need(const stb_ctx* ctx, int64_t nnz, int maxq) {
@@ -1341,7 +1494,12 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
   stb_status s = ensure_workspace(ctx, want_cand, want_combo, want_piece);
   if (s) return s;
   PairWorkspace* w = ctx->ws;
+  const bool dl = job.dl_coef != nullptr;
+  if (dl && !w->dl && dalloc(&w->dl, (size_t)(2 * w->cap_piece)) != hipSuccess)
+    return stb_fail(ctx, STB_E_NO_MEMORY, "double-layer piece sums");
   Lists L = w->L;
+  L.pv2 = w->dl;
+  L.pv3 = w->dl ? w->dl + w->cap_piece : nullptr;
   // the lists' lengths in use: the workspace's, within the caller's limits
   // (the combo fields' stride follows cap_combo, so a shorter length only
   // narrows the fields inside their allocation)
@@ -1356,11 +1514,14 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
   g.apex = job.apex; g.apex_w = job.apex_w; g.apex_n = job.apex_n; g.maxq = job.maxq;
   g.mixed = job.mixed ? 1 : 0;
   g.eta_far = job.eta_far;
+  g.skip_flat = dl ? 1 : 0;
   hipStream_t st = ctx->stream;
   unsigned long long h[CNT_N];
-  // first guess: ~4 lit apexes and ~4 pieces per lit apex; adapted below
-  int64_t chunk = std::min<int64_t>(L.cap_cand, std::max<int64_t>(1, L.cap_combo / 4));
-  chunk = std::min<int64_t>(chunk, std::max<int64_t>(1, L.cap_piece / 16));
+  // first guess: ~4 lit apexes (one where a candidate has one) and ~4 pieces
+  // per lit apex; adapted below
+  const int64_t guess = std::min(job.maxq, 4);
+  int64_t chunk = std::min<int64_t>(L.cap_cand, std::max<int64_t>(1, L.cap_combo / guess));
+  chunk = std::min<int64_t>(chunk, std::max<int64_t>(1, L.cap_piece / (4 * guess)));
   int64_t c0 = 0;
   // device count argument of list counter k (see list_count)
   auto dev = [](int k) { return -(int64_t)k - 1; };
@@ -1413,14 +1574,25 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
     // FP64 nodes: one-gap recipes (front and back of the one-gap list),
     // two-gap recipes, full evaluations
     HIPCHK(ctx, t0(4));
-    hipLaunchKernelGGL((k_nodes_rec<1, true>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L,
-                       L.job, dev(CNT_JOB), job.gl, job.ng);
-    hipLaunchKernelGGL((k_nodes_rec<1, false>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st,
-                       L, nullptr, dev(CNT_JOB1X), job.gl, job.ng);
-    hipLaunchKernelGGL((k_nodes_rec<2, false>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st,
-                       L, L.job2, dev(CNT_JOB2), job.gl, job.ng);
-    hipLaunchKernelGGL(k_nodes, dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L, L.jobf,
-                       dev(CNT_JOBF), job.gl, job.ng);
+    if (dl) {
+      hipLaunchKernelGGL((k_nodes_dl<1, true>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L,
+                         L.job, dev(CNT_JOB), job.gl, job.ng);
+      hipLaunchKernelGGL((k_nodes_dl<1, false>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st,
+                         L, nullptr, dev(CNT_JOB1X), job.gl, job.ng);
+      hipLaunchKernelGGL((k_nodes_dl<2, false>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st,
+                         L, L.job2, dev(CNT_JOB2), job.gl, job.ng);
+      hipLaunchKernelGGL(k_nodes_dl_full, dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L, L.jobf,
+                         dev(CNT_JOBF), job.gl, job.ng);
+    } else {
+      hipLaunchKernelGGL((k_nodes_rec<1, true>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L,
+                         L.job, dev(CNT_JOB), job.gl, job.ng);
+      hipLaunchKernelGGL((k_nodes_rec<1, false>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st,
+                         L, nullptr, dev(CNT_JOB1X), job.gl, job.ng);
+      hipLaunchKernelGGL((k_nodes_rec<2, false>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st,
+                         L, L.job2, dev(CNT_JOB2), job.gl, job.ng);
+      hipLaunchKernelGGL(k_nodes, dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L, L.jobf,
+                         dev(CNT_JOBF), job.gl, job.ng);
+    }
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, t1(4));
     if (g.mixed) {
@@ -1431,11 +1603,15 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
       HIPCHK(ctx, t1(5));
     }
     HIPCHK(ctx, t0(6));
-    hipLaunchKernelGGL(k_combine, dim3(grid_for(ub_combo)), dim3(kBlk), 0, st, L, dev(CNT_COMBO));
-    HIPCHK(ctx, hipGetLastError());
     const bool check = g.mixed && g.apex_w;
-    hipLaunchKernelGGL(k_store, dim3(grid_for(nc)), dim3(kBlk), 0, st, g, L, c0, nc, job.out,
-                       check ? 1 : 0, job.nseg, job.seg_off, job.seg_causal);
+    if (dl) {
+      hipLaunchKernelGGL(k_store_dl, dim3(grid_for(nc)), dim3(kBlk), 0, st, g, L, c0, nc, job.dl_coef, job.out);
+    } else {
+      hipLaunchKernelGGL(k_combine, dim3(grid_for(ub_combo)), dim3(kBlk), 0, st, L, dev(CNT_COMBO));
+      HIPCHK(ctx, hipGetLastError());
+      hipLaunchKernelGGL(k_store, dim3(grid_for(nc)), dim3(kBlk), 0, st, g, L, c0, nc, job.out,
+                         check ? 1 : 0, job.nseg, job.seg_off, job.seg_causal);
+    }
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, t1(6));
     // the chunk's one wait: its list counts

@@ -142,7 +142,7 @@ stb_status footprint(stb_ctx* c, const ServedMesh& sm, const stb_request& r, int
     int32_t *cols = nullptr, *rowof = nullptr;
     stb_quad_params p = stb_default_params();
     s = stb_cull_points(c, sm.mesh, p, r.np, pts, &rp, &cols, &rowof, &nnz);
-    dfree(rp); dfree(cols); dfree(rowof);
+    dfree(rp); ctx_keep(c, cols); ctx_keep(c, rowof);
   } else {
     s = stb_fail(c, STB_E_DEVICE, "copy in");
   }
@@ -253,6 +253,7 @@ stb_status stb_server_create(stb_ctx* ctx, int64_t hbm_budget_bytes, int32_t nsl
       c->tune_per_cu[q] = ctx->tune_per_cu[q];
     }
     c->tuned = ctx->tuned;
+    c->kept_max = 0;
     S->slots.push_back(c);
     S->slot_ws.push_back(0);
   }

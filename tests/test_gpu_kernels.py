@@ -122,3 +122,22 @@ def test_marching_equals_dense_solve(stb, ctx, level, slabs):
     # a solve by an explicit inverse: a few K eps cond(D) of the block's size
     cond = np.linalg.cond(D)
     assert np.linalg.norm(x - ref) <= 8 * K * EPS * cond ** 2 * np.linalg.norm(ref)
+
+
+# odd and even node counts; points on both sides of the logarithm series' limit
+# (far: gaps of a tenth of r, near: gaps of several r), and in panels' planes
+@pytest.mark.parametrize("n_g", [2, 3, 16, 33])
+def test_double_layer_nodes(stb, ctx, n_g):
+    import oracle
+    mesh = inputs.icosphere_mesh(1, 6, T=3.0)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    M.set_normals(mesh.outward_normals())
+    v = np.random.default_rng(1).standard_normal(mesh.nv)
+    cen = mesh.tet_coords().mean(axis=1)[::37]
+    near = cen + np.concatenate([np.full((len(cen), 1), 0.3), 1e-3 * mesh.outward_normals()[::37]], axis=1)
+    flat = cen + np.array([0.4, 0.0, 0.0, 0.0])
+    pts = np.concatenate([inputs.shell_points(60, mesh.T, seed=2), near, flat])
+    u = stb.potential_D(ctx, M, v, pts, params=stb.default_params(n_g=n_g))
+    ref = oracle.potential_dl(mesh.vtx, mesh.tets, mesh.outward_normals(), v, pts, n_g=n_g)
+    # the double layer's parity bound: 1e-10 relative above 1e-5 of the largest value
+    assert np.all(np.abs(u - ref) <= 1e-10 * np.maximum(np.abs(ref), 1e-5 * np.abs(ref).max()))
