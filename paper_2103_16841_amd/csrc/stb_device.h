@@ -1552,6 +1552,40 @@ STB_HD __forceinline__ float L_eval_far(const ComboL& cb, const FarConst& F, dou
   return empty ? 0.0f : len;
 }
 
+// One endpoint of a far piece's one-gap recipe at a node, in delta: the constant
+// end, or the root of face k that L_eval_far takes at the same place, from the
+// same roundings of beta, gamma and the discriminant.  sg: the sign sigma of the
+// root w = (C + sigma sqrt(D)) / e = w_c + (-beta + sigma sqrt(D)) / e, of which
+// q / e in delta is the one with sigma = -sign(beta).
+struct FarEnd {
+  double a, K1, K0;
+  float sg, cval;
+  bool cst;
+};
+
+STB_HD __forceinline__ FarEnd far_end(const Endpoint& E, bool is_lo, double d2, double wc, float dlo, float dhi) {
+  FarEnd F;
+  F.a = E.a;
+  F.K1 = fma(E.a, wc, E.C);
+  F.K0 = fma(E.a, fma(wc, wc, d2), 2.0 * E.C * wc);
+  F.sg = copysignf(1.0f, (float)(E.isb ? -E.C : E.C));
+  F.cst = E.cst;
+  F.cval = is_lo ? dlo : dhi;
+  return F;
+}
+
+STB_HD __forceinline__ float far_end_value(const FarEnd& F, double B, double wc, double P1, float dlo, float dhi) {
+  const double e64 = B - F.a;
+  const double be64 = fma(B, wc, -F.K1);
+  const double ga64 = fma(B, P1, -F.K0);
+  const float D = (float)fma(be64, be64, -e64 * ga64);
+  const float e = (float)e64, be = (float)be64, ga = (float)ga64;
+  const float q = -(be + copysignf(sqrt32(fmaxf(D, 0.0f)), be));
+  const bool first = F.sg * copysignf(1.0f, be) < 0.0f;
+  const float v = (first ? q : ga) * rcp32(first ? e : q);
+  return fminf(fmaxf(F.cst ? F.cval : v, dlo), dhi);
+}
+
 // A combo is far when the apex's spatial distance from the trial panel's
 // bounding ball exceeds eta times the ball's radius.
 STB_HD __forceinline__ bool apex_far(const TrialRec& T, const double* x4, double eta) {

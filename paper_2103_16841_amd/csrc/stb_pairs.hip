@@ -57,7 +57,7 @@ constexpr int kBlk = 256;
 constexpr int kMaxBlocks = 256 * 16;
 
 enum {
-  CNT_COMBO = 0, CNT_DEEP, CNT_PIECE, CNT_JOB, CNT_JOB1X, CNT_JOB2, CNT_JOBF, CNT_JOB32, CNT_QZ, CNT_REDO, CNT_PAIRS,
+  CNT_COMBO = 0, CNT_DEEP, CNT_PIECE, CNT_JOB, CNT_JOB1X, CNT_JOB2, CNT_JOBF, CNT_JOB32, CNT_JOB32F, CNT_QZ, CNT_REDO, CNT_PAIRS,
   CNT_CAUSAL, CNT_EVAL_MID, CNT_MISS, CNT_N
 };
 
@@ -162,7 +162,8 @@ struct Lists {
   int32_t* job2;         // ... by a two-gap recipe
   int32_t* jobf;         // ... full evaluation (no recipe, slivers, trapezoid halves)
   uint32_t* prec;        // per piece: recipe of its gap structure
-  int32_t* job32;        // non-empty pieces of far combos, FP32 nodes (mixed)
+  int32_t* job32;        // non-empty pieces of far combos, FP32 nodes (mixed): one-gap
+                         // recipes from the front, the others from the back
   uint8_t* pne;          // per piece: non-empty
   uint8_t* redo;         // per candidate (mixed): entry recomputed in FP64
   unsigned long long* cnt;
@@ -695,7 +696,7 @@ __device__ __forceinline__ int empty_per(int64_t n) {
 // One-gap recipes whose two endpoints are both q / e roots (nearly all of
 // them) go to the front of the one-gap list, the other one-gap recipes to
 // its back (filled downward from the end).
-enum { JOB_R1Q = 0, JOB_R2 = 1, JOB_FULL = 2, JOB_FP32 = 3, JOB_R1X = 4 };
+enum { JOB_R1Q = 0, JOB_R2 = 1, JOB_FULL = 2, JOB_FP32 = 3, JOB_R1X = 4, JOB_FP32F = 6 };
 
 // Pieces narrower than this take the full evaluation: their nodes sit
 // within rounding of the breakpoints, where the structure is ambiguous.
@@ -715,37 +716,38 @@ __device__ __forceinline__ unsigned route_fp64(double H, uint32_t rec) {
 // The same for any piece of combo k: far combos (mixed precision only) go to
 // the FP32 nodes.
 __device__ __forceinline__ unsigned route_of(const Lists& L, int32_t k, double H, uint32_t rec) {
-  if (L.mixed && (L.key[k] & kKeyFar)) return JOB_FP32;
-  return route_fp64(H, rec);
+  const unsigned r = route_fp64(H, rec);
+  if (L.mixed && (L.key[k] & kKeyFar)) return r == JOB_R1Q || r == JOB_R1X ? JOB_FP32 : JOB_FP32F;
+  return r;
 }
 
 // Job lists of one pass: every lane routes up to kEmptyPer pieces (3 bits
 // of route each in `route`, presence in `has`, piece j from piece_of(j)).
 // Slots are handed out per wave: the lane's counts of the three frequent
-// lists in 21-bit fields of one 64-bit word, one shuffle scan over the wave,
+// lists in 16-bit fields of one 64-bit word, one shuffle scan over the wave,
 // and lane f reserves list f's slots with one atomic when the wave has any
-// (no block barriers); the other three lists, which few waves touch, the
-// same way when the wave has any entry for them.  Every lane of the wave
-// must call it.
+// (no block barriers); the other four lists, which few waves touch (in mixed
+// precision all), the same way when the wave has any entry for them.  Every
+// lane of the wave must call it.
 constexpr int JOB_QZ = 5;   // not a job list: the queue for the quarter points
+static_assert(kEmptyPer * 64 < 65536, "a wave's list counts fit 16 bits");
 
 template <class F>
 __device__ __forceinline__ void route_pieces(const Lists& L, unsigned has, uint64_t route, F piece_of) {
   const int lane = threadIdx.x & 63;
   auto route_at = [&](int j) { return (unsigned)(route >> (3 * j)) & 7u; };
-  // one word of three lists: counts, and the wave's slots
-  auto reserve = [&](uint64_t v, int c0, int c1, int c2, unsigned long long (&s)[3]) {
+  // one word of up to four lists: counts, and the wave's slots
+  auto reserve = [&](uint64_t v, int c0, int c1, int c2, int c3, unsigned long long (&s)[4]) {
     const uint64_t incl = wave_prefix(v);
     const uint64_t tot = __shfl(incl, 63, 64);
     unsigned long long b = 0;
-    if (lane < 3) {
-      const unsigned long long n = (tot >> (21 * lane)) & 0x1fffffull;
-      if (n) b = atomicAdd(L.cnt + (lane == 0 ? c0 : lane == 1 ? c1 : c2), n);
+    if (lane < 4) {
+      const unsigned long long n = (tot >> (16 * lane)) & 0xffffull;
+      if (n) b = atomicAdd(L.cnt + (lane == 0 ? c0 : lane == 1 ? c1 : lane == 2 ? c2 : c3), n);
     }
     const uint64_t ex = incl - v;
 #pragma unroll
-    for (int f = 0; f < 3; ++f) s[f] = __shfl(b, f, 64) + ((ex >> (21 * f)) & 0x1fffffull);
-    return tot;
+    for (int f = 0; f < 4; ++f) s[f] = __shfl(b, f, 64) + ((ex >> (16 * f)) & 0xffffull);
   };
   // the one-gap q/e jobs (nearly every piece) in piece order: item j of
   // every lane before item j + 1, lanes in order within an item, so that
@@ -755,12 +757,13 @@ __device__ __forceinline__ void route_pieces(const Lists& L, unsigned has, uint6
   for (int j = 0; j < kEmptyPer; ++j) {
     const bool h = (has >> j) & 1u;
     const unsigned r = route_at(j);
-    vf += !h ? 0ull : r == JOB_R1Q ? 1ull : r == JOB_R1X ? 1ull << 21 : r == JOB_QZ ? 1ull << 42 : 0ull;
-    vr += !h ? 0ull : r == JOB_R2 ? 1ull : r == JOB_FULL ? 1ull << 21 : r == JOB_FP32 ? 1ull << 42 : 0ull;
+    vf += !h ? 0ull : r == JOB_R1Q ? 1ull : r == JOB_R1X ? 1ull << 16 : r == JOB_QZ ? 1ull << 32 : 0ull;
+    vr += !h ? 0ull : r == JOB_R2 ? 1ull : r == JOB_FULL ? 1ull << 16 : r == JOB_FP32 ? 1ull << 32
+          : r == JOB_FP32F ? 1ull << 48 : 0ull;
     rest |= (h && r != JOB_R1Q) ? 1u << j : 0u;
   }
-  unsigned long long sf[3], sr[3] = {0ull, 0ull, 0ull};
-  (void)reserve(vf, CNT_JOB, CNT_JOB1X, CNT_QZ, sf);
+  unsigned long long sf[4], sr[4] = {0ull, 0ull, 0ull, 0ull};
+  reserve(vf, CNT_JOB, CNT_JOB1X, CNT_QZ, CNT_QZ, sf);
   unsigned long long s0 = __shfl(sf[0], 0, 64);   // lane 0 has none before it
   const unsigned long long below = (1ull << lane) - 1ull;
   for (int j = 0; j < kEmptyPer; ++j) {
@@ -771,18 +774,20 @@ __device__ __forceinline__ void route_pieces(const Lists& L, unsigned has, uint6
   }
   // the other lists: only the lane's items that go there (nearly always
   // none or a few of its kEmptyPer), so the wave runs the slowest lane's
-  if (__ballot(vr != 0ull)) (void)reserve(vr, CNT_JOB2, CNT_JOBF, CNT_JOB32, sr);
+  if (__ballot(vr != 0ull)) reserve(vr, CNT_JOB2, CNT_JOBF, CNT_JOB32, CNT_JOB32F, sr);
   while (rest) {
     const int j = __ffs(rest) - 1;
     rest &= rest - 1u;
     const unsigned r = route_at(j);
     const int32_t p = piece_of(j);
     int32_t* dst = r == JOB_R2 ? L.job2 + sr[0] : r == JOB_FULL ? L.jobf + sr[1] : r == JOB_FP32 ? L.job32 + sr[2]
+                 : r == JOB_FP32F ? L.job32 + (L.cap_piece - 1 - (int64_t)sr[3])
                  : r == JOB_R1X ? L.job + (L.cap_piece - 1 - (int64_t)sf[1]) : L.pz + sf[2];
     *dst = p;
     sr[0] += r == JOB_R2 ? 1 : 0;
     sr[1] += r == JOB_FULL ? 1 : 0;
     sr[2] += r == JOB_FP32 ? 1 : 0;
+    sr[3] += r == JOB_FP32F ? 1 : 0;
     sf[1] += r == JOB_R1X ? 1 : 0;
     sf[2] += r == JOB_QZ ? 1 : 0;
   }
@@ -1151,9 +1156,88 @@ __global__ __launch_bounds__(kBlk) void k_store_dl(Geo g, Lists L, int64_t c0, i
   }
 }
 
-// The n_g nodes of a far piece in mixed precision: node angle, sin/cos and
-// the per-face coefficients in FP64, root solves and interval measure in
-// FP32 (L_eval_far), node sum in FP32 with Kahan compensation.
+// The n_g nodes of a far piece with a one-gap recipe in mixed precision: the
+// node's sin/cos and the two endpoints' coefficients in FP64, their roots and
+// the gap's measure in FP32, node sum in FP32 with Kahan compensation in node
+// order.  The roots have the roundings of L_eval_far's, which sweeps all four
+// faces, and the FP32 bound is its bound of the one gap.  7,680 panels, bound by
+// instructions: 26.2 ms with the four-face sweep for every far piece, 10.6 ms.
+__global__ __launch_bounds__(kBlk, 4) void k_nodes32_rec(Lists L, int64_t njob_arg, const double* __restrict__ gl,
+                                                         int ng) {
+  const int B = (int)blockDim.x;
+  const int64_t njob = list_count(L, njob_arg, L.cap_piece, 3);
+  for (int64_t k = (int64_t)blockIdx.x * B + threadIdx.x; k < njob; k += (int64_t)gridDim.x * B) {
+    const int32_t p = L.job32[k];
+    const double H = L.ph[p], a = L.pa[p];
+    const uint32_t rec = L.prec[p];
+    const int64_t c = L.pc[p];
+    const int64_t cap = L.cap_combo;
+    const double d2 = L.cb[kCbD2 * cap + c], wlo = L.cb[kCbWlo * cap + c], whi = L.cb[kCbWhi * cap + c];
+    // the centre and range of far_const
+    const double wc = 0.5 * (wlo + whi), ad = sqrt(d2), P1 = (wc - ad) * (wc + ad);
+    FarConst G;
+    G.m = (float)(wc - ad);
+    G.ad = (float)ad;
+    const float dlo = (float)(wlo - wc), dhi = (float)(whi - wc);
+    const uint32_t i0 = (rec >> 4) & 15u, i1 = rec & 15u;
+    const Endpoint E0 = endpoint_load(L, c, (int)i0, wlo, whi), E1 = endpoint_load(L, c, (int)i1, wlo, whi);
+    FarEnd F0 = far_end(E0, i0 == 0u, d2, wc, dlo, dhi), F1 = far_end(E1, i1 == 0u, d2, wc, dlo, dhi);
+    // A face of constant time bounds the range exactly where w_hi (from below)
+    // or w_lo (from above) does: on such a tie the recipe has the constant, and
+    // the sweep over the faces the inner one of it and the face's FP32 root.
+    if (i0 < 2u || i1 < 2u) {
+      for (int f = 0; f < 4; ++f) {
+        Endpoint E = endpoint_load(L, c, 2 + 2 * f, wlo, whi);
+        if (!(fabs(E.fb) + fabs(E.fc) < 1e-15)) continue;
+        const bool lo = E.a > 0.0;
+        FarEnd X = far_end(E, lo, d2, wc, dlo, dhi);
+        X.sg = lo ? -1.0f : 1.0f;
+        if (!(fma(X.K1, X.K1, -E.a * X.K0) > 0.0)) continue;
+        const float v = far_end_value(X, 0.0, wc, P1, dlo, dhi);
+        if (lo && i0 == 0u) F0.cval = fmaxf(F0.cval, v);
+        if (!lo && i1 == 1u) F1.cval = fminf(F1.cval, v);
+      }
+    }
+    // B(m -+ delta) = P cos delta +- Q sin delta (see k_nodes_rec)
+    double sm, cm;
+    sincos_small(a + 0.5 * H, &sm, &cm);
+    const double P0 = fma(E0.fb, cm, E0.fc * sm), Q0 = fma(E0.fb, sm, -(E0.fc * cm));
+    const double Pq = fma(E1.fb, cm, E1.fc * sm), Qq = fma(E1.fb, sm, -(E1.fc * cm));
+    const float kWulp32 = 4.76837158203125e-7f, kE = 2.384185791015625e-7f;
+    const bool short_piece = H <= kPi;
+    float acc = 0.0f, comp = 0.0f, eacc = 0.0f;
+    for (int gi = 0; gi < ng; ++gi) {
+      const double u = gl[gi];
+      const double ds = 6.0 * u * (1.0 - u);
+      const double wt = (H * ds) * gl[kMaxNg + gi];
+      double sd, cd;   // of delta = phi_m - phi
+      const double dl = H * gl[2 * kMaxNg + gi];
+      if (short_piece) sincos_half_pi(dl, &sd, &cd);
+      else sincos_small(fabs(dl), &sd, &cd);
+      if (!short_piece) sd = copysign(1.0, dl) * sd;
+      const float v0 = far_end_value(F0, fma(P0, cd, Q0 * sd), wc, P1, dlo, dhi);
+      const float v1 = far_end_value(F1, fma(Pq, cd, Qq * sd), wc, P1, dlo, dhi);
+      const bool open = v1 > v0;
+      const float m = open ? rgap32(v0, v1, G) : 0.0f;
+      const bool keep = m > kWulp32 * fmaxf(fabsf(v0), fabsf(v1));
+      const float el = !open ? kE * (fabsf(v0) + fabsf(v1)) : keep ? kE * (fabsf(v0) + fabsf(v1) + m) : m;
+      const float term = (float)wt * (keep ? m : 0.0f);
+      eacc = fmaf((float)wt, el, eacc);
+      const float y = term - comp;
+      const float t = acc + y;
+      comp = (t - acc) - y;
+      acc = t;
+    }
+    L.pv[p] = (double)acc;
+    // (see k_nodes32)
+    L.pe[p] = acc == 0.0f ? INFINITY : eacc + 1.2e-7f * fabsf(acc);
+  }
+}
+
+// The n_g nodes of the other far pieces (the back of the far list): node
+// angle, sin/cos and the per-face coefficients in FP64, root solves and
+// interval measure in FP32 (L_eval_far), node sum in FP32 with Kahan
+// compensation.
 __global__ __launch_bounds__(kBlk, 4) void k_nodes32(Lists L, int64_t njob_arg,
                                                      const double* __restrict__ gl, int ng) {
   const int B = (int)blockDim.x;
@@ -1162,7 +1246,7 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes32(Lists L, int64_t njob_arg,
   for (int64_t base = (int64_t)blockIdx.x * B; base < njob; base += (int64_t)gridDim.x * B) {
     const int64_t k = base + threadIdx.x;
     if (k >= njob) continue;
-    const int32_t p = L.job32[k];
+    const int32_t p = L.job32[L.cap_piece - 1 - k];
     const double H = L.ph[p], a = L.pa[p];
     const ComboL cb = load_combo(L, L.pc[p]);
     const FarConst F = far_const(cb);
@@ -1305,41 +1389,28 @@ __global__ __launch_bounds__(kBlk) void k_store(Geo g, Lists L, int64_t c0, int6
 // candidate go to the FP64 node kernels again, routed by their recipes as in
 // the FP64 pass (the job lists and their counters start empty), so that a
 // recomputed entry is the FP64 assembly's value through the same outer
-// points, bit for bit.
-__global__ __launch_bounds__(kBlk) void k_redo(Geo g, Lists L, int64_t nc) {
-  __shared__ AllocLds sh;
-  for (int64_t base = (int64_t)blockIdx.x * kBlk; base < nc; base += (int64_t)gridDim.x * kBlk) {
-    const int64_t c = base + threadIdx.x;
-    const bool v = c < nc && L.redo[c];
-    unsigned cnt[5] = {0, 0, 0, 0, 0};
-    int32_t k0 = 0, nk = 0;
-    if (v) {
-      k0 = L.combo0[c];
-      nk = __popcll(L.mask[c]);
-      for (int32_t k = k0; k < k0 + nk; ++k) {
-        if (!(L.key[k] & kKeyFar)) continue;
-        for (int32_t p = L.p0[k]; p < L.p0[k] + L.np[k]; ++p)
-          if (L.pne[p]) ++cnt[route_fp64(L.ph[p], L.prec[p])];
-      }
+// points, bit for bit.  One lane per piece, like the empty-piece test (7,680
+// panels: 12.3 ms with one lane per candidate walking its combos and pieces,
+// 3.0 ms).
+__global__ __launch_bounds__(kBlk) void k_redo(Lists L, int64_t npiece_arg) {
+  const int B = (int)blockDim.x;
+  const int64_t npiece = list_count(L, npiece_arg, L.cap_piece, 3);
+  const int per = empty_per(npiece);
+  const int64_t step = (int64_t)gridDim.x * B * per;
+  for (int64_t base = (int64_t)blockIdx.x * B * per; base < npiece; base += step) {
+    unsigned has = 0;
+    uint64_t route = 0;
+    const int64_t wbase = base + (int64_t)(threadIdx.x >> 6) * 64 * per + (threadIdx.x & 63);
+    auto piece_of = [&](int j) { return (int32_t)(wbase + (int64_t)j * 64); };
+    for (int j = 0; j < per; ++j) {
+      const int64_t p = wbase + (int64_t)j * 64;
+      if (p >= npiece) break;
+      const uint32_t key = L.key[L.pc[p]];
+      if (!(key & kKeyFar) || !L.redo[key >> kKeyShift] || !L.pne[p]) continue;
+      has |= 1u << j;
+      route |= (uint64_t)route_fp64(L.ph[p], L.prec[p]) << (3 * j);
     }
-    unsigned long long sl[5];
-    sl[JOB_R1Q] = block_alloc(L.cnt + CNT_JOB, cnt[JOB_R1Q], sh);
-    sl[JOB_R2] = block_alloc(L.cnt + CNT_JOB2, cnt[JOB_R2], sh);
-    sl[JOB_FULL] = block_alloc(L.cnt + CNT_JOBF, cnt[JOB_FULL], sh);
-    sl[JOB_R1X] = block_alloc(L.cnt + CNT_JOB1X, cnt[JOB_R1X], sh);
-    if (v) {
-      for (int32_t k = k0; k < k0 + nk; ++k) {
-        if (!(L.key[k] & kKeyFar)) continue;
-        for (int32_t p = L.p0[k]; p < L.p0[k] + L.np[k]; ++p) {
-          if (!L.pne[p]) continue;
-          const unsigned r = route_fp64(L.ph[p], L.prec[p]);
-          if (r == JOB_R1X) L.job[L.cap_piece - 1 - (int64_t)(sl[r]++)] = p;
-          else if (r == JOB_R1Q) L.job[sl[r]++] = p;
-          else if (r == JOB_R2) L.job2[sl[r]++] = p;
-          else L.jobf[sl[r]++] = p;
-        }
-      }
-    }
+    route_pieces(L, has, route, piece_of);
   }
 }
 
@@ -1597,8 +1668,10 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
     HIPCHK(ctx, t1(4));
     if (g.mixed) {
       HIPCHK(ctx, t0(5));
-      hipLaunchKernelGGL(k_nodes32, dim3(gfor(5, ub_piece)), dim3(ctx->tune_block[5]), 0, st, L,
+      hipLaunchKernelGGL(k_nodes32_rec, dim3(gfor(5, ub_piece)), dim3(ctx->tune_block[5]), 0, st, L,
                          dev(CNT_JOB32), job.gl, job.ng);
+      hipLaunchKernelGGL(k_nodes32, dim3(gfor(5, ub_piece)), dim3(ctx->tune_block[5]), 0, st, L,
+                         dev(CNT_JOB32F), job.gl, job.ng);
       HIPCHK(ctx, hipGetLastError());
       HIPCHK(ctx, t1(5));
     }
@@ -1633,43 +1706,29 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
     }
     const unsigned long long ncombo = hc[CNT_COMBO], npiece = hc[CNT_PIECE];
     const unsigned long long njob = hc[CNT_JOB], njob1x = hc[CNT_JOB1X], njob2 = hc[CNT_JOB2];
-    unsigned long long njr = 0;   // jobs of the recomputed entries
     if (check) {
       // mixed: entries whose FP32 error bound is too large for their size
       // are recomputed with FP64 nodes
-      unsigned long long nredo = hc[CNT_REDO];
-      if (nredo) {
+      if (hc[CNT_REDO]) {
         // the FP64 job lists were consumed by the launches above (same stream)
         HIPCHK(ctx, hipMemsetAsync(L.cnt + CNT_JOB, 0, 4 * sizeof(unsigned long long), st));
         static_assert(CNT_JOB1X == CNT_JOB + 1 && CNT_JOB2 == CNT_JOB + 2 && CNT_JOBF == CNT_JOB + 3,
                       "job counters contiguous");
-        hipLaunchKernelGGL(k_redo, dim3(grid_for(nc)), dim3(kBlk), 0, st, g, L, nc);
+        HIPCHK(ctx, t0(7));
+        hipLaunchKernelGGL(k_redo, dim3(gfor(2, npiece)), dim3(kBlk), 0, st, L, (int64_t)npiece);
+        hipLaunchKernelGGL((k_nodes_rec<1, true>), dim3(gfor(4, npiece)), dim3(ctx->tune_block[4]), 0, st, L, L.job,
+                           dev(CNT_JOB), job.gl, job.ng);
+        hipLaunchKernelGGL((k_nodes_rec<1, false>), dim3(gfor(4, npiece)), dim3(ctx->tune_block[4]), 0, st, L, nullptr,
+                           dev(CNT_JOB1X), job.gl, job.ng);
+        hipLaunchKernelGGL((k_nodes_rec<2, false>), dim3(gfor(4, npiece)), dim3(ctx->tune_block[4]), 0, st, L, L.job2,
+                           dev(CNT_JOB2), job.gl, job.ng);
+        hipLaunchKernelGGL(k_nodes, dim3(gfor(4, npiece)), dim3(ctx->tune_block[4]), 0, st, L, L.jobf, dev(CNT_JOBF),
+                           job.gl, job.ng);
         HIPCHK(ctx, hipGetLastError());
-        unsigned long long hr[CNT_N];
-        HIPCHK(ctx, hipMemcpyAsync(hr, L.cnt, sizeof(hr), hipMemcpyDeviceToHost, st));
-        HIPCHK(ctx, hipStreamSynchronize(st));
-        const unsigned long long r1 = hr[CNT_JOB], r1x = hr[CNT_JOB1X], r2 = hr[CNT_JOB2], rf = hr[CNT_JOBF];
-        njr = r1 + r1x + r2 + rf;
-        if (njr) {
-          HIPCHK(ctx, t0(7));
-          if (r1)
-            hipLaunchKernelGGL((k_nodes_rec<1, true>), dim3(gfor(4, r1)), dim3(ctx->tune_block[4]), 0, st, L,
-                               L.job, (int64_t)r1, job.gl, job.ng);
-          if (r1x)
-            hipLaunchKernelGGL((k_nodes_rec<1, false>), dim3(gfor(4, r1x)), dim3(ctx->tune_block[4]), 0, st,
-                               L, L.job + (L.cap_piece - (int64_t)r1x), (int64_t)r1x, job.gl, job.ng);
-          if (r2)
-            hipLaunchKernelGGL((k_nodes_rec<2, false>), dim3(gfor(4, r2)), dim3(ctx->tune_block[4]), 0, st,
-                               L, L.job2, (int64_t)r2, job.gl, job.ng);
-          if (rf)
-            hipLaunchKernelGGL(k_nodes, dim3(gfor(4, rf)), dim3(ctx->tune_block[4]), 0, st, L, L.jobf,
-                               (int64_t)rf, job.gl, job.ng);
-          HIPCHK(ctx, hipGetLastError());
-          HIPCHK(ctx, t1(7));
-        }
+        HIPCHK(ctx, t1(7));
       }
       HIPCHK(ctx, t0(3));
-      if (njr)
+      if (hc[CNT_REDO])
         hipLaunchKernelGGL(k_combine, dim3(grid_for(ncombo)), dim3(kBlk), 0, st, L, (int64_t)ncombo);
       hipLaunchKernelGGL(k_store, dim3(grid_for(nc)), dim3(kBlk), 0, st, g, L, c0, nc, job.out, 0,
                          job.nseg, job.seg_off, job.seg_causal);
@@ -1689,11 +1748,14 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
       ctx->kern_ms[k] += ms;
       ctx->kern_n[k] += 1;
     }
+    // jobs of the recomputed entries
+    const unsigned long long njr =
+        check && hc[CNT_REDO] ? h[CNT_JOB] + h[CNT_JOB1X] + h[CNT_JOB2] + h[CNT_JOBF] : 0ull;
     // every job evaluates n_g nodes, every queued piece two quarter points
     const unsigned long long ng = (unsigned long long)job.ng;
     const unsigned long long ev_test = h[CNT_EVAL_MID] + 2 * hc[CNT_QZ];
     const unsigned long long ev_full = hc[CNT_JOBF] * ng, ev_nodes = (njob + njob1x + njob2) * ng + ev_full;
-    const unsigned long long ev32 = hc[CNT_JOB32] * ng;
+    const unsigned long long ev32 = (hc[CNT_JOB32] + hc[CNT_JOB32F]) * ng;
     const unsigned long long evals = ev_test + ev_nodes + ev32 + njr * ng;
     ctx->kern_units[0] += (int64_t)h[CNT_PAIRS];
     ctx->kern_units[1] += (int64_t)ncombo;

@@ -141,3 +141,20 @@ def test_double_layer_nodes(stb, ctx, n_g):
     ref = oracle.potential_dl(mesh.vtx, mesh.tets, mesh.outward_normals(), v, pts, n_g=n_g)
     # the double layer's parity bound: 1e-10 relative above 1e-5 of the largest value
     assert np.all(np.abs(u - ref) <= 1e-10 * np.maximum(np.abs(ref), 1e-5 * np.abs(ref).max()))
+
+
+# odd and even node counts; all lit pairs (also near ones, with pieces longer than
+# pi) and far ones only; panels with faces of constant time, tied with the range's ends
+@pytest.mark.parametrize("n_g", [2, 3, 33])
+@pytest.mark.parametrize("eta", [0.0, 2.0])
+def test_mixed_recipe_nodes(stb, ctx, n_g, eta):
+    mesh = inputs.icosphere_mesh(1, 4, T=3.0, jitter=0.0)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    par = lambda e: stb.default_params(m_q=2, n_g=n_g, prec=stb.STB_MIXED, eta_far=e)
+    A = stb.assemble_V(ctx, M, par(eta))
+    assert ctx.kernel_times()["nodes_fp32"][2] > 0
+    B = stb.assemble_V(ctx, M, par(1e300))   # no far pairs: FP64 through the same points
+    (ra, ca, va), (rb, cb, vb) = A.export(), B.export()
+    assert np.array_equal(ra, rb) and np.array_equal(ca, cb)
+    # the mixed assembly's bound per entry
+    assert np.all(np.abs(va - vb) <= 1e-6 * np.abs(vb))
