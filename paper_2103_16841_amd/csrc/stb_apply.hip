@@ -13,72 +13,141 @@
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// One wavefront per 16-row block.  MFMA 16x16x4 (FP32) operand layout:
+// MFMA 16x16x4 (FP32) operand layout:
 //   A: lane l holds A[l % 16][l / 16];  B: lane l holds B[l / 16][l % 16];
 //   D: lane l, register v holds D[4 (l / 16) + v][l % 16].
-// One workgroup (four wavefronts) per 16-row block: wavefront v takes the
-// block's quads v, v + 4, ... (two independent MFMA chains, even and odd
-// steps), and the four partial tiles are summed in LDS in a fixed order.
-__global__ __launch_bounds__(256) void k_bell_mfma(int64_t nblk, int64_t n,
+// One workgroup (eight wavefronts) per 16-row block: wavefronts v and v + 4
+// take the block's quads v, v + 4, ..., the one the even and the other the odd
+// ones of every eight, and the last cnt % 8 go to the even one.  Each has one
+// MFMA chain; the partial tiles are summed in LDS in a fixed order.
+//
+// A quad's 64 values are stored without their zeros (a third is left of an
+// icosphere's quads): a record has the mask of the lanes that have one, the
+// place of the first and the four columns, and lane l's value is found by
+// counting the mask's lower bits.  The zero lanes multiply 0, as they would
+// from a full store, so the sums are those of the full quads.
+//
+// Bound by instructions (the products and the work to place the values): 30,720
+// panels (2.3 million quads, 48 million entries) take 157 us, 132 us of them
+// also without the loads of values and of W.  230 us with full quads (626 MB
+// instead of 266) and four wavefronts per block that request eight quads at a
+// time and wait; 205 us with the next group's loads ahead and the longest
+// blocks first.
+constexpr int kBellAhead = 8;   // quads per group of loads: 8 records of 8 words, a lane each
+
+__global__ __launch_bounds__(512) void k_bell_mfma(int64_t nblk, int64_t n, int64_t ncols,
                                                    const int64_t* __restrict__ bptr,
-                                                   const int32_t* __restrict__ bcol,
+                                                   const int64_t* __restrict__ rowptr,
+                                                   const BellQuad* __restrict__ brec,
                                                    const float* __restrict__ bval,
                                                    const float* __restrict__ w32,
                                                    double* __restrict__ y) {
-  const int64_t blk = blockIdx.x;
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // the last rows, which see the most columns of a causal matrix, first
+  const int64_t blk = nblk - 1 - (int64_t)blockIdx.x;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int kk = lane >> 4, jj = lane & 15;
-  f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+  const int str = wv & 3, odd = wv >> 2;   // the chain: stream of quads, half
   const int64_t q0 = bptr[blk], q1 = bptr[blk + 1];
-  int64_t q = q0 + wv;
-  // eight quads per wave and pass: their values, columns and W rows are all
-  // requested before the first product waits on them
-  for (; q + 28 < q1; q += 32) {
-    float a[8], b[8];
-    int32_t c[8];
+  const int cnt = q1 > q0 + str ? (int)((q1 - q0 - str + 3) >> 2) : 0;   // quads of the stream
+  const int half = (cnt >> 3) << 2;            // its whole eights, split evenly
+  const int len = odd ? half : cnt - half;     // quads of the chain
+  const int* const rec = reinterpret_cast<const int*>(brec + q0 + str + 4 * odd) + (lane & 7);
+  const float* const val = bval + rowptr[blk * 16];
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr int U = kBellAhead;
+  // word lane % 8 of the record of the group's quad lane / 8: quad 2 t + odd of
+  // the stream while t < half, then quad half + t; past the end one without
+  // values, of the zero row of W
+  const int none = (lane & 4) ? (int)ncols : 0;
+  auto ld_rec = [&](int g) {
+    const int t = min(g * U + (lane >> 3), len - 1);
+    return rec[(int64_t)(t < half ? 2 * t : half + t) * (4 * 8)];
+  };
+  auto past_end = [&](int w, int g) {
+    const int in = -(int)(g * U + (lane >> 3) < len);
+    return (w & in) | (none & ~in);
+  };
+  struct Group {
+    float a[U], b[U];
+    uint64_t m[U];
+  };
+  auto ld_group = [&](int r, Group& G) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      a[u] = bval[(q + 4 * u) * 64 + lane];
-      c[u] = bcol[(q + 4 * u) * 4 + kk];
+    for (int u = 0; u < U; ++u) {
+      const uint32_t c = (uint32_t)__shfl(r, u * 8 + 4 + kk, 64);
+      G.b[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(w32) + (c * 64u + jj * 4u));
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) b[u] = c[u] >= 0 ? w32[(int64_t)c[u] * 16 + jj] : 0.f;
+    for (int u = 0; u < U; ++u) {
+      const uint32_t lo = __builtin_amdgcn_readlane(r, u * 8), hi = __builtin_amdgcn_readlane(r, u * 8 + 1);
+      const uint32_t off = __builtin_amdgcn_readlane(r, u * 8 + 2);
+      G.m[u] = (uint64_t)hi << 32 | lo;
+      // a lane without a value reads the next one's place (the store ends in a spare one)
+      G.a[u] = (val + off)[__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u))];
+    }
+  };
+  const int groups = (len + U - 1) / U;
+  Group G;
 #pragma unroll
-    for (int u = 0; u < 8; u += 2) {
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[u], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u + 1], b[u + 1], acc1, 0, 0, 0);
+  for (int u = 0; u < U; ++u) {
+    G.a[u] = G.b[u] = 0.f;
+    G.m[u] = 0ull;
+  }
+  auto products = [&](const Group& P) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_amdgcn_inverse_ballot_w64(P.m[u]) ? P.a[u] : 0.f, P.b[u], acc, 0, 0, 0);
+  };
+  // The next group's values and rows of W and, before them, the records after
+  // it are under way while this group's products wait for theirs.  Two groups
+  // by turns (a copy of one would wait for its loads), the first a group of
+  // zeros (one that starts on loaded values has them loaded at the loop's head
+  // again).
+  if (len > 0) {
+    int r0 = ld_rec(0);
+    for (int g = -1;; g += 2) {
+      Group N;
+      const int r1 = ld_rec(g + 2);
+      ld_group(past_end(r0, g + 1), N);
+      __builtin_amdgcn_sched_barrier(0);
+      products(G);
+      __builtin_amdgcn_sched_barrier(0);
+      r0 = ld_rec(g + 3);
+      ld_group(past_end(r1, g + 2), G);
+      __builtin_amdgcn_sched_barrier(0);
+      products(N);
+      __builtin_amdgcn_sched_barrier(0);
+      if (g + 2 >= groups) break;
     }
   }
-  for (; q < q1; q += 4) {
-    const float a0 = bval[q * 64 + lane];
-    const int32_t c0 = bcol[q * 4 + kk];
-    const float b0 = c0 >= 0 ? w32[(int64_t)c0 * 16 + jj] : 0.f;
-    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b0, acc0, 0, 0, 0);
-  }
-  __shared__ float part[4][4][64];
+  __shared__ float part[8][4][64];
 #pragma unroll
-  for (int v = 0; v < 4; ++v) part[wv][v][lane] = acc0[v] + acc1[v];
+  for (int v = 0; v < 4; ++v) part[wv][v][lane] = acc[v];
   __syncthreads();
   if (wv != 0) return;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    const float t = ((part[0][v][lane] + part[1][v][lane]) + part[2][v][lane]) + part[3][v][lane];
+    float s[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s[k] = part[k][v][lane] + part[4 + k][v][lane];
+    const float t = ((s[0] + s[1]) + s[2]) + s[3];
     const int64_t row = blk * 16 + 4 * kk + v;
     if (row < n) y[row * 16 + jj] = (double)t;
   }
 }
 
+// W in FP32 with a row of zeros after the last one, for the quads' empty columns.
 __global__ void k_to_f32(int64_t m, const double* __restrict__ a, float* __restrict__ b) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < m) b[i] = (float)a[i];
+  if (i < m + 16) b[i] = i < m ? (float)a[i] : 0.f;
 }
 
 void stb_free_blocked(stb_mat* M) {
   dfree(M->d_bptr);
-  dfree(M->d_bcol);
+  dfree(M->d_brec);
   dfree(M->d_bval);
   M->d_bptr = nullptr;
-  M->d_bcol = nullptr;
+  M->d_brec = nullptr;
   M->d_bval = nullptr;
   M->nblk = M->nquad = 0;
 }
@@ -131,17 +200,18 @@ __device__ __forceinline__ int blk_slot(const uint32_t* bits, const int* pre, in
   return pre[c >> 5] + __popc(bits[c >> 5] & ((1u << (c & 31)) - 1u));
 }
 
-// Fills one block: column of every slot, then the values.  Slot s of row r
-// sits at bval[q0 * 64 + 16 s + r] (the MFMA A-operand order), so a range
-// of slots is one contiguous range of bval: the values of kFillSlots slots
-// are scattered into an LDS tile (zero where a row lacks the column) and the
-// tile is copied out whole.
+// Fills one block: column of every slot, then the values.  Slot s of row r is
+// lane 16 (s % 4) + r of quad s / 4 (the MFMA A-operand order): the values of
+// kFillSlots slots are scattered into an LDS tile in that order (zero where a
+// row lacks the column), a wavefront takes a quad's mask, and the values that
+// are not zero go out one after the other from the block's first place in the
+// CSR, which has at least as many.
 __global__ __launch_bounds__(kBlkThreads) void k_blk_fill(int64_t nblk, int64_t n, int64_t ncols,
                                                           const int64_t* __restrict__ rowptr,
                                                           const int32_t* __restrict__ cols,
                                                           const double* __restrict__ vals,
                                                           const int64_t* __restrict__ qptr,
-                                                          int32_t* __restrict__ bcol,
+                                                          BellQuad* __restrict__ brec,
                                                           float* __restrict__ bval) {
   extern __shared__ uint32_t lds[];
   int64_t b = blockIdx.x;
@@ -151,6 +221,8 @@ __global__ __launch_bounds__(kBlkThreads) void k_blk_fill(int64_t nblk, int64_t 
   int* pre = reinterpret_cast<int*>(lds + nw);
   float* tile = reinterpret_cast<float*>(lds + 2 * nw);
   __shared__ int64_t klo[16], khi[16];
+  __shared__ uint64_t mask[kFillSlots / 4];
+  __shared__ uint32_t first_of[kFillSlots / 4 + 1];
   blk_mark(b, n, rowptr, cols, bits, nw);
   // exclusive prefix of popcounts over the words: per-thread chunk, then a
   // serial scan of the 256 chunk sums by thread 0
@@ -175,18 +247,20 @@ __global__ __launch_bounds__(kBlkThreads) void k_blk_fill(int64_t nblk, int64_t 
     int slot = pre[w];
     while (m) {
       int bit = __ffs(m) - 1;
-      bcol[q0 * 4 + slot] = w * 32 + bit;
+      brec[q0 + (slot >> 2)].col[slot & 3] = w * 32 + bit;
       ++slot;
       m &= m - 1;
     }
   }
-  for (int64_t k = nslot + threadIdx.x; k < nq * 4; k += kBlkThreads) bcol[q0 * 4 + k] = -1;
-  for (int64_t k = (int64_t)nslot * 16 + threadIdx.x; k < nq * 64; k += kBlkThreads) bval[q0 * 64 + k] = 0.f;
+  for (int64_t k = nslot + threadIdx.x; k < nq * 4; k += kBlkThreads) brec[q0 + (k >> 2)].col[k & 3] = (int32_t)ncols;
   const int64_t rb = b * 16;
+  float* const val = bval + rowptr[rb];
+  uint32_t run = 0;   // values of the passes so far
   const int nr = (int)((rb + 16 < n ? rb + 16 : n) - rb);
   for (int s0 = 0; s0 < nslot; s0 += kFillSlots) {
     const int ns = nslot - s0 < kFillSlots ? nslot - s0 : kFillSlots;
-    for (int e = threadIdx.x; e < ns * 16; e += kBlkThreads) tile[e] = 0.f;
+    const int nqs = (ns + 3) >> 2;   // whole quads: the last pass's tail is zero
+    for (int e = threadIdx.x; e < nqs * 64; e += kBlkThreads) tile[e] = 0.f;
     if ((int)threadIdx.x < 2 * nr) {
       // the row's first entry with slot >= s0 (lanes 0..nr-1) or >= s0 + ns
       // (lanes nr..2nr-1): slots increase along a row's sorted columns
@@ -205,7 +279,40 @@ __global__ __launch_bounds__(kBlkThreads) void k_blk_fill(int64_t nblk, int64_t 
       for (int64_t k = klo[r] + threadIdx.x; k < khi[r]; k += kBlkThreads)
         tile[(blk_slot(bits, pre, cols[k]) - s0) * 16 + r] = (float)vals[k];
     __syncthreads();
-    for (int e = threadIdx.x; e < ns * 16; e += kBlkThreads) bval[q0 * 64 + (int64_t)s0 * 16 + e] = tile[e];
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int q = wv; q < nqs; q += kBlkThreads / 64) {
+      const uint64_t m = __ballot(tile[q * 64 + lane] != 0.f);
+      if (lane == 0) mask[q] = m;
+    }
+    __syncthreads();
+    // exclusive prefix of the quads' counts: two per lane of the first wavefront
+    static_assert(kFillSlots / 4 == 128, "two quads per lane");
+    if (wv == 0) {
+      const uint32_t n0 = 2 * lane < nqs ? (uint32_t)__popcll(mask[2 * lane]) : 0u;
+      const uint32_t n1 = 2 * lane + 1 < nqs ? (uint32_t)__popcll(mask[2 * lane + 1]) : 0u;
+      uint32_t incl = n0 + n1;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t v = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += v;
+      }
+      first_of[2 * lane] = run + incl - n0 - n1;
+      first_of[2 * lane + 1] = run + incl - n1;
+      if (lane == 63) first_of[128] = run + incl;
+    }
+    __syncthreads();
+    for (int q = wv; q < nqs; q += kBlkThreads / 64) {
+      const uint64_t m = mask[q];
+      const uint32_t off = first_of[q];
+      if (lane == 0) {
+        BellQuad& R = brec[q0 + (s0 >> 2) + q];
+        R.mask = m;
+        R.off = off;
+        R.pad = 0u;
+      }
+      if ((m >> lane) & 1ull) val[off + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = tile[q * 64 + lane];
+    }
+    run = first_of[128];
     __syncthreads();
   }
 }
@@ -228,13 +335,15 @@ stb_status stb_build_blocked(stb_ctx* ctx, stb_mat* M, hipStream_t st) {
   if (s) return s;
   int64_t nquad = 0;
   HIPCHK(ctx, hipMemcpy(&nquad, M->d_bptr + nblk, sizeof(int64_t), hipMemcpyDeviceToHost));
-  HIPCHK(ctx, dalloc(&M->d_bcol, (size_t)nquad * 4));
-  HIPCHK(ctx, dalloc(&M->d_bval, (size_t)nquad * 64));
+  int64_t nnz = 0;
+  HIPCHK(ctx, hipMemcpy(&nnz, M->d_rowptr + n, sizeof(int64_t), hipMemcpyDeviceToHost));
+  HIPCHK(ctx, dalloc(&M->d_brec, (size_t)nquad));
+  HIPCHK(ctx, dalloc(&M->d_bval, (size_t)nnz + 1));
   const size_t lds_fill = lds + sizeof(float) * 16 * kFillSlots;
   HIPCHK(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_blk_fill),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_fill));
   hipLaunchKernelGGL(k_blk_fill, dim3((unsigned)nblk), dim3(kBlkThreads), lds_fill, st, nblk, n, ncols,
-                     M->d_rowptr, M->d_cols, M->d_vals, M->d_bptr, M->d_bcol, M->d_bval);
+                     M->d_rowptr, M->d_cols, M->d_vals, M->d_bptr, M->d_brec, M->d_bval);
   HIPCHK(ctx, hipGetLastError());
   M->nblk = nblk;
   M->nquad = nquad;
@@ -247,14 +356,14 @@ stb_status stb_apply16_dev(stb_ctx* ctx, stb_mat* M, const double* w, double* y,
     if (s) return s;
   }
   float* w32 = nullptr;
-  HIPCHK(ctx, dalloc(&w32, (size_t)mat_ncols(M) * 16));
+  HIPCHK(ctx, dalloc(&w32, ((size_t)mat_ncols(M) + 1) * 16));
   int64_t m = mat_ncols(M) * 16;
   if (m > 0) {
-    hipLaunchKernelGGL(k_to_f32, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, m, w, w32);
+    hipLaunchKernelGGL(k_to_f32, dim3((unsigned)((m + 16 + 255) / 256)), dim3(256), 0, st, m, w, w32);
   }
   if (M->nblk > 0) {
-    hipLaunchKernelGGL(k_bell_mfma, dim3((unsigned)M->nblk), dim3(256), 0, st, M->nblk, M->n, M->d_bptr,
-                       M->d_bcol, M->d_bval, w32, y);
+    hipLaunchKernelGGL(k_bell_mfma, dim3((unsigned)M->nblk), dim3(512), 0, st, M->nblk, M->n, mat_ncols(M), M->d_bptr,
+                       M->d_rowptr, M->d_brec, M->d_bval, w32, y);
   }
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -271,7 +380,7 @@ stb_status stb_apply16_dev(stb_ctx* ctx, stb_mat* M, const double* w, double* y,
 // device the library runs on holds one copy (16 MiB) until the process ends;
 // every call on a device shares it, so calls that overlap on one device race.
 constexpr int64_t kNoAllocMaxCols = kMaxBlockedN;
-static __device__ __align__(256) float scratch[kNoAllocMaxCols * 16];
+static __device__ __align__(256) float scratch[(kNoAllocMaxCols + 1) * 16];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -312,10 +421,10 @@ extern "C" stb_status stb_apply16_noalloc(stb_ctx* ctx, const stb_mat* M, const 
   HIPCHK(ctx, hipSetDevice(ctx->device));
   const int64_t m = ncols * 16;
   if (m > 0)
-    hipLaunchKernelGGL(k_to_f32, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, m, w_dev, w32);
+    hipLaunchKernelGGL(k_to_f32, dim3((unsigned)((m + 16 + 255) / 256)), dim3(256), 0, st, m, w_dev, w32);
   if (M->nblk > 0)
-    hipLaunchKernelGGL(k_bell_mfma, dim3((unsigned)M->nblk), dim3(256), 0, st, M->nblk, M->n, M->d_bptr,
-                       M->d_bcol, M->d_bval, (const float*)w32, y_dev);
+    hipLaunchKernelGGL(k_bell_mfma, dim3((unsigned)M->nblk), dim3(512), 0, st, M->nblk, M->n, mat_ncols(M), M->d_bptr,
+                       M->d_rowptr, M->d_brec, M->d_bval, (const float*)w32, y_dev);
   HIPCHK(ctx, hipGetLastError());
   return STB_OK;
 }

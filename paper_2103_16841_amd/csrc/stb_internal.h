@@ -97,6 +97,16 @@ struct stb_mesh {
   std::mutex tree_mu;
 };
 
+// One quad of the blocked copy: 16 rows by four columns, of which only the
+// values other than zero are stored.
+struct BellQuad {
+  uint64_t mask;    // lanes (MFMA A-operand order) that have a value
+  uint32_t off;     // of the first one, from the block's first CSR entry
+  uint32_t pad;
+  int32_t col[4];   // the number of columns: none
+};
+static_assert(sizeof(BellQuad) == 32, "eight words per record");
+
 struct stb_mat {
   stb_ctx* ctx = nullptr;
   int64_t n = 0, nnz = 0, n_causal = 0;
@@ -119,8 +129,8 @@ struct stb_mat {
   // union of its rows' columns in quads; FP32 values in MFMA A-operand order
   int64_t nblk = 0, nquad = 0;
   int64_t* d_bptr = nullptr;     // [nblk + 1] quad offsets
-  int32_t* d_bcol = nullptr;     // [nquad * 4] column of each quad slot (-1 = pad)
-  float* d_bval = nullptr;       // [nquad * 64]
+  BellQuad* d_brec = nullptr;    // [nquad]
+  float* d_bval = nullptr;       // [nnz + 1]: the quads' values other than zero, block by block
 };
 
 

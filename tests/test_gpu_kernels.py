@@ -158,3 +158,25 @@ def test_mixed_recipe_nodes(stb, ctx, n_g, eta):
     assert np.array_equal(ra, rb) and np.array_equal(ca, cb)
     # the mixed assembly's bound per entry
     assert np.all(np.abs(va - vb) <= 1e-6 * np.abs(vb))
+
+
+# blocks of fewer rows than 16, chains shorter than a group of loads, remainders
+# of groups, and long chains; the quads' stored values against the CSR's
+@pytest.mark.parametrize("level,slabs", [(0, 1), (0, 3), (1, 5), (2, 9)])
+def test_sixteen_right_hand_sides(stb, ctx, level, slabs):
+    mesh = inputs.icosphere_mesh(level, slabs)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    A = stb.assemble_V(ctx, M, stb.default_params(m_q=1, n_g=2))
+    rows = np.unique(np.concatenate([np.arange(min(A.n, 40)), np.arange(max(A.n - 40, 0), A.n)]))
+    D = _rows_of(A, rows)
+    W = np.random.default_rng(3).standard_normal((A.n, 16))
+    Y = A.apply(W)
+    ref = D @ W
+    # products of rounded factors (2 units each) summed in FP32: terms + 3 units of the terms' size
+    bound = ((D != 0).sum(1) + 3)[:, None] * 2.0 ** -24
+    assert np.all(np.abs(Y[rows] - ref) <= bound * (np.abs(D) @ np.abs(W)))
+    # every column alone: unit vectors pick single entries, exactly the FP32 values
+    E = np.zeros((A.n, 16))
+    pick = np.linspace(0, A.n - 1, 16).astype(int)
+    E[pick, np.arange(16)] = 1.0
+    assert np.array_equal(A.apply(E)[rows], D[:, pick].astype(np.float32).astype(np.float64))
