@@ -234,7 +234,9 @@ stb_status stb_tree_cull(stb_ctx* ctx, stb_mesh* m, int nmin, int64_t np, const 
 void stb_free_tree(stb_mesh* m);
 // Candidates of evaluation points by the search p.lit_search selects (the
 // cluster tree or the flat cull); records the surviving leaves in
-// ctx->work.
+// ctx->work.  stb_count_points: only their number.
+stb_status stb_count_points(stb_ctx* ctx, stb_mesh* m, const stb_quad_params& p, int64_t np, const double* d_pts,
+                            int64_t* nnz);
 stb_status stb_cull_points(stb_ctx* ctx, stb_mesh* m, const stb_quad_params& p, int64_t np,
                            const double* d_pts, int64_t** d_rowptr, int32_t** d_cols, int32_t** d_rowof,
                            int64_t* nnz);

@@ -151,95 +151,147 @@ __device__ __forceinline__ bool maybe_lit(const ApexBox& b, const CullPanel& T) 
   return (b.thi - T.tmin > lb - slack) && (b.tlo - T.tmax < ub + slack);
 }
 
-constexpr int kCullThreads = 256;
-// Rows per block: each panel record read from L2 serves this many rows.
-constexpr int kCullRows = 8;
+// The same test in FP32 with its error: sure when the distance is clear of
+// both bounds by more than a few FP32 units of everything that enters them
+// (the slack of the exact test is a hundredth of that).  Lanes that are not
+// sure (a few in a thousand wavefronts on the meshes here; NaN and values out
+// of FP32's range among them) take the exact test, so the candidates are its
+// candidates.  The 16 FP32 operations replace some 30 FP64 ones with a square
+// root (30,720 panels and as many rows: count 0.74 -> 0.40 ms, fill 0.95 ->
+// 0.64 ms).
+struct RowCull {
+  float cx, cy, cz, up, lo, err;   // thi + rho, tlo - rho
+};
+struct PanelCull {
+  float cx, cy, cz, up, lo, err;   // rad - tmin, -rad - tmax
+};
+constexpr float kCullErr = 4e-6f;
 
-__global__ __launch_bounds__(kCullThreads) void k_cull_count(int64_t nrows,
-                                                             const ApexBox* __restrict__ rows,
-                                                             int64_t nt,
-                                                             const TrialRec* __restrict__ T,
-                                                             int64_t* __restrict__ cnt) {
-  const int64_t i0 = (int64_t)blockIdx.x * kCullRows;
-  if (i0 >= nrows) return;
-  const int nr = (int)std::min<int64_t>(kCullRows, nrows - i0);
-  __shared__ ApexBox s_b[kCullRows];
-  __shared__ int red[kCullRows][kCullThreads];
-  if ((int)threadIdx.x < nr) s_b[threadIdx.x] = rows[i0 + threadIdx.x];
+__device__ __forceinline__ RowCull row_cull(const ApexBox& b) {
+  return RowCull{(float)b.cx, (float)b.cy, (float)b.cz, (float)(b.thi + b.rho), (float)(b.tlo - b.rho),
+                 kCullErr * (float)(fabs(b.cx) + fabs(b.cy) + fabs(b.cz) + fabs(b.thi) + fabs(b.tlo) + b.rho)};
+}
+__device__ __forceinline__ PanelCull panel_cull(const CullPanel& T) {
+  return PanelCull{(float)T.cx, (float)T.cy, (float)T.cz, (float)(T.rad - T.tmin), (float)(-T.rad - T.tmax),
+                   kCullErr * (float)(fabs(T.cx) + fabs(T.cy) + fabs(T.cz) + fabs(T.tmin) + fabs(T.tmax) + T.rad +
+                                      T.diam)};
+}
+
+// Lanes (of those with `in`) whose panel may be lit from the row: a ballot.
+__device__ __forceinline__ uint64_t lit_ballot(bool in, const RowCull& r, const PanelCull& p, const ApexBox& b,
+                                               const TrialRec* T) {
+  const float dx = r.cx - p.cx, dy = r.cy - p.cy, dz = r.cz - p.cz;
+  const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+  const float d = __builtin_amdgcn_sqrtf(d2);
+  const float err = fmaf(kCullErr, d, r.err + p.err);
+  const float over = (r.up + p.up) - d, under = d - (r.lo + p.lo);   // both above 0: may be lit
+  const bool normal = d2 > 1e-30f;   // below, the squares may have underflowed
+  bool yes = normal && over > err && under > err;
+  const bool no = normal && (over < -err || under < -err);
+  if (__any(in && !yes && !no)) {
+    if (!yes && !no) yes = maybe_lit(b, cull_panel(*T));
+  }
+  return __ballot(in && yes);
+}
+
+// The cull's work is split over rows and panels: a workgroup's four wavefronts
+// take 64 rows, 16 each, and one segment of the panels (gridDim.y of them), 64
+// panels at a time, a lane each.  A wavefront keeps its panels in registers
+// over its rows and its counts in scalars, so it meets no other one, and the
+// four read the same panels at about the same time (a panel's fields are one
+// 128-byte line).  Segments are taken until about kCullWaves wavefronts are under
+// way (1,000 points and 30,720 panels gave 125 workgroups and 155 + 287 us
+// with one workgroup per eight rows that walked all panels, with two barriers
+// per 256 of them in the fill; 31 + 42 us so, with the FP32 test above).
+constexpr int kCullRows = 16;      // rows of a wavefront
+constexpr int kCullBlkRows = 4 * kCullRows;
+constexpr int64_t kCullWaves = 8192;
+
+int64_t cull_segments(int64_t nrows, int64_t nt) {
+  const int64_t groups = std::max<int64_t>((nrows + kCullRows - 1) / kCullRows, 1);
+  const int64_t most = std::min<int64_t>(std::max<int64_t>((nt + 63) / 64, 1), 1024);
+  return std::min(std::max<int64_t>(kCullWaves / groups, 1), most);
+}
+
+// The panels [j0, j1) of segment g.
+__device__ __forceinline__ void cull_segment(int64_t nt, int64_t& j0, int64_t& j1) {
+  const int64_t len = ((nt + gridDim.y - 1) / gridDim.y + 63) & ~(int64_t)63;
+  j0 = (int64_t)blockIdx.y * len;
+  j1 = j0 + len < nt ? j0 + len : nt;
+}
+
+// Candidates of every row and segment (row-major).
+__global__ __launch_bounds__(256) void k_cull_count(int64_t nrows, const ApexBox* __restrict__ rows, int64_t nt,
+                                                    const TrialRec* __restrict__ T, int64_t* __restrict__ cnt) {
+  __shared__ RowCull s_r[kCullBlkRows];
+  const int64_t b0 = (int64_t)blockIdx.x * kCullBlkRows;
+  for (int r = threadIdx.x; r < kCullBlkRows; r += 256) s_r[r] = row_cull(rows[b0 + r < nrows ? b0 + r : nrows - 1]);
   __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const RowCull* const row = s_r + wave * kCullRows;
+  const int64_t i0 = b0 + wave * kCullRows;
+  const int nr = (int)(nrows - i0 < kCullRows ? nrows - i0 : kCullRows);   // may be below 1
+  int64_t j0, j1;
+  cull_segment(nt, j0, j1);
   int c[kCullRows];
 #pragma unroll
   for (int r = 0; r < kCullRows; ++r) c[r] = 0;
-  for (int64_t j = threadIdx.x; j < nt; j += kCullThreads) {
-    const CullPanel P = cull_panel(T[j]);
+  for (; j0 < j1; j0 += 64) {
+    const bool in = j0 + lane < j1;
+    const TrialRec* const Tj = T + (in ? j0 + lane : j1 - 1);
+    const PanelCull P = panel_cull(cull_panel(*Tj));
 #pragma unroll
     for (int r = 0; r < kCullRows; ++r)
-      if (r < nr) c[r] += maybe_lit(s_b[r], P) ? 1 : 0;
+      if (r < nr) c[r] += __popcll(lit_ballot(in, row[r], P, rows[i0 + r], Tj));
   }
+  int v = 0;
 #pragma unroll
-  for (int r = 0; r < kCullRows; ++r) red[r][threadIdx.x] = c[r];
-  __syncthreads();
-  for (int off = kCullThreads / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off)
-#pragma unroll
-      for (int r = 0; r < kCullRows; ++r) red[r][threadIdx.x] += red[r][threadIdx.x + off];
-    __syncthreads();
-  }
-  if ((int)threadIdx.x < nr) cnt[i0 + threadIdx.x] = red[threadIdx.x][0];
+  for (int r = 0; r < kCullRows; ++r) v = lane == r ? c[r] : v;
+  if (lane < kCullRows && i0 + lane < nrows) cnt[(i0 + lane) * gridDim.y + blockIdx.y] = v;
 }
 
-// Fill the candidate columns of each row in ascending order: per 256-wide
-// chunk of panels (read once for the block's rows), a wavefront ballot +
-// mbcnt gives each lane its rank inside the wave per row; an LDS prefix
-// over the four waves orders the chunk.
-__global__ __launch_bounds__(kCullThreads) void k_cull_fill(int64_t nrows,
-                                                            const ApexBox* __restrict__ rows,
-                                                            int64_t nt,
-                                                            const TrialRec* __restrict__ T,
-                                                            const int64_t* __restrict__ rowptr,
-                                                            int32_t* __restrict__ cols,
-                                                            int32_t* __restrict__ rowof) {
-  const int64_t i0 = (int64_t)blockIdx.x * kCullRows;
-  if (i0 >= nrows) return;
-  const int nr = (int)std::min<int64_t>(kCullRows, nrows - i0);
-  constexpr int kWaves = kCullThreads / 64;
-  __shared__ ApexBox s_b[kCullRows];
-  __shared__ int wave_cnt[kCullRows][kWaves];
-  if ((int)threadIdx.x < nr) s_b[threadIdx.x] = rows[i0 + threadIdx.x];
+// The rows' starts from the scanned counts of all segments.
+__global__ void k_cull_rowptr(int64_t nrows, int64_t nseg, const int64_t* __restrict__ start,
+                              int64_t* __restrict__ rowptr) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i <= nrows) rowptr[i] = start[i * nseg];
+}
+
+// Fill the candidate columns of each row in ascending order, and the row of
+// each: a wavefront starts where its segment of the row does and ranks its
+// lanes by a ballot.
+__global__ __launch_bounds__(256) void k_cull_fill(int64_t nrows, const ApexBox* __restrict__ rows, int64_t nt,
+                                                   const TrialRec* __restrict__ T, const int64_t* __restrict__ start,
+                                                   int32_t* __restrict__ cols, int32_t* __restrict__ rowof) {
+  __shared__ RowCull s_r[kCullBlkRows];
+  const int64_t b0 = (int64_t)blockIdx.x * kCullBlkRows;
+  for (int r = threadIdx.x; r < kCullBlkRows; r += 256) s_r[r] = row_cull(rows[b0 + r < nrows ? b0 + r : nrows - 1]);
   __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const RowCull* const row = s_r + wave * kCullRows;
+  const int64_t i0 = b0 + wave * kCullRows;
+  const int nr = (int)(nrows - i0 < kCullRows ? nrows - i0 : kCullRows);   // may be below 1
+  int64_t j0, j1;
+  cull_segment(nt, j0, j1);
   int64_t base[kCullRows];
 #pragma unroll
-  for (int r = 0; r < kCullRows; ++r) base[r] = r < nr ? rowptr[i0 + r] : 0;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int64_t j0 = 0; j0 < nt; j0 += kCullThreads) {
-    const int64_t j = j0 + threadIdx.x;
-    CullPanel P{};
-    if (j < nt) P = cull_panel(T[j]);
-    uint32_t pm = 0;   // rows for which panel j is a candidate
-    int rank[kCullRows];
+  for (int r = 0; r < kCullRows; ++r) base[r] = r < nr ? start[(i0 + r) * gridDim.y + blockIdx.y] : 0;
+  for (; j0 < j1; j0 += 64) {
+    const bool in = j0 + lane < j1;
+    const TrialRec* const Tj = T + (in ? j0 + lane : j1 - 1);
+    const PanelCull P = panel_cull(cull_panel(*Tj));
 #pragma unroll
     for (int r = 0; r < kCullRows; ++r) {
-      const bool p = r < nr && j < nt && maybe_lit(s_b[r], P);
-      const uint64_t bal = __ballot(p);
-      rank[r] = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
-      if (lane == 0) wave_cnt[r][wave] = __popcll(bal);
-      pm |= (p ? 1u : 0u) << r;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kCullRows; ++r) {
-      int off = 0, tot = 0;
-      for (int w = 0; w < kWaves; ++w) {
-        off += w < wave ? wave_cnt[r][w] : 0;
-        tot += wave_cnt[r][w];
+      if (r >= nr) break;
+      const uint64_t bal = lit_ballot(in, row[r], P, rows[i0 + r], Tj);
+      if ((bal >> lane) & 1ull) {
+        const int64_t at =
+            base[r] + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
+        cols[at] = (int32_t)(j0 + lane);
+        rowof[at] = (int32_t)(i0 + r);
       }
-      if ((pm >> r) & 1u) {
-        cols[base[r] + off + rank[r]] = (int32_t)j;
-        rowof[base[r] + off + rank[r]] = (int32_t)(i0 + r);
-      }
-      base[r] += tot;
+      base[r] += __popcll(bal);
     }
-    __syncthreads();
   }
 }
 
@@ -564,67 +616,114 @@ void stb_point_boxes(stb_ctx* ctx, int64_t np, const double* d_pts, ApexBox* d_b
                        d_pts, d_box);
 }
 
+// The start of every row's and segment's candidates (nrows * nseg + 1, kept
+// block): the count pass and its scan, enqueued on ctx's stream.
+static stb_status cull_starts(stb_ctx* ctx, int64_t nrows, const ApexBox* d_rows, const stb_mesh* m, int64_t nseg,
+                              int64_t** start) {
+  int64_t* d_cnt = nullptr;
+  *start = nullptr;
+  if (kalloc(ctx, &d_cnt, (size_t)(nrows * nseg)) != hipSuccess ||
+      kalloc(ctx, start, (size_t)(nrows * nseg) + 1) != hipSuccess) {
+    ctx_keep(ctx, d_cnt);
+    return fail(ctx, STB_E_NO_MEMORY, "cull counts");
+  }
+  if (nrows > 0)
+    hipLaunchKernelGGL(k_cull_count, dim3((unsigned)((nrows + kCullBlkRows - 1) / kCullBlkRows), (unsigned)nseg),
+                       dim3(256), 0, ctx->stream, nrows, d_rows, m->nt, m->d_trial, d_cnt);
+  hipError_t e = hipGetLastError();
+  stb_status s = e == hipSuccess ? device_exclusive_scan(ctx, d_cnt, *start, nrows * nseg)
+                                 : fail(ctx, STB_E_DEVICE, "cull count: %s", hipGetErrorString(e));
+  ctx_keep(ctx, d_cnt);
+  if (s) { ctx_keep(ctx, *start); *start = nullptr; }
+  return s;
+}
+
 // Exclusive prefix of the candidate counts of these rows (count pass only),
 // copied to the host.
 stb_status stb_cull_rowptr(stb_ctx* ctx, int64_t nrows, const ApexBox* d_rows, const stb_mesh* m,
                            int64_t* rowptr_host) {
   rowptr_host[0] = 0;
   if (nrows <= 0) return STB_OK;
-  int64_t *d_cnt = nullptr, *d_scan = nullptr;
-  HIPCHK(ctx, dalloc(&d_cnt, (size_t)nrows));
-  if (dalloc(&d_scan, (size_t)nrows + 1) != hipSuccess) {
-    dfree(d_cnt);
+  const int64_t nseg = cull_segments(nrows, m->nt);
+  int64_t *d_start = nullptr, *d_rp = nullptr;
+  stb_status s = cull_starts(ctx, nrows, d_rows, m, nseg, &d_start);
+  if (s) return s;
+  if (kalloc(ctx, &d_rp, (size_t)nrows + 1) != hipSuccess) {
+    ctx_keep(ctx, d_start);
     return fail(ctx, STB_E_NO_MEMORY, "cull counts");
   }
-  hipLaunchKernelGGL(k_cull_count, dim3((unsigned)((nrows + kCullRows - 1) / kCullRows)), dim3(kCullThreads), 0,
-                     ctx->stream, nrows,
-                     d_rows, m->nt, m->d_trial, d_cnt);
+  hipLaunchKernelGGL(k_cull_rowptr, dim3((unsigned)(nrows / 256 + 1)), dim3(256), 0, ctx->stream, nrows, nseg,
+                     d_start, d_rp);
   hipError_t e = hipGetLastError();
-  stb_status s = e == hipSuccess ? device_exclusive_scan(ctx, d_cnt, d_scan, nrows)
-                                 : fail(ctx, STB_E_DEVICE, "cull count: %s", hipGetErrorString(e));
-  if (s == STB_OK &&
-      hipMemcpy(rowptr_host, d_scan, sizeof(int64_t) * (nrows + 1), hipMemcpyDeviceToHost) != hipSuccess)
-    s = fail(ctx, STB_E_DEVICE, "cull count copy");
-  dfree(d_cnt);
-  dfree(d_scan);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(rowptr_host, d_rp, sizeof(int64_t) * (nrows + 1), hipMemcpyDeviceToHost, ctx->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  if (e != hipSuccess) s = fail(ctx, STB_E_DEVICE, "cull count copy: %s", hipGetErrorString(e));
+  ctx_keep(ctx, d_start);
+  ctx_keep(ctx, d_rp);
   return s;
 }
 
 // Number of candidates the cull would produce for these rows.
 stb_status stb_cull_count(stb_ctx* ctx, int64_t nrows, const ApexBox* d_rows, const stb_mesh* m,
                           int64_t* nnz) {
-  std::vector<int64_t> rp((size_t)std::max<int64_t>(nrows, 0) + 1);
-  stb_status s = stb_cull_rowptr(ctx, nrows, d_rows, m, rp.data());
-  *nnz = rp.back();
-  return s;
+  *nnz = 0;
+  if (nrows <= 0) return STB_OK;
+  const int64_t nseg = cull_segments(nrows, m->nt);
+  int64_t* d_start = nullptr;
+  stb_status s = cull_starts(ctx, nrows, d_rows, m, nseg, &d_start);
+  if (s) return s;
+  hipError_t e = hipMemcpyAsync(nnz, d_start + nrows * nseg, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  ctx_keep(ctx, d_start);
+  return e == hipSuccess ? STB_OK : fail(ctx, STB_E_DEVICE, "cull count copy: %s", hipGetErrorString(e));
 }
 
 // Cull rows (apex boxes) against all trial panels into CSR candidates, with
 // the row of every candidate alongside.
 stb_status stb_cull(stb_ctx* ctx, int64_t nrows, const ApexBox* d_rows, const stb_mesh* m,
                        int64_t** d_rowptr, int32_t** d_cols, int32_t** d_rowof, int64_t* nnz, bool lend) {
-  int64_t* d_cnt = nullptr;
-  HIPCHK(ctx, dalloc(&d_cnt, (size_t)nrows));
-  HIPCHK(ctx, dalloc(d_rowptr, (size_t)nrows + 1));
-  if (nrows > 0) {
-    hipLaunchKernelGGL(k_cull_count, dim3((unsigned)((nrows + kCullRows - 1) / kCullRows)), dim3(kCullThreads),
-                       0, ctx->stream,
-                       nrows, d_rows, m->nt, m->d_trial, d_cnt);
-    HIPCHK(ctx, hipGetLastError());
-  }
-  stb_status s = device_exclusive_scan(ctx, d_cnt, *d_rowptr, nrows);
-  dfree(d_cnt);
+  const int64_t nseg = cull_segments(nrows, m->nt);
+  int64_t* d_start = nullptr;
+  stb_status s = cull_starts(ctx, nrows, d_rows, m, nseg, &d_start);
   if (s) return s;
-  HIPCHK(ctx, hipMemcpy(nnz, *d_rowptr + nrows, sizeof(int64_t), hipMemcpyDeviceToHost));
-  HIPCHK(ctx, lend ? kalloc(ctx, d_cols, (size_t)*nnz) : dalloc(d_cols, (size_t)*nnz));
-  HIPCHK(ctx, lend ? kalloc(ctx, d_rowof, (size_t)*nnz) : dalloc(d_rowof, (size_t)*nnz));
-  if (nrows > 0) {
-    hipLaunchKernelGGL(k_cull_fill, dim3((unsigned)((nrows + kCullRows - 1) / kCullRows)), dim3(kCullThreads),
-                       0, ctx->stream,
-                       nrows, d_rows, m->nt, m->d_trial, *d_rowptr, *d_cols, *d_rowof);
+  auto run = [&]() -> stb_status {
+    HIPCHK(ctx, dalloc(d_rowptr, (size_t)nrows + 1));
+    hipLaunchKernelGGL(k_cull_rowptr, dim3((unsigned)(nrows / 256 + 1)), dim3(256), 0, ctx->stream, nrows, nseg,
+                       d_start, *d_rowptr);
     HIPCHK(ctx, hipGetLastError());
+    HIPCHK(ctx, hipMemcpy(nnz, d_start + nrows * nseg, sizeof(int64_t), hipMemcpyDeviceToHost));
+    HIPCHK(ctx, lend ? kalloc(ctx, d_cols, (size_t)*nnz) : dalloc(d_cols, (size_t)*nnz));
+    HIPCHK(ctx, lend ? kalloc(ctx, d_rowof, (size_t)*nnz) : dalloc(d_rowof, (size_t)*nnz));
+    if (nrows > 0) {
+      hipLaunchKernelGGL(k_cull_fill, dim3((unsigned)((nrows + kCullBlkRows - 1) / kCullBlkRows), (unsigned)nseg),
+                         dim3(256), 0, ctx->stream, nrows, d_rows, m->nt, m->d_trial, d_start, *d_cols, *d_rowof);
+      HIPCHK(ctx, hipGetLastError());
+    }
+    return STB_OK;
+  };
+  s = run();
+  ctx_keep(ctx, d_start);
+  return s;
+}
+
+// The number of candidates stb_cull_points would find.
+stb_status stb_count_points(stb_ctx* ctx, stb_mesh* m, const stb_quad_params& p, int64_t np, const double* d_pts,
+                            int64_t* nnz) {
+  if (p.lit_search == STB_LIT_TREE) {
+    int64_t* rowptr = nullptr;
+    int32_t *cols = nullptr, *rowof = nullptr;
+    stb_status s = stb_cull_points(ctx, m, p, np, d_pts, &rowptr, &cols, &rowof, nnz);
+    dfree(rowptr); ctx_keep(ctx, cols); ctx_keep(ctx, rowof);
+    return s;
   }
-  return STB_OK;
+  ApexBox* d_box = nullptr;
+  if (kalloc(ctx, &d_box, (size_t)std::max<int64_t>(np, 1)) != hipSuccess)
+    return fail(ctx, STB_E_NO_MEMORY, "point boxes");
+  stb_point_boxes(ctx, np, d_pts, d_box);
+  stb_status s = stb_cull_count(ctx, np, d_box, m, nnz);
+  ctx_keep(ctx, d_box);
+  return s;
 }
 
 stb_status stb_cull_points(stb_ctx* ctx, stb_mesh* m, const stb_quad_params& p, int64_t np,

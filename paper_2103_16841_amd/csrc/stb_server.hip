@@ -138,11 +138,7 @@ stb_status footprint(stb_ctx* c, const ServedMesh& sm, const stb_request& r, int
   int64_t nnz = 0;
   hipError_t e = hipMemcpyAsync(pts, r.pts, sizeof(double) * 4 * r.np, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) {
-    int64_t* rp = nullptr;
-    int32_t *cols = nullptr, *rowof = nullptr;
-    stb_quad_params p = stb_default_params();
-    s = stb_cull_points(c, sm.mesh, p, r.np, pts, &rp, &cols, &rowof, &nnz);
-    dfree(rp); ctx_keep(c, cols); ctx_keep(c, rowof);
+    s = stb_count_points(c, sm.mesh, stb_default_params(), r.np, pts, &nnz);
   } else {
     s = stb_fail(c, STB_E_DEVICE, "copy in");
   }

@@ -180,3 +180,25 @@ def test_sixteen_right_hand_sides(stb, ctx, level, slabs):
     pick = np.linspace(0, A.n - 1, 16).astype(int)
     E[pick, np.arange(16)] = 1.0
     assert np.array_equal(A.apply(E)[rows], D[:, pick].astype(np.float32).astype(np.float64))
+
+
+# one row, both sides of a wavefront's 16 and a workgroup's 64 rows, panels that
+# are no multiple of 64, points on light cones of vertices (the bounds' ends), and
+# a mesh far from the origin, where single precision decides little
+@pytest.mark.parametrize("npts", [1, 15, 17, 63, 65, 130])
+@pytest.mark.parametrize("shift", [0.0, 64.0])
+def test_cull_rows_and_segments(stb, ctx, npts, shift):
+    import oracle
+    mesh = inputs.icosphere_mesh(0, 3, T=2.0)
+    vtx = np.ascontiguousarray(mesh.vtx + shift)
+    M = stb.Mesh(ctx, vtx, mesh.tets)
+    w = np.random.default_rng(2).standard_normal(mesh.nt)
+    pts = inputs.shell_points(npts, mesh.T, seed=npts)
+    k = np.arange(0, npts, 3)   # t - t_v = |x - x_v| for a vertex v
+    v = mesh.vtx[k % mesh.nv]
+    pts[k, 0] = v[:, 0] + np.linalg.norm(pts[k, 1:] - v[:, 1:], axis=1)
+    pts = pts + shift
+    u = stb.potential_S(ctx, M, w, pts)
+    ref, mag = oracle.potential(vtx, mesh.tets, w, pts), oracle.potential(vtx, mesh.tets, np.abs(w), pts)
+    # the potential's parity bound, at coordinates known to 64 eps when shifted
+    assert np.all(np.abs(u - ref) <= 1e-10 * np.maximum(mag, 1e-3 * mag.max()))
