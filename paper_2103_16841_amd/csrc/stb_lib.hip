@@ -282,8 +282,7 @@ __global__ __launch_bounds__(256) void k_cull_fill(int64_t nrows, const ApexBox*
     const PanelCull P = panel_cull(cull_panel(*Tj));
 #pragma unroll
     for (int r = 0; r < kCullRows; ++r) {
-      if (r >= nr) break;
-      const uint64_t bal = lit_ballot(in, row[r], P, rows[i0 + r], Tj);
+      const uint64_t bal = r < nr ? lit_ballot(in, row[r], P, rows[i0 + r], Tj) : 0ull;
       if ((bal >> lane) & 1ull) {
         const int64_t at =
             base[r] + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));

@@ -682,13 +682,16 @@ __global__ __launch_bounds__(kBlk, 3) void k_bp(Geo g, Lists L, int64_t c0, int6
 // pieces.  L at the midpoint (k_empty); the pieces where it is zero are
 // queued for the quarter points (k_quarter).  On 9.4e8 pieces the two took
 // 51 ms with 4 pieces per lane (one allocation each 13.7 ns), 28.9 with 8,
-// 27.9 with 16; a short list takes fewer, so that it spreads over
-// kEmptyWaves waves (3,840 panels, 3.1e7 pieces: 1.24 -> 1.13 ms).
+// 27.9 with 16; a short list takes fewer, so that it spreads over kEmptyWaves
+// waves (3,840 panels, 3.1e7 pieces: 1.24 -> 1.13 ms).  Twice as many waves cost
+// the test more in allocations than they save in its chain (144 panels: 42 us
+// with 2048, 33 with 1024, 35 with 512); of the queue few waves allocate (15 us with
+// 2048, 21 with 512).
 constexpr int kEmptyPer = 16;
-constexpr int64_t kEmptyWaves = 2048;
+constexpr int64_t kEmptyWaves = 1024, kQuarterWaves = 2048;
 
-__device__ __forceinline__ int empty_per(int64_t n) {
-  const int64_t per = (n + 64 * kEmptyWaves - 1) / (64 * kEmptyWaves);
+__device__ __forceinline__ int empty_per(int64_t n, int64_t waves) {
+  const int64_t per = (n + 64 * waves - 1) / (64 * waves);
   return (int)(per < 1 ? 1 : per < kEmptyPer ? per : kEmptyPer);
 }
 
@@ -806,7 +809,7 @@ __device__ __forceinline__ void route_pieces(const Lists& L, unsigned has, uint6
 __global__ __launch_bounds__(kBlk, 4) void k_empty(Lists L, int64_t npiece_arg) {
   const int B = (int)blockDim.x;
   const int64_t npiece = list_count(L, npiece_arg, L.cap_piece, 3);
-  const int per = empty_per(npiece);
+  const int per = empty_per(npiece, kEmptyWaves);
   __shared__ AllocLds sh;
   unsigned long long ev_mid = 0;
   const int64_t step = (int64_t)gridDim.x * B * per;
@@ -855,7 +858,7 @@ __global__ __launch_bounds__(kBlk, 4) void k_empty(Lists L, int64_t npiece_arg) 
 __global__ __launch_bounds__(kBlk, 3) void k_quarter(Lists L, int64_t nq_arg) {
   const int B = (int)blockDim.x;
   const int64_t nq = list_count(L, nq_arg, L.cap_piece, 3);
-  const int per = empty_per(nq);
+  const int per = empty_per(nq, kQuarterWaves);
   const int64_t step = (int64_t)gridDim.x * B * per;
   for (int64_t base = (int64_t)blockIdx.x * B * per; base < nq; base += step) {
     unsigned ne = 0;
@@ -986,22 +989,27 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes_rec(Lists L, const int32_t* _
 // The n_g nodes of one piece.  Gauss piece [a, a + H]: phi = a + H s(u_g),
 // weight H s'(u_g) w_g with s(u) = 3u^2 - 2u^3.  Trapezoid half h of the
 // period (no breakpoints): phi = (h n_g + g) 2 pi / (2 n_g), weight
-// 2 pi / (2 n_g).
+// 2 pi / (2 n_g).  kNodeLanes lanes per piece, a node each in turn: few pieces
+// come here (a thousandth of the nodes on the icospheres), and one lane's walk
+// over a piece's nodes was all this launch took (144 panels, 1,000 points of
+// 30,720 panels: 24 us, 5.9 us).
+constexpr int kNodeLanes = 16;
 __global__ __launch_bounds__(kBlk, 4) void k_nodes(Lists L, const int32_t* __restrict__ jobs,
                                                    int64_t njob_arg, const double* __restrict__ gl,
                                                    int ng) {
   const int B = (int)blockDim.x;
   const int64_t njob = list_count(L, njob_arg, L.cap_piece, 3);
   const double ht = kTwoPi / (2 * ng);
-  for (int64_t base = (int64_t)blockIdx.x * B; base < njob; base += (int64_t)gridDim.x * B) {
-    const int64_t k = base + threadIdx.x;
-    if (k >= njob) continue;
+  const int lane = threadIdx.x & (kNodeLanes - 1);
+  const int64_t step = (int64_t)gridDim.x * (B / kNodeLanes);
+  // a piece's lanes are of one wavefront and leave the loop together
+  for (int64_t k = (int64_t)blockIdx.x * (B / kNodeLanes) + threadIdx.x / kNodeLanes; k < njob; k += step) {
     const int32_t p = jobs[k];
     const double H = L.ph[p], a = L.pa[p];
     const ComboL cb = load_combo(L, L.pc[p]);
     const bool trap = H < 0.0;
     double acc = 0.0;
-    for (int gi = 0; gi < ng; ++gi) {
+    for (int gi = lane; gi < ng; gi += kNodeLanes) {
       const double u = gl[gi];
       const double s = u * u * (3.0 - 2.0 * u);
       const double ds = 6.0 * u * (1.0 - u);
@@ -1009,7 +1017,9 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes(Lists L, const int32_t* __res
       const double wt = trap ? ht : (H * ds) * gl[kMaxNg + gi];
       acc += wt * L_at(cb, phi);
     }
-    L.pv[p] = acc;
+#pragma unroll
+    for (int d = kNodeLanes / 2; d > 0; d >>= 1) acc += __shfl_xor(acc, d, kNodeLanes);
+    if (lane == 0) L.pv[p] = acc;
   }
 }
 
@@ -1395,7 +1405,7 @@ __global__ __launch_bounds__(kBlk) void k_store(Geo g, Lists L, int64_t c0, int6
 __global__ __launch_bounds__(kBlk) void k_redo(Lists L, int64_t npiece_arg) {
   const int B = (int)blockDim.x;
   const int64_t npiece = list_count(L, npiece_arg, L.cap_piece, 3);
-  const int per = empty_per(npiece);
+  const int per = empty_per(npiece, kEmptyWaves);
   const int64_t step = (int64_t)gridDim.x * B * per;
   for (int64_t base = (int64_t)blockIdx.x * B * per; base < npiece; base += step) {
     unsigned has = 0;

@@ -202,3 +202,21 @@ def test_cull_rows_and_segments(stb, ctx, npts, shift):
     ref, mag = oracle.potential(vtx, mesh.tets, w, pts), oracle.potential(vtx, mesh.tets, np.abs(w), pts)
     # the potential's parity bound, at coordinates known to 64 eps when shifted
     assert np.all(np.abs(u - ref) <= 1e-10 * np.maximum(mag, 1e-3 * mag.max()))
+
+
+# fewer nodes than a piece's lanes, one more, and two rounds of them; points whose
+# cones meet a panel's plane in whole circles (no breakpoints) and in short pieces
+@pytest.mark.parametrize("n_g", [2, 15, 17, 33])
+def test_full_evaluation_nodes(stb, ctx, n_g):
+    import oracle
+    mesh = inputs.icosphere_mesh(0, 4, T=4.0)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    w = np.random.default_rng(4).standard_normal(mesh.nt)
+    cen = mesh.tet_coords().mean(axis=1)
+    pts = np.concatenate([cen + [1e-2, 0, 0, 0], cen + [0.2, 1e-3, 0, 0], inputs.shell_points(40, mesh.T, seed=9)])
+    u = stb.potential_S(ctx, M, w, pts, stb.default_params(n_g=n_g))
+    assert ctx.path_counts()["full"] > 0
+    ref = oracle.potential(mesh.vtx, mesh.tets, w, pts, n_g=n_g)
+    mag = oracle.potential(mesh.vtx, mesh.tets, np.abs(w), pts, n_g=n_g)
+    # the potential's parity bound
+    assert np.all(np.abs(u - ref) <= 1e-10 * np.maximum(mag, 1e-3 * mag.max()))
