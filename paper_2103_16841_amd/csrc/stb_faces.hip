@@ -123,14 +123,79 @@ __global__ void k_face_shift(int64_t n, const int32_t* __restrict__ in, int32_t 
   if (i < n) out[i] = in[i] + add;
 }
 
+// First position in [lo, hi) whose column is >= j (hi: none): bracketed by
+// steps of 1, 2, 4, ... from the guess, then bisected.
+__device__ __forceinline__ int64_t face_pos(const int32_t* __restrict__ fcols, int64_t lo, int64_t hi, int64_t guess,
+                                            int32_t j) {
+  if (lo >= hi) return lo;
+  const int64_t g = std::min(std::max(guess, lo), hi - 1);
+  int64_t a, b;   // the position lies in [a, b] (b = hi: none)
+  if (fcols[g] < j) {
+    a = g + 1;
+    b = hi;
+    for (int64_t step = 1;; step <<= 1) {
+      const int64_t q = g + step;
+      if (q >= hi) break;
+      if (fcols[q] >= j) { b = q; break; }
+      a = q + 1;
+    }
+  } else {
+    a = lo;
+    b = g;
+    for (int64_t step = 1;; step <<= 1) {
+      const int64_t q = g - step;
+      if (q < lo) break;
+      if (fcols[q] < j) { a = q + 1; break; }
+      b = q;
+    }
+  }
+  while (a < b) {
+    const int64_t mid = a + ((b - a) >> 1);
+    if (fcols[mid] < j) a = mid + 1;
+    else b = mid;
+  }
+  return a;
+}
+
+// The same for a wavefront whose lanes hold ascending columns of one row:
+// the first lane's position by a search of 64 probes per round, then 64
+// columns from there, a lane each, that every lane searches by shuffles.  A
+// lane whose column lies past them searches on by itself.
+__device__ __forceinline__ int64_t face_pos_wave(const int32_t* __restrict__ fcols, int64_t lo, int64_t hi, int32_t j) {
+  const int lane = threadIdx.x & 63;
+  const int32_t j0 = __shfl(j, 0, 64);
+  int64_t a = lo, b = hi;   // the first lane's position lies in [a, b]
+  while (b - a > 64) {
+    const int64_t step = (b - a + 63) >> 6, q = a + lane * step;
+    const int n = __popcll(__ballot(q < b && fcols[q < b ? q : b - 1] < j0));
+    if (n == 0) {
+      b = a;
+    } else {
+      const int64_t a1 = a + (n - 1) * step + 1;
+      b = std::min(b, a + n * step);
+      a = a1;
+    }
+  }
+  if (a < b) a += __popcll(__ballot(a + lane < b && fcols[a + lane < b ? a + lane : b - 1] < j0));
+  const int32_t w = a + lane < hi ? fcols[a + lane] : INT32_MAX;
+  int k = 0;   // columns of the window below j
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1)
+    if (__shfl(w, k + d - 1, 64) < j) k += d;
+  if (__shfl(w, k, 64) < j) ++k;   // k is 63 here
+  return k < 64 ? a + k : face_pos(fcols, a + 64 < hi ? a + 64 : hi, hi, a + 64, j);
+}
+
 // Matrix entries of panel rows r0 .. r0 + nrow from the face sums, one lane
 // per candidate: per active face slot of the row's panel (slot order), the
 // candidate's column is looked up among the face's candidate columns
 // (ascending).  A face's columns are those of the panel that owns the face
-// row, a neighbour across the face whose cull found nearly the same columns,
-// so the search starts at the candidate's own rank in its row and gallops
-// from there before it bisects.
-__global__ void k_face_combine(int64_t nnz, int64_t r0, const int32_t* __restrict__ rowof,
+// row, a neighbour across the face whose cull found nearly the same columns.
+// Bound by the searches' chains of loads: 64 candidates of one row search
+// together (1.4e8 candidates of 30,720 panels 3.31 -> 2.86 ms); where a
+// wavefront spans rows each lane searches from the candidate's own rank in its
+// row.
+__global__ __launch_bounds__(256) void k_face_combine(int64_t nnz, int64_t r0, const int32_t* __restrict__ rowof,
                                const int32_t* __restrict__ cols, const int32_t* __restrict__ pf,
                                const double* __restrict__ pw, int64_t f0, int64_t nfu,
                                const int64_t* __restrict__ frowptr,
@@ -140,61 +205,41 @@ __global__ void k_face_combine(int64_t nnz, int64_t r0, const int32_t* __restric
                                uint8_t* __restrict__ keep,
                                unsigned long long* __restrict__ causal) {
   unsigned long long n = 0;
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nnz;
-       c += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t li = rowof[c];
-    const int64_t i = r0 + li;
-    const int32_t j = cols[c];
+  for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < nnz; base += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t c = base + threadIdx.x;
+    const bool in = c < nnz;
+    const int32_t li = rowof[in ? c : nnz - 1];
+    const int32_t j = cols[in ? c : nnz - 1];
+    const bool one_row = __all(in && li == __shfl(li, 0, 64));
+    const int64_t i = r0 + li, first = rowptr[li];
     double acc = 0.0;
     bool any = false;
     for (int s = 0; s < 4; ++s) {
       const int64_t lf = (int64_t)pf[4 * i + s] - f0;
-      if (pf[4 * i + s] < 0 || lf < 0 || lf >= nfu) continue;
-      int64_t lo = frowptr[lf], hi = frowptr[lf + 1];
-      if (prim[lf] == li) {
-        lo += c - rowptr[li];   // the face's candidates are this row's, in order
-      } else if (lo < hi) {
-        // first position in [lo, hi) whose column is >= j: bracket it by
-        // steps of 1, 2, 4, ... from the guess, then bisect the bracket
-        const int64_t g = std::min(std::max(lo + (c - rowptr[li]), lo), hi - 1);
-        int64_t a, b;   // the position lies in [a, b] (b = hi: none)
-        if (fcols[g] < j) {
-          a = g + 1;
-          b = hi;
-          for (int64_t step = 1;; step <<= 1) {
-            const int64_t q = g + step;
-            if (q >= hi) break;
-            if (fcols[q] >= j) { b = q; break; }
-            a = q + 1;
-          }
-        } else {
-          a = lo;
-          b = g;
-          for (int64_t step = 1;; step <<= 1) {
-            const int64_t q = g - step;
-            if (q < lo) break;
-            if (fcols[q] < j) { a = q + 1; break; }
-            b = q;
-          }
-        }
-        while (a < b) {
-          const int64_t mid = a + ((b - a) >> 1);
-          if (fcols[mid] < j) a = mid + 1;
-          else b = mid;
-        }
-        lo = a;
-      }
-      if (lo < frowptr[lf + 1] && fcols[lo] == j) {
-        acc += pw[4 * i + s] * S[lo];
-        any = any || lit[lo] != 0;
+      if (pf[4 * i + s] < 0 || lf < 0 || lf >= nfu) continue;   // all lanes of one row alike
+      const int64_t lo = frowptr[lf], hi = frowptr[lf + 1];
+      const int64_t at = prim[lf] == li ? lo + (c - first)   // the face's candidates are this row's, in order
+                         : one_row      ? face_pos_wave(fcols, lo, hi, j)
+                                        : face_pos(fcols, lo, hi, lo + (c - first), j);
+      if (at < hi && fcols[at] == j) {
+        acc += pw[4 * i + s] * S[at];
+        any = any || lit[at] != 0;
       }
     }
+    if (!in) continue;
     vals[c] = any ? acc : 0.0;
     if (keep) keep[c] = any ? 1 : 0;
     n += any ? 1ull : 0ull;
   }
+  // one addition per workgroup: additions to one address take 13 ns each
+  __shared__ unsigned long long part[4];
   for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off, 64);
-  if ((threadIdx.x & 63) == 0 && n) atomicAdd(causal, n);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = n;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    n = part[0] + part[1] + part[2] + part[3];
+    if (n) atomicAdd(causal, n);
+  }
 }
 
 inline uint64_t hash3(const int32_t* k) {
@@ -498,7 +543,13 @@ stb_status stb_face_assemble(stb_ctx* ctx, const stb_quad_params& p, FaceUnit* u
     const FaceUnit& fu = units[k];
     const U& x = u[(size_t)k];
     if (fu.nnz <= 0) continue;
-    const int64_t blocks = std::min<int64_t>((fu.nnz + 255) / 256, (int64_t)std::max(ctx->ncu, 1) * 32);
+    // at least eight candidates per lane before more than 8 workgroups per CU
+    // (each adds its count to one address: 3,840 panels 414 us with 8192
+    // workgroups of four additions, 130 with 2048 of one); a long list takes 32
+    // (30,720 panels: 3.87 ms with 8, 2.86 with 32)
+    const int64_t cu = std::max(ctx->ncu, 1);
+    const int64_t blocks = std::min((fu.nnz + 255) / 256,
+                                    std::min(std::max(fu.nnz / (256 * 8), 8 * cu), 32 * cu));
     hipLaunchKernelGGL(k_face_combine, dim3((unsigned)blocks), dim3(256), 0, st, fu.nnz, fu.r0, fu.rowof,
                        fu.cols, fu.mesh->d_pf, fu.mesh->d_pw, x.f0, x.f1 - x.f0, x.frowptr, x.fcols,
                        x.fprim, fu.rowptr, S_g + x.oc, lit_g + x.oc, fu.vals, fu.keep, d_causal + k);

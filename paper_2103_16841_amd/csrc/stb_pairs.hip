@@ -1286,6 +1286,9 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes32(Lists L, int64_t njob_arg,
   }
 }
 
+// A combo's integral from its pieces, in order.  Bound by memory latency: the
+// marks and sums of four pieces are requested at once (two or three a combo;
+// with each piece's sum waiting for its mark 3.8e8 combos took 4.7 ms, 3.5 ms).
 __global__ __launch_bounds__(kBlk) void k_combine(Lists L, int64_t ncombo_arg) {
   const int64_t ncombo = list_count(L, ncombo_arg, L.cap_combo, 3);
   int64_t k = (int64_t)blockIdx.x * kBlk + threadIdx.x;
@@ -1293,16 +1296,27 @@ __global__ __launch_bounds__(kBlk) void k_combine(Lists L, int64_t ncombo_arg) {
     const int32_t p0 = L.p0[k], np = L.np[k];
     // empty pieces have no node sum (not written); far combos' non-empty
     // pieces went through the FP32 nodes and carry a rounding bound
-    const bool far = (L.key[k] & kKeyFar) != 0;
+    const bool far = L.mixed && (L.key[k] & kKeyFar) != 0;
     double I = 0.0;
     float e = 0.0f;
-    for (int s = 0; s < np; ++s) {
-      if (!L.pne[p0 + s]) continue;
-      I += L.pv[p0 + s];
-      if (far) e += L.pe[p0 + s];
+    for (int s = 0; s < np; s += 4) {
+      uint8_t ne[4];
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int32_t p = p0 + min(s + u, np - 1);
+        ne[u] = L.pne[p];
+        v[u] = L.pv[p];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool use = s + u < np && ne[u];
+        I = use ? I + v[u] : I;
+        if (use && far) e += L.pe[p0 + s + u];
+      }
     }
     L.I[k] = I / (4.0 * kPi);
-    L.Ie[k] = e * (float)(1.0 / (4.0 * kPi));
+    if (L.mixed) L.Ie[k] = e * (float)(1.0 / (4.0 * kPi));
   }
 }
 

@@ -220,3 +220,16 @@ def test_full_evaluation_nodes(stb, ctx, n_g):
     mag = oracle.potential(mesh.vtx, mesh.tets, np.abs(w), pts, n_g=n_g)
     # the potential's parity bound
     assert np.all(np.abs(u - ref) <= 1e-10 * np.maximum(mag, 1e-3 * mag.max()))
+
+
+# rows shorter than a wavefront (every wavefront spans rows), about one, several;
+# faces whose candidates start before, with and after the row's
+@pytest.mark.parametrize("level,slabs", [(0, 1), (0, 3), (1, 2), (1, 5)])
+def test_entries_from_face_sums(stb, ctx, level, slabs):
+    from _tol import assert_entries, oracle_rows
+    mesh = inputs.icosphere_mesh(level, slabs, T=2.0)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    A = stb.assemble_V(ctx, M)
+    rows = np.unique(np.linspace(0, A.n - 1, 12).astype(int))
+    ref, mag, pert = oracle_rows(mesh.vtx, mesh.tets, rows=rows)
+    assert_entries(_rows_of(A, rows), ref, mag, pert)
