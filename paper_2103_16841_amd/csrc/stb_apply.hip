@@ -21,16 +21,16 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // ones of every eight, and the last cnt % 8 go to the even one.  Each has one
 // MFMA chain; the partial tiles are summed in LDS in a fixed order.
 //
-// A quad's 64 values are stored without their zeros (a third is left of an
-// icosphere's quads): a record has the mask of the lanes that have one, the
+// A quad's 64 values are stored without their zeros (two fifths are left of
+// an icosphere's quads): a record has the mask of the lanes that have one, the
 // place of the first and the four columns, and lane l's value is found by
 // counting the mask's lower bits.  The zero lanes multiply 0, as they would
 // from a full store, so the sums are those of the full quads.
 //
 // Bound by instructions (the products and the work to place the values): 30,720
-// panels (2.3 million quads, 48 million entries) take 157 us, 132 us of them
-// also without the loads of values and of W.  230 us with full quads (626 MB
-// instead of 266) and four wavefronts per block that request eight quads at a
+// panels (2.7 million quads, 72 million entries) take 157 us, 132 us of them
+// also without the loads of values and of W.  230 us with full quads (726 MB
+// instead of 372) and four wavefronts per block that request eight quads at a
 // time and wait; 205 us with the next group's loads ahead and the longest
 // blocks first.
 constexpr int kBellAhead = 8;   // quads per group of loads: 8 records of 8 words, a lane each
