@@ -317,34 +317,47 @@ __global__ __launch_bounds__(kBlkThreads) void k_blk_fill(int64_t nblk, int64_t 
   }
 }
 
+// The matrix gets the copy only when all of it is there: d_bptr says that it is.
 stb_status stb_build_blocked(stb_ctx* ctx, stb_mat* M, hipStream_t st) {
   const int64_t n = M->n, ncols = mat_ncols(M);
   if (ncols > kMaxBlockedN)
     return stb_fail(ctx, STB_E_INVALID_ARG, "16-RHS product supports n <= %lld", (long long)kMaxBlockedN);
   const int64_t nblk = (n + 15) / 16;
   size_t lds = sizeof(uint32_t) * 2 * (size_t)((ncols + 31) / 32);
-  int64_t* d_nq = nullptr;
+  int64_t *d_nq = nullptr, *d_bptr = nullptr, nquad = 0;
+  BellQuad* d_brec = nullptr;
+  float* d_bval = nullptr;
   stb_free_blocked(M);
-  HIPCHK(ctx, dalloc(&d_nq, (size_t)nblk));
-  HIPCHK(ctx, dalloc(&M->d_bptr, (size_t)nblk + 1));
-  hipLaunchKernelGGL(k_blk_count, dim3((unsigned)nblk), dim3(kBlkThreads), lds / 2, st, nblk, n, ncols,
-                     M->d_rowptr, M->d_cols, d_nq);
-  HIPCHK(ctx, hipGetLastError());
-  stb_status s = stb_exclusive_scan(ctx, d_nq, M->d_bptr, nblk, st);
+  auto fill = [&]() -> stb_status {
+    HIPCHK(ctx, dalloc(&d_nq, (size_t)nblk));
+    HIPCHK(ctx, dalloc(&d_bptr, (size_t)nblk + 1));
+    hipLaunchKernelGGL(k_blk_count, dim3((unsigned)nblk), dim3(kBlkThreads), lds / 2, st, nblk, n, ncols,
+                       M->d_rowptr, M->d_cols, d_nq);
+    HIPCHK(ctx, hipGetLastError());
+    stb_status s = stb_exclusive_scan(ctx, d_nq, d_bptr, nblk, st);
+    if (s) return s;
+    HIPCHK(ctx, hipMemcpy(&nquad, d_bptr + nblk, sizeof(int64_t), hipMemcpyDeviceToHost));
+    int64_t nnz = 0;
+    HIPCHK(ctx, hipMemcpy(&nnz, M->d_rowptr + n, sizeof(int64_t), hipMemcpyDeviceToHost));
+    HIPCHK(ctx, dalloc(&d_brec, (size_t)nquad));
+    HIPCHK(ctx, dalloc(&d_bval, (size_t)nnz + 1));
+    const size_t lds_fill = lds + sizeof(float) * 16 * kFillSlots;
+    HIPCHK(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_blk_fill),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_fill));
+    hipLaunchKernelGGL(k_blk_fill, dim3((unsigned)nblk), dim3(kBlkThreads), lds_fill, st, nblk, n, ncols,
+                       M->d_rowptr, M->d_cols, M->d_vals, d_bptr, d_brec, d_bval);
+    HIPCHK(ctx, hipGetLastError());
+    return STB_OK;
+  };
+  const stb_status s = fill();
   dfree(d_nq);
-  if (s) return s;
-  int64_t nquad = 0;
-  HIPCHK(ctx, hipMemcpy(&nquad, M->d_bptr + nblk, sizeof(int64_t), hipMemcpyDeviceToHost));
-  int64_t nnz = 0;
-  HIPCHK(ctx, hipMemcpy(&nnz, M->d_rowptr + n, sizeof(int64_t), hipMemcpyDeviceToHost));
-  HIPCHK(ctx, dalloc(&M->d_brec, (size_t)nquad));
-  HIPCHK(ctx, dalloc(&M->d_bval, (size_t)nnz + 1));
-  const size_t lds_fill = lds + sizeof(float) * 16 * kFillSlots;
-  HIPCHK(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_blk_fill),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_fill));
-  hipLaunchKernelGGL(k_blk_fill, dim3((unsigned)nblk), dim3(kBlkThreads), lds_fill, st, nblk, n, ncols,
-                     M->d_rowptr, M->d_cols, M->d_vals, M->d_bptr, M->d_brec, M->d_bval);
-  HIPCHK(ctx, hipGetLastError());
+  if (s) {
+    dfree(d_bptr); dfree(d_brec); dfree(d_bval);
+    return s;
+  }
+  M->d_bptr = d_bptr;
+  M->d_brec = d_brec;
+  M->d_bval = d_bval;
   M->nblk = nblk;
   M->nquad = nquad;
   return STB_OK;

@@ -147,15 +147,22 @@ stb_status stb_fail(stb_ctx* ctx, stb_status s, const char* fmt, ...);
 
 static inline int64_t mat_ncols(const stb_mat* M) { return M->ncols ? M->ncols : M->n; }
 
+// Every device allocation of the library.  A refused one leaves *p null and no
+// error behind for a later hipGetLastError.  allowance: bytes the calling
+// thread may have allocated from now on before it is refused as on a full device
+// (negative: no limit, the default); for tests of what a refusal leaves.
+hipError_t stb_dev_malloc(void** p, size_t bytes);
+void stb_dev_free(void* p);
+void stb_set_alloc_allowance(int64_t bytes);
+
 template <typename T>
 static inline hipError_t dalloc(T** p, size_t count) {
-  *p = nullptr;
   if (count == 0) count = 1;
-  return hipMalloc((void**)p, count * sizeof(T));
+  return stb_dev_malloc((void**)p, count * sizeof(T));
 }
 
 static inline void dfree(void* p) {
-  if (p) (void)hipFree(p);
+  if (p) stb_dev_free(p);
 }
 
 // Large temporaries that the context keeps between calls (freeing a block

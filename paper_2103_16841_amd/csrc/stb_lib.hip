@@ -18,6 +18,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -833,6 +834,41 @@ static stb_status mirror_host(stb_mat* M) {
   return STB_OK;
 }
 
+namespace {
+thread_local int64_t alloc_allowance = -1;
+thread_local std::map<void*, size_t> alloc_sizes;   // of the allocations under the allowance
+}  // namespace
+
+void stb_set_alloc_allowance(int64_t bytes) {
+  alloc_allowance = bytes;
+  alloc_sizes.clear();
+}
+
+hipError_t stb_dev_malloc(void** p, size_t bytes) {
+  *p = nullptr;
+  if (alloc_allowance >= 0 && bytes > (size_t)alloc_allowance) return hipErrorOutOfMemory;
+  const hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+  } else if (alloc_allowance >= 0) {
+    alloc_allowance -= (int64_t)bytes;
+    alloc_sizes[*p] = bytes;
+  }
+  return e;
+}
+
+void stb_dev_free(void* p) {
+  if (alloc_allowance >= 0) {
+    const auto it = alloc_sizes.find(p);
+    if (it != alloc_sizes.end()) {
+      alloc_allowance += (int64_t)it->second;
+      alloc_sizes.erase(it);
+    }
+  }
+  (void)hipFree(p);
+}
+
 // ---------------------------------------------------------------- C ABI
 hipError_t ctx_alloc(stb_ctx* ctx, void** p, size_t bytes) {
   *p = nullptr;
@@ -852,18 +888,14 @@ hipError_t ctx_alloc(stb_ctx* ctx, void** p, size_t bytes) {
     *p = ctx->lent.back().first;
     return hipSuccess;
   }
-  hipError_t e = hipMalloc(p, bytes);
+  hipError_t e = stb_dev_malloc(p, bytes);
   if (e == hipErrorOutOfMemory && !ctx->kept.empty()) {
-    (void)hipGetLastError();
-    for (auto& b : ctx->kept) (void)hipFree(b.first);
+    for (auto& b : ctx->kept) stb_dev_free(b.first);
     ctx->kept.clear();
     ctx->kept_bytes = 0;
-    e = hipMalloc(p, bytes);
+    e = stb_dev_malloc(p, bytes);
   }
-  if (e != hipSuccess) {
-    *p = nullptr;
-    return e;
-  }
+  if (e != hipSuccess) return e;
   ctx->lent.push_back({*p, bytes});
   return hipSuccess;
 }
@@ -877,17 +909,17 @@ void ctx_keep(stb_ctx* ctx, void* p) {
         ctx->kept.push_back(ctx->lent[k]);
         ctx->kept_bytes += n;
       } else {
-        (void)hipFree(p);
+        stb_dev_free(p);
       }
       ctx->lent.erase(ctx->lent.begin() + (long)k);
       return;
     }
-  (void)hipFree(p);   // not lent by ctx_alloc
+  stb_dev_free(p);   // not lent by ctx_alloc
 }
 
 void ctx_drop_kept(stb_ctx* ctx) {
-  for (auto& b : ctx->kept) (void)hipFree(b.first);
-  for (auto& b : ctx->lent) (void)hipFree(b.first);
+  for (auto& b : ctx->kept) stb_dev_free(b.first);
+  for (auto& b : ctx->lent) stb_dev_free(b.first);
   ctx->kept.clear();
   ctx->lent.clear();
   ctx->kept_bytes = 0;

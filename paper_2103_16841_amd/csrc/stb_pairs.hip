@@ -1524,9 +1524,7 @@ static stb_status ensure_workspace(stb_ctx* ctx, int64_t want_cand, int64_t want
   void* base = nullptr;
   // halve the request until it fits
   for (;;) {
-    if (hipMalloc(&base, ws_bytes(want_cand, want_combo, want_piece)) == hipSuccess) break;
-    (void)hipGetLastError();
-    base = nullptr;
+    if (stb_dev_malloc(&base, ws_bytes(want_cand, want_combo, want_piece)) == hipSuccess) break;
     if (want_combo <= 4096) return stb_fail(ctx, STB_E_NO_MEMORY, "pair workspace does not fit");
     want_cand = std::max<int64_t>(want_cand / 2, 1024);
     want_combo /= 2;
