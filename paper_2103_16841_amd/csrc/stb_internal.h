@@ -248,6 +248,12 @@ stb_status stb_cull_points(stb_ctx* ctx, stb_mesh* m, const stb_quad_params& p, 
                            const double* d_pts, int64_t** d_rowptr, int32_t** d_cols, int32_t** d_rowof,
                            int64_t* nnz);
 
+// out = D^-1 for the K x K matrix D (row-major, overwritten; 1 <= K <= 16384) in
+// device memory by Gauss-Jordan elimination with partial pivoting
+// (stb_solve.hip).  STB_E_INTERNAL for a singular matrix and one with a value
+// that is not finite.  Runs on ctx's stream and synchronises it.
+stb_status stb_gj_invert(stb_ctx* ctx, int64_t K, double* D, double* out);
+
 // Frees the L2 projection's adjacency (stb_proj.hip).
 void stb_free_projection(stb_mesh* m);
 

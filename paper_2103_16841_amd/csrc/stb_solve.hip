@@ -233,7 +233,8 @@ __global__ __launch_bounds__(256) void k_mot_lower(int64_t n, const int64_t* __r
 // the largest is as stable as the largest.  K = 960: eliminating the whole
 // matrix column by column took two launches a column, 6.2 + 3.8 us; this
 // panel with 16 waves and exact (value, row) shuffles 4.5 us a column, as it
-// stands 2.5 us.
+// stands 2.5 us.  A pivot without a finite reciprocal (zero, NaN, infinity)
+// makes the matrix singular: it is reported, not divided by.
 //
 // Maximum over the wavefront of a non-negative key (DPP row shifts, then the
 // two row broadcasts; lane 63 holds it).
@@ -311,8 +312,11 @@ __global__ __launch_bounds__(T) void k_gj_panel(int64_t K, int64_t k0, double* _
 #pragma unroll
       for (int r = 0; r < RPT; ++r)
         if (threadIdx.x + r * T == (unsigned)bi) {
-          const double inv = A[r][c] != 0.0 ? stb::frcp(A[r][c]) : 0.0;
-          if (A[r][c] == 0.0) *singular = 1;
+          double inv = 1.0 / A[r][c];
+          if (!(fabs(A[r][c]) > 0.0 && fabs(A[r][c]) < HUGE_VAL && fabs(inv) < HUGE_VAL)) {
+            *singular = 1;
+            inv = 0.0;
+          }
 #pragma unroll
           for (int j = 0; j < NB; ++j) {
             A[r][j] = (j == c ? 1.0 : A[r][j]) * inv;
@@ -408,20 +412,6 @@ hipError_t gj_steps(int64_t K, double* D, int32_t* piv, uint8_t* used, double* r
   return hipGetLastError();
 }
 
-// Enqueues out = D^-1 (D is overwritten); used: K zeros, rbuf: 16 K doubles.  A
-// panel's rows stay in one workgroup's registers, so the panels narrow as K
-// grows.
-hipError_t gj_invert(int64_t K, double* D, double* out, int32_t* piv, uint8_t* used, double* rbuf, int* sing,
-                     hipStream_t st) {
-  hipError_t e = K <= 1024   ? gj_steps<256, 4, 16>(K, D, piv, used, rbuf, sing, st)
-                 : K <= 2048 ? gj_steps<512, 4, 16>(K, D, piv, used, rbuf, sing, st)
-                 : K <= 4096 ? gj_steps<1024, 4, 8>(K, D, piv, used, rbuf, sing, st)
-                 : K <= 8192 ? gj_steps<1024, 8, 4>(K, D, piv, used, rbuf, sing, st)
-                             : gj_steps<1024, 16, 2>(K, D, piv, used, rbuf, sing, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gj_permute, dim3((unsigned)((K + 255) / 256), (unsigned)K), dim3(256), 0, st, K, D, piv, out);
-  return hipGetLastError();
-}
 constexpr int64_t kMotMaxPanels = 16 * 1024;
 
 // Time step n, part 1: r[k] = b[i] - sum_j A[i][j] x[j] for the rows i =
@@ -481,6 +471,43 @@ __global__ __launch_bounds__(256) void k_mot_apply(int64_t K, const int32_t* __r
 }
 
 }  // namespace
+
+// A panel's rows stay in one workgroup's registers, so the panels narrow as K
+// grows.
+stb_status stb_gj_invert(stb_ctx* ctx, int64_t K, double* D, double* out) {
+  if (K < 1 || K > kMotMaxPanels)
+    return stb_fail(ctx, STB_E_INVALID_ARG, "inverse of order %lld (1 to %lld)", (long long)K, (long long)kMotMaxPanels);
+  hipStream_t st = ctx->stream;
+  int32_t* piv = nullptr;
+  uint8_t* used = nullptr;
+  double* rbuf = nullptr;
+  int* d_sing = nullptr;
+  auto cleanup = [&]() { dfree(piv); dfree(used); dfree(rbuf); dfree(d_sing); };
+  if (dalloc(&piv, (size_t)K) != hipSuccess || dalloc(&used, (size_t)K) != hipSuccess ||
+      dalloc(&rbuf, (size_t)(16 * K)) != hipSuccess || dalloc(&d_sing, 1) != hipSuccess) {
+    cleanup();
+    return stb_fail(ctx, STB_E_NO_MEMORY, "inverse of order %lld", (long long)K);
+  }
+  hipError_t e = hipMemsetAsync(used, 0, K, st);
+  if (e == hipSuccess) e = hipMemsetAsync(d_sing, 0, sizeof(int), st);
+  if (e == hipSuccess)
+    e = K <= 1024   ? gj_steps<256, 4, 16>(K, D, piv, used, rbuf, d_sing, st)
+        : K <= 2048 ? gj_steps<512, 4, 16>(K, D, piv, used, rbuf, d_sing, st)
+        : K <= 4096 ? gj_steps<1024, 4, 8>(K, D, piv, used, rbuf, d_sing, st)
+        : K <= 8192 ? gj_steps<1024, 8, 4>(K, D, piv, used, rbuf, d_sing, st)
+                    : gj_steps<1024, 16, 2>(K, D, piv, used, rbuf, d_sing, st);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(k_gj_permute, dim3((unsigned)((K + 255) / 256), (unsigned)K), dim3(256), 0, st, K, D, piv, out);
+    e = hipGetLastError();
+  }
+  int sing = 0;
+  if (e == hipSuccess) e = hipMemcpyAsync(&sing, d_sing, sizeof(int), hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  else (void)hipStreamSynchronize(st);
+  cleanup();
+  if (e != hipSuccess) return stb_fail(ctx, STB_E_DEVICE, "inverse: %s", hipGetErrorString(e));
+  return sing ? stb_fail(ctx, STB_E_INTERNAL, "the diagonal block is singular") : STB_OK;
+}
 
 extern "C" {
 
@@ -767,21 +794,17 @@ stb_status stb_solve_mot(stb_ctx* ctx, const stb_mesh* mesh, const stb_mat* A, c
   std::vector<int32_t> rflat((size_t)(S * K));
   for (int64_t n = 0; n < S; ++n)
     std::copy(rows[(size_t)n].begin(), rows[(size_t)n].end(), rflat.begin() + n * K);
-  int32_t *d_slab = nullptr, *d_loc = nullptr, *d_rows = nullptr, *d_piv = nullptr;
-  uint8_t* d_used = nullptr;
-  double *D = nullptr, *Dinv = nullptr, *rbuf = nullptr, *x = nullptr, *b = nullptr, *r = nullptr;
+  int32_t *d_slab = nullptr, *d_loc = nullptr, *d_rows = nullptr;
+  double *D = nullptr, *Dinv = nullptr, *x = nullptr, *b = nullptr, *r = nullptr;
   unsigned long long* d_bad = nullptr;
-  int* d_sing = nullptr;
   auto cleanup = [&]() {
-    dfree(d_slab); dfree(d_loc); dfree(d_rows); dfree(d_piv); dfree(d_used); ctx_keep(ctx, D); ctx_keep(ctx, Dinv);
-    dfree(rbuf); dfree(x); dfree(b); dfree(r); dfree(d_bad); dfree(d_sing);
+    dfree(d_slab); dfree(d_loc); dfree(d_rows); ctx_keep(ctx, D); ctx_keep(ctx, Dinv);
+    dfree(x); dfree(b); dfree(r); dfree(d_bad);
   };
   if (dalloc(&d_slab, (size_t)nt) != hipSuccess || dalloc(&d_loc, (size_t)nt) != hipSuccess ||
-      dalloc(&d_rows, (size_t)(S * K)) != hipSuccess || dalloc(&d_piv, (size_t)K) != hipSuccess ||
-      dalloc(&d_used, (size_t)K) != hipSuccess || kalloc(ctx, &D, (size_t)(K * K)) != hipSuccess ||
-      kalloc(ctx, &Dinv, (size_t)(K * K)) != hipSuccess || dalloc(&rbuf, (size_t)(16 * K)) != hipSuccess ||
-      dalloc(&x, (size_t)nt) != hipSuccess || dalloc(&b, (size_t)nt) != hipSuccess ||
-      dalloc(&r, (size_t)K) != hipSuccess || dalloc(&d_bad, 1) != hipSuccess || dalloc(&d_sing, 1) != hipSuccess) {
+      dalloc(&d_rows, (size_t)(S * K)) != hipSuccess || kalloc(ctx, &D, (size_t)(K * K)) != hipSuccess ||
+      kalloc(ctx, &Dinv, (size_t)(K * K)) != hipSuccess || dalloc(&x, (size_t)nt) != hipSuccess ||
+      dalloc(&b, (size_t)nt) != hipSuccess || dalloc(&r, (size_t)K) != hipSuccess || dalloc(&d_bad, 1) != hipSuccess) {
     cleanup();
     return stb_fail(ctx, STB_E_NO_MEMORY, "marching-on-in-time buffers (%lld panels per slab)", (long long)K);
   }
@@ -790,9 +813,7 @@ stb_status stb_solve_mot(stb_ctx* ctx, const stb_mesh* mesh, const stb_mat* A, c
   if (e == hipSuccess) e = hipMemcpyAsync(d_rows, rflat.data(), 4 * S * K, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(b, b_host, 8 * nt, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemsetAsync(d_bad, 0, 8, st);
-  if (e == hipSuccess) e = hipMemsetAsync(d_sing, 0, sizeof(int), st);
   if (e == hipSuccess) e = hipMemsetAsync(D, 0, 8 * K * K, st);
-  if (e == hipSuccess) e = hipMemsetAsync(d_used, 0, K, st);
   if (e == hipSuccess) e = hipMemsetAsync(x, 0, 8 * nt, st);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_mot_lower, dim3((unsigned)((nt * 64 + 255) / 256)), dim3(256), 0, st, nt, A->d_rowptr,
@@ -812,26 +833,21 @@ stb_status stb_solve_mot(stb_ctx* ctx, const stb_mesh* mesh, const stb_mat* A, c
                     bad);
   }
   const auto c0 = std::chrono::steady_clock::now();
-  e = gj_invert(K, D, Dinv, d_piv, d_used, rbuf, d_sing, st);
-  int sing = 0;
-  if (e == hipSuccess) e = hipMemcpyAsync(&sing, d_sing, sizeof(int), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  const stb_status s = stb_gj_invert(ctx, K, D, Dinv);
+  if (s) { cleanup(); return s; }
   const auto c1 = std::chrono::steady_clock::now();
-  if (e == hipSuccess && !sing) {
-    const unsigned gw = (unsigned)((K * 64 + 255) / 256);
-    for (int64_t n = 0; n < S && e == hipSuccess; ++n) {
-      hipLaunchKernelGGL(k_mot_rhs, dim3((unsigned)K), dim3(256), 0, st, K, d_rows + n * K, A->d_rowptr, A->d_cols,
-                         A->d_vals, x, b, r);
-      hipLaunchKernelGGL(k_mot_apply, dim3(gw), dim3(256), 0, st, K, d_rows + n * K, Dinv, r, x);
-      e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipMemcpyAsync(x_host, x, 8 * nt, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+  const unsigned gw = (unsigned)((K * 64 + 255) / 256);
+  for (int64_t n = 0; n < S && e == hipSuccess; ++n) {
+    hipLaunchKernelGGL(k_mot_rhs, dim3((unsigned)K), dim3(256), 0, st, K, d_rows + n * K, A->d_rowptr, A->d_cols,
+                       A->d_vals, x, b, r);
+    hipLaunchKernelGGL(k_mot_apply, dim3(gw), dim3(256), 0, st, K, d_rows + n * K, Dinv, r, x);
+    e = hipGetLastError();
   }
+  if (e == hipSuccess) e = hipMemcpyAsync(x_host, x, 8 * nt, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
   const auto c2 = std::chrono::steady_clock::now();
   cleanup();
   if (e != hipSuccess) return stb_fail(ctx, STB_E_DEVICE, "marching-on-in-time: %s", hipGetErrorString(e));
-  if (sing) return stb_fail(ctx, STB_E_INTERNAL, "the diagonal block is singular");
   if (info4) {
     info4[0] = (double)S;
     info4[1] = (double)K;
