@@ -5,6 +5,8 @@ import ctypes
 import numpy as np
 import pytest
 
+from paper_2103_16841_amd import inputs
+
 pytestmark = pytest.mark.gpu
 
 EPS = 2.0 ** -53
@@ -66,3 +68,70 @@ def test_smallest_pivots(invert):
             for j, v in enumerate(row):
                 ref[j, i] = 1.0 / v if v else 0.0
         assert s == OK and np.array_equal(X.cpu().numpy(), ref)
+
+
+# Rounding: the K eliminations round every entry of the remaining block and of the
+# inverse, and the error passes through D^-1: at most 8 K eps cond(D) of the
+# inverse's size, for growth factors near one (as with partial pivoting here).
+def _bound(K, cond):
+    return 8 * K * EPS * cond
+
+
+# every panel width (16 columns up to K = 2,048 in two workgroup sizes, 8, 4 and 2
+# beyond), both sides of the limits, whole panels of odd K, a last panel of one
+@pytest.mark.parametrize("K", [1, 2, 15, 16, 17, 57, 1024, 1025, 2047, 2049, 4097, 8193])
+def test_inverse_with_pivots_off_the_diagonal(invert, K):
+    """D = P (2 I + E), |E| about 1/2: every column's pivot is its row of P."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(K)
+    E = torch.randn(K, K, generator=g, device="cuda", dtype=torch.float64) * (0.25 / K ** 0.5)
+    perm = torch.randperm(K, generator=torch.Generator().manual_seed(K)).cuda()
+    D = (2 * torch.eye(K, device="cuda", dtype=torch.float64) + E)[perm].contiguous()
+    s, X = invert(D)
+    assert s == OK
+    # D X - I is at most cond(D) times X's relative error; cond(D) <= 2 for |E| <= 2/3
+    R = D @ X - torch.eye(K, device="cuda", dtype=torch.float64)
+    assert float(R.norm()) <= 2 * _bound(K, 2.0) * K ** 0.5
+
+
+@pytest.mark.parametrize("K", [15, 17, 57, 256, 1025])
+def test_inverse_of_dense_random_matrices(invert, K):
+    """No row stands out: the pivots are a matter of a few per cent."""
+    D = np.random.default_rng(K).standard_normal((K, K))
+    s, X = invert(_dev(D))
+    ref = np.linalg.inv(D)
+    assert s == OK
+    # the reference has an error of its own
+    assert np.linalg.norm(X.cpu().numpy() - ref) <= 2 * _bound(K, np.linalg.cond(D)) * np.linalg.norm(ref)
+
+
+# odd K (57), K of the second workgroup size (1,200), by parts of an icosphere's
+# triangles
+@pytest.mark.parametrize("level,ntri", [(1, 19), (3, 400)])
+def test_marching_on_parts_of_a_sphere(level, ntri):
+    from paper_2103_16841_amd import stb
+    pts, tris = inputs.icosphere(level)
+    tris = tris[:ntri]
+    use = np.unique(tris)
+    mesh = inputs.extrude(pts[use], np.searchsorted(use, tris).astype(tris.dtype), 2, 1.0)
+    ctx = stb.Context(0)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    A = stb.assemble_V(ctx, M, stb.default_params(m_q=2, n_g=8))
+    b = A.apply(np.random.default_rng(ntri).standard_normal(A.n))
+    x, info = stb.solve_mot(ctx, M, A, b)
+    K = 3 * ntri
+    assert info["slabs"] == 2 and info["panels_per_slab"] == K
+    lo = mesh.tet_coords()[:, :, 0].min(1)
+    i0, i1 = np.where(lo < 0.25)[0], np.where(lo > 0.25)[0]
+    block = lambda i, j: A.get(np.repeat(i, K).astype(np.int32), np.tile(j, K).astype(np.int32)).reshape(K, K)
+    D, L = block(i0, i0), block(i1, i0)
+    x0 = np.linalg.solve(D, b[i0])
+    x1 = np.linalg.solve(D, b[i1] - L @ x0)
+    # the second slab has the first one's error times D^-1 L beside its own
+    cond, G = np.linalg.cond(D), np.linalg.norm(np.linalg.solve(D, L), 2)
+    e0 = _bound(K, cond) * np.linalg.norm(x0)
+    e1 = _bound(K, cond) * (np.linalg.norm(x1) + G * np.linalg.norm(x0)) + G * e0
+    assert np.linalg.norm(x[i0] - x0) <= e0 and np.linalg.norm(x[i1] - x1) <= e1
+    A.close()
+    M.close()
+    ctx.close()
