@@ -1482,13 +1482,15 @@ static size_t ws_bytes(int64_t cc, int64_t cb, int64_t cp) {
   return b;
 }
 
-// List capacities a run over nnz candidates with maxq apexes each asks for.
+// List capacities a run over nnz candidates with maxq apexes each asks for: eight
+// pieces per combo on average, and in any case all the pieces one candidate can
+// have, since a chunk has at least one.
 static void ws_want(int64_t nnz, int maxq, int64_t* cc, int64_t* cb, int64_t* cp) {
   const int64_t kCandMax = std::min<int64_t>((int64_t)1 << (32 - kKeyShift),
                                              (int64_t)INT32_MAX / std::max(maxq, 1));
   *cc = std::min<int64_t>(nnz, kCandMax);
   *cb = std::min<int64_t>(*cc * maxq, (int64_t)1 << 27);
-  *cp = std::min<int64_t>(*cb * 8, (int64_t)1 << 28);
+  *cp = std::max<int64_t>(std::min<int64_t>(*cb * 8, (int64_t)1 << 28), (int64_t)kMaxBp * maxq);
 }
 
 int64_t stb_pairs_ws_held(const stb_ctx* ctx) {

@@ -1,5 +1,6 @@
 """What a refused allocation or a refused input leaves: an error, no result that
-looks like one, and a library that goes on working.  Allocations are refused by
+looks like one, and a library that goes on working; and calls that were refused
+for their size alone.  Allocations are refused by
 the calling thread's allowance (stb_set_alloc_allowance, an internal function)."""
 import contextlib
 import ctypes
@@ -73,5 +74,36 @@ def test_refused_matrix_core_copy(stb):
     assert refused >= 5
     assert np.array_equal(Y.cpu().numpy(), ref)
     A.close()
+    M.close()
+    ctx.close()
+
+
+def test_one_candidate(stb):
+    """A point and a panel by themselves, also where the point sees more pieces than
+    a candidate has on average (close to a vertex: twelve and more)."""
+    import oracle
+    sphere = inputs.icosphere_mesh(0, 1, T=1.0)
+    use = np.unique(sphere.tets[0])
+    vtx = np.ascontiguousarray(sphere.vtx[use])
+    tet = np.searchsorted(use, sphere.tets[:1]).astype(np.int32)
+    normal = sphere.outward_normals()[:1]
+    ctx = stb.Context(0)
+    M = stb.Mesh(ctx, vtx, tet)
+    M.set_normals(normal)
+    rng = np.random.default_rng(0)
+    pts = vtx[tet[0]][rng.integers(0, 4, 400)]
+    step = 10.0 ** rng.uniform(-3, 0, (400, 1)) * rng.standard_normal((400, 4))
+    step[:, 0] = np.abs(step[:, 0])
+    pts = pts + step
+    one, v = np.ones(1), rng.standard_normal(4)
+    uS = np.concatenate([stb.potential_S(ctx, M, one, p[None]) for p in pts])
+    uD = np.concatenate([stb.potential_D(ctx, M, v, p[None]) for p in pts])
+    # the same points in one call: the same arithmetic per pair
+    assert np.array_equal(uS, stb.potential_S(ctx, M, one, pts))
+    assert np.array_equal(uD, stb.potential_D(ctx, M, v, pts))
+    rS = oracle.potential(vtx, tet, one, pts)
+    rD = oracle.potential_dl(vtx, tet, normal, v, pts)
+    assert np.all(np.abs(uS - rS) <= 1e-10 * np.maximum(np.abs(rS), 1e-3 * np.abs(rS).max()))
+    assert np.all(np.abs(uD - rD) <= 1e-10 * np.maximum(np.abs(rD), 1e-5 * np.abs(rD).max()))
     M.close()
     ctx.close()
