@@ -172,9 +172,11 @@ static inline void dfree(void* p) {
 // block back, or frees it when the kept blocks would exceed ctx->kept_max
 // (8 GiB: a context that assembled a very large mesh does not go on holding its
 // temporaries; 0 for a server's slots, whose memory is budgeted).  The blocks
-// are freed with the context (ctx_drop_kept).
+// are freed with the context (ctx_drop_kept); ctx_drop_free frees the ones that
+// are not lent.
 hipError_t ctx_alloc(stb_ctx* ctx, void** p, size_t bytes);
 void ctx_keep(stb_ctx* ctx, void* p);
+void ctx_drop_free(stb_ctx* ctx);
 void ctx_drop_kept(stb_ctx* ctx);
 
 template <typename T>

@@ -890,9 +890,7 @@ hipError_t ctx_alloc(stb_ctx* ctx, void** p, size_t bytes) {
   }
   hipError_t e = stb_dev_malloc(p, bytes);
   if (e == hipErrorOutOfMemory && !ctx->kept.empty()) {
-    for (auto& b : ctx->kept) stb_dev_free(b.first);
-    ctx->kept.clear();
-    ctx->kept_bytes = 0;
+    ctx_drop_free(ctx);
     e = stb_dev_malloc(p, bytes);
   }
   if (e != hipSuccess) return e;
@@ -917,12 +915,16 @@ void ctx_keep(stb_ctx* ctx, void* p) {
   stb_dev_free(p);   // not lent by ctx_alloc
 }
 
-void ctx_drop_kept(stb_ctx* ctx) {
+void ctx_drop_free(stb_ctx* ctx) {
   for (auto& b : ctx->kept) stb_dev_free(b.first);
-  for (auto& b : ctx->lent) stb_dev_free(b.first);
   ctx->kept.clear();
-  ctx->lent.clear();
   ctx->kept_bytes = 0;
+}
+
+void ctx_drop_kept(stb_ctx* ctx) {
+  ctx_drop_free(ctx);
+  for (auto& b : ctx->lent) stb_dev_free(b.first);
+  ctx->lent.clear();
 }
 
 extern "C" {

@@ -1450,14 +1450,12 @@ unsigned grid_for(int64_t n, int per = 1, int block = kBlk, int64_t max_blocks =
 struct PairWorkspace {
   int64_t cap_cand = 0, cap_combo = 0, cap_piece = 0;
   void* base = nullptr;
-  double* dl = nullptr;   // [2 cap_piece], made by the first double-layer run
   Lists L{};
 };
 
 void stb_free_workspace(stb_ctx* ctx) {
   if (!ctx->ws) return;
   dfree(ctx->ws->base);
-  dfree(ctx->ws->dl);
   delete ctx->ws;
   ctx->ws = nullptr;
 }
@@ -1495,7 +1493,7 @@ static void ws_want(int64_t nnz, int maxq, int64_t* cc, int64_t* cb, int64_t* cp
 
 int64_t stb_pairs_ws_held(const stb_ctx* ctx) {
   const PairWorkspace* w = ctx->ws;
-  return w ? (int64_t)ws_bytes(w->cap_cand, w->cap_combo, w->cap_piece) + (w->dl ? 16 * w->cap_piece : 0) : 0;
+  return w ? (int64_t)ws_bytes(w->cap_cand, w->cap_combo, w->cap_piece) : 0;
 }
 
 int64_t stb_pairs_ws_need(const stb_ctx* ctx, int64_t nnz, int maxq) {
@@ -1524,9 +1522,14 @@ static stb_status ensure_workspace(stb_ctx* ctx, int64_t want_cand, int64_t want
   }
   stb_free_workspace(ctx);
   void* base = nullptr;
-  // halve the request until it fits
+  // without the context's kept blocks if need be, then halve the request until
+  // it fits
   for (;;) {
     if (stb_dev_malloc(&base, ws_bytes(want_cand, want_combo, want_piece)) == hipSuccess) break;
+    if (!ctx->kept.empty()) {
+      ctx_drop_free(ctx);
+      continue;
+    }
     if (want_combo <= 4096) return stb_fail(ctx, STB_E_NO_MEMORY, "pair workspace does not fit");
     want_cand = std::max<int64_t>(want_cand / 2, 1024);
     want_combo /= 2;
@@ -1586,15 +1589,32 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
   int64_t* const want[3] = {&want_cand, &want_combo, &want_piece};
   for (int k = 0; k < 3; ++k)
     if (ctx->list_limit[k]) *want[k] = std::min(*want[k], ctx->list_limit[k]);
+  const bool dl = job.dl_coef != nullptr;
   stb_status s = ensure_workspace(ctx, want_cand, want_combo, want_piece);
   if (s) return s;
+  // the double layer's other two sums per piece: a block lent by the context;
+  // where it does not fit beside the workspace, that makes room
+  struct Lent {
+    stb_ctx* ctx;
+    double* p;
+    ~Lent() { ctx_keep(ctx, p); }
+  } dl_sums{ctx, nullptr};
+  while (dl) {
+    const PairWorkspace* w = ctx->ws;
+    if (kalloc(ctx, &dl_sums.p, (size_t)(2 * w->cap_piece)) == hipSuccess) break;
+    if (w->cap_combo <= 4096) return stb_fail(ctx, STB_E_NO_MEMORY, "double-layer piece sums do not fit");
+    want_cand = std::min(want_cand, std::max<int64_t>(w->cap_cand / 2, 1024));
+    want_combo = std::min(want_combo, w->cap_combo / 2);
+    want_piece = std::min(want_piece, w->cap_piece / 2);
+    stb_free_workspace(ctx);
+    if ((s = ensure_workspace(ctx, want_cand, want_combo, want_piece))) return s;
+  }
   PairWorkspace* w = ctx->ws;
-  const bool dl = job.dl_coef != nullptr;
-  if (dl && !w->dl && dalloc(&w->dl, (size_t)(2 * w->cap_piece)) != hipSuccess)
-    return stb_fail(ctx, STB_E_NO_MEMORY, "double-layer piece sums");
   Lists L = w->L;
-  L.pv2 = w->dl;
-  L.pv3 = w->dl ? w->dl + w->cap_piece : nullptr;
+  if (dl) {
+    L.pv2 = dl_sums.p;
+    L.pv3 = dl_sums.p + w->cap_piece;
+  }
   // the lists' lengths in use: the workspace's, within the caller's limits
   // (the combo fields' stride follows cap_combo, so a shorter length only
   // narrows the fields inside their allocation)

@@ -107,3 +107,42 @@ def test_one_candidate(stb):
     assert np.all(np.abs(uD - rD) <= 1e-10 * np.maximum(np.abs(rD), 1e-5 * np.abs(rD).max()))
     M.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("layer", ["S", "D"])
+def test_potential_in_little_memory(stb, layer):
+    """With ever more memory a potential is refused up to some point and computed
+    from there on: the lists, and the double layer's sums beside them, take what
+    there is, and the values do not depend on it."""
+    mesh = inputs.icosphere_mesh(1, 8)
+    pts = inputs.shell_points(300, mesh.T, seed=3)
+    rng = np.random.default_rng(1)
+    w = rng.standard_normal(mesh.nv if layer == "D" else mesh.nt)
+    call = stb.potential_D if layer == "D" else stb.potential_S
+
+    def run(nbytes):
+        ctx = stb.Context(0)
+        M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+        M.set_normals(mesh.outward_normals())
+        try:
+            with allowance(stb, nbytes):
+                return call(ctx, M, w, pts)
+        except stb.StbError as e:
+            assert e.status == NO_MEMORY
+            return None
+        finally:
+            M.close()
+            ctx.close()
+    ref = run(-1)
+    refused, served = 0, 0
+    budget = 1 << 16
+    while served < 50:
+        u = run(int(budget))
+        if u is None:
+            refused += 1
+            assert served == 0, "%d bytes refused where less was enough" % budget
+        else:
+            served += 1
+            assert np.array_equal(u, ref)
+        budget *= 1.07
+    assert refused > 10
