@@ -200,6 +200,9 @@ stb_status stb_cull(stb_ctx* ctx, int64_t nrows, const stb::ApexBox* d_rows, con
                     bool lend = false);
 stb_status stb_cull_count(stb_ctx* ctx, int64_t nrows, const stb::ApexBox* d_rows, const stb_mesh* m,
                           int64_t* nnz);
+// Device bytes that the cull of nrows rows against nt panels takes beside its
+// results while it runs.
+int64_t stb_cull_bytes(int64_t nrows, int64_t nt);
 // Exclusive prefix of the per-row candidate counts (nrows + 1 entries, host).
 stb_status stb_cull_rowptr(stb_ctx* ctx, int64_t nrows, const stb::ApexBox* d_rows, const stb_mesh* m,
                            int64_t* rowptr_host);

@@ -638,6 +638,12 @@ static stb_status cull_starts(stb_ctx* ctx, int64_t nrows, const ApexBox* d_rows
   return s;
 }
 
+// Device bytes of the cull's temporaries: counts, starts and the scan's scratch.
+int64_t stb_cull_bytes(int64_t nrows, int64_t nt) {
+  const int64_t m = nrows * cull_segments(nrows, nt);
+  return 8 * (m + (m + 1) + stb_scan_tmp_elems<int64_t>(m));
+}
+
 // Exclusive prefix of the candidate counts of these rows (count pass only),
 // copied to the host.
 stb_status stb_cull_rowptr(stb_ctx* ctx, int64_t nrows, const ApexBox* d_rows, const stb_mesh* m,

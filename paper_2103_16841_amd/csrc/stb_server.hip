@@ -69,11 +69,11 @@ namespace {
 // Device bytes a request needs while it runs, beyond the slot's own
 // workspace: its inputs and outputs, and for a potential the cull's
 // candidate arrays (one int64 row pointer per point, column + row + value
-// per candidate, counted exactly by a cull pass).
+// per candidate, counted exactly by a cull pass) and temporaries.
 int64_t matvec_bytes(const stb_mat* M) { return M->n * 16 * (8 + 8 + 4); }
 
 int64_t potential_bytes(int64_t nt, int64_t np, int64_t nnz) {
-  return nt * 8 + np * (32 + 8 + 64 + 8) + nnz * (4 + 4 + 8);
+  return nt * 8 + np * (32 + 8 + 64 + 8) + nnz * (4 + 4 + 8) + stb_cull_bytes(np, nt);
 }
 
 stb_status run_request(stb_ctx* c, const ServedMesh& sm, const stb_request& r, std::string* err) {

@@ -146,3 +146,28 @@ def test_potential_in_little_memory(stb, layer):
             assert np.array_equal(u, ref)
         budget *= 1.07
     assert refused > 10
+
+
+def test_server_counts_the_cull(stb):
+    """A potential's footprint has the cull's counts per point and panel segment in
+    it: 100 points that no panel reaches (no candidates, no lists) on 2,880 panels,
+    45 segments of 64."""
+    mesh = inputs.icosphere_mesh(1, 12)
+    ctx = stb.Context(0)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    pts = inputs.shell_points(100, mesh.T, seed=1)
+    pts[:, 0] = -1.0
+    io = mesh.nt * 8 + 100 * (32 + 8 + 64 + 8)
+    counts = 8 * 100 * 45
+    for budget, fits in ((io + counts, False), (io + 2 * counts, False), (io + 2 * counts + 4096, True)):
+        S = stb.Server(ctx, hbm_budget=budget, nslots=1)
+        ticket = S.submit_potential(S.add_mesh(M), np.ones(mesh.nt), pts)
+        if fits:
+            assert np.array_equal(S.wait(ticket)[0], np.zeros(100))
+        else:
+            with pytest.raises(stb.StbError) as e:
+                S.wait(ticket)
+            assert e.value.status == NO_MEMORY
+        S.close()
+    M.close()
+    ctx.close()
