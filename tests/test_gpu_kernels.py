@@ -233,3 +233,22 @@ def test_entries_from_face_sums(stb, ctx, level, slabs):
     rows = np.unique(np.linspace(0, A.n - 1, 12).astype(int))
     ref, mag, pert = oracle_rows(mesh.vtx, mesh.tets, rows=rows)
     assert_entries(_rows_of(A, rows), ref, mag, pert)
+
+
+# the matrix-core copy entry by entry: one row, a last block of one row and of 15, a
+# last quad of one column, one pass of the fill and several, empty rows
+@pytest.mark.parametrize("level,ntri,slabs", [(0, 1, 1), (0, 5, 1), (0, 17, 1), (0, 19, 3), (1, 67, 3), (1, 80, 8)])
+def test_every_entry_of_the_matrix_core_copy(stb, ctx, level, ntri, slabs):
+    pts, tris = inputs.icosphere(level)
+    use = np.unique(tris[:ntri])
+    mesh = inputs.extrude(pts[use], np.searchsorted(use, tris[:ntri]).astype(tris.dtype), slabs, 4.0)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    A = stb.assemble_V(ctx, M, stb.default_params(m_q=1, n_g=4))
+    D = A.to_dense().astype(np.float32).astype(np.float64)
+    for c in range(0, A.n, 16):
+        E = np.zeros((A.n, 16))
+        k = np.arange(c, min(c + 16, A.n))
+        E[k, k - c] = 1.0
+        assert np.array_equal(A.apply(E)[:, :len(k)], D[:, k]), c
+    A.close()
+    M.close()
