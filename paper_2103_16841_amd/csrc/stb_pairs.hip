@@ -948,7 +948,7 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes_rec(Lists L, const int32_t* _
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           const int e = 2 * g + t;
-          endpoint_pair_node<QE>(E[e], P[e], Q[e], CC[e], SG[e], d2, wlo, whi, cd, sd, vm[t], vp[t]);
+          endpoint_pair_node<QE, false>(E[e], P[e], Q[e], CC[e], SG[e], d2, wlo, whi, cd, sd, vm[t], vp[t]);
         }
         // a gap that closed (end <= start) measures 0: rdiff of equal ends,
         // so no branch (w >= |d| > 0 when d^2 > 0; rdiff ignores 1/w at d = 0)
@@ -1053,9 +1053,11 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes_dl(Lists L, const int32_t* __
       E[2 * g] = endpoint_load(L, c, (rec >> (8 * g + 4)) & 15u, wlo, whi);
       E[2 * g + 1] = endpoint_load(L, c, (rec >> (8 * g)) & 15u, wlo, whi);
     }
-    const double m = a + 0.5 * H;
-    double sm, cm;
-    sincos_small(m, &sm, &cm);
+    // m = fl(a + H / 2) + lo: the nodes are mirrored about the true midpoint
+    const double m = a + 0.5 * H, mh = m - a, lo = (a - (m - mh)) + fma(0.5, H, -mh);
+    double s0, c0;
+    sincos_small(m, &s0, &c0);
+    const double sm = fma(lo, c0, s0), cm = fma(-lo, s0, c0);
     double P[2 * NG], Q[2 * NG], CC[2 * NG], SG[2 * NG];
 #pragma unroll
     for (int e = 0; e < 2 * NG; ++e) {
@@ -1074,7 +1076,7 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes_dl(Lists L, const int32_t* __
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           const int e = 2 * g + t;
-          endpoint_pair_node<QE>(E[e], P[e], Q[e], CC[e], SG[e], d2, wlo, whi, cd, sd, vm[t], vp[t]);
+          endpoint_pair_node<QE, true>(E[e], P[e], Q[e], CC[e], SG[e], d2, wlo, whi, cd, sd, vm[t], vp[t]);
         }
         dl_gap_node(vm[0], fmax(vm[1], vm[0]), d2, am, hm);
         dl_gap_node(vp[0], fmax(vp[1], vp[0]), d2, ap, hp);

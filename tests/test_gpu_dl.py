@@ -345,3 +345,29 @@ def test_arguments(stb, ctx):
     m.set_normals(-nrm)
     u2 = stb.potential_D(ctx, m, np.ones(mesh.nv), pts)
     assert u1[0] == -u2[0] and u1[0] < -0.9
+
+
+# A root takes about a dozen roundings here and a dozen in the oracle, and the
+# nodes' errors partly cancel: most values of single pairs agree within 24 eps.
+# (Reciprocals and square roots one Newton step short, 10 and 19 eps a time and
+# always to the same side, do not.)
+@pytest.mark.parametrize("panel", [0, 1, 2, 30])
+@pytest.mark.parametrize("n_g", [2, 16])
+def test_pairs_to_rounding(stb, ctx, panel, n_g):
+    sphere = inputs.icosphere_mesh(0, 2, T=2.0)
+    use = np.unique(sphere.tets[panel])
+    vtx = np.ascontiguousarray(sphere.vtx[use])
+    tet = np.searchsorted(use, sphere.tets[panel:panel + 1]).astype(np.int32)
+    normal = sphere.outward_normals()[panel:panel + 1]
+    M = stb.Mesh(ctx, vtx, tet)
+    M.set_normals(normal)
+    # points whose cones pass through the panel near its centre
+    pts = inputs.shell_points(4000, 1.0, seed=5)
+    c = vtx.mean(0)
+    pts[:, 0] = c[0] + np.linalg.norm(pts[:, 1:] - c[1:], axis=1) + np.random.default_rng(3).uniform(-0.2, 0.2, 4000)
+    u = stb.potential_D(ctx, M, np.ones(4), pts, params=stb.default_params(n_g=n_g))
+    ref = oracle.potential_dl(vtx, tet, normal, np.ones(4), pts, n_g=n_g)
+    k = np.abs(ref) > 1e-3 * np.abs(ref).max()
+    assert k.sum() > 3000
+    assert np.quantile(np.abs(u[k] - ref[k]) / np.abs(ref[k]), 0.7) <= 24 * 2.0 ** -53
+    M.close()
