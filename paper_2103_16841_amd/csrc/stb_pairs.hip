@@ -1452,12 +1452,15 @@ unsigned grid_for(int64_t n, int per = 1, int block = kBlk, int64_t max_blocks =
 struct PairWorkspace {
   int64_t cap_cand = 0, cap_combo = 0, cap_piece = 0;
   void* base = nullptr;
+  double* dl = nullptr;   // [2 cap_dl]: the double layer's other two sums per piece
+  int64_t cap_dl = 0;
   Lists L{};
 };
 
 void stb_free_workspace(stb_ctx* ctx) {
   if (!ctx->ws) return;
   dfree(ctx->ws->base);
+  dfree(ctx->ws->dl);
   delete ctx->ws;
   ctx->ws = nullptr;
 }
@@ -1495,7 +1498,7 @@ static void ws_want(int64_t nnz, int maxq, int64_t* cc, int64_t* cb, int64_t* cp
 
 int64_t stb_pairs_ws_held(const stb_ctx* ctx) {
   const PairWorkspace* w = ctx->ws;
-  return w ? (int64_t)ws_bytes(w->cap_cand, w->cap_combo, w->cap_piece) : 0;
+  return w ? (int64_t)ws_bytes(w->cap_cand, w->cap_combo, w->cap_piece) + 16 * w->cap_dl : 0;
 }
 
 int64_t stb_pairs_ws_need(const stb_ctx* ctx, int64_t nnz, int maxq) {
@@ -1580,6 +1583,34 @@ static stb_status ensure_workspace(stb_ctx* ctx, int64_t want_cand, int64_t want
   return STB_OK;
 }
 
+// The double layer's two sums per piece beside the workspace, for as many pieces
+// as a run wants of those that the workspace holds.  Where they do not fit, the
+// context's kept blocks go, then the workspace is halved until both fit.
+static stb_status ensure_dl_sums(stb_ctx* ctx, int64_t want_cand, int64_t want_combo, int64_t want_piece) {
+  for (;;) {
+    PairWorkspace* w = ctx->ws;
+    const int64_t n = std::min(want_piece, w->cap_piece);
+    if (w->cap_dl >= n) return STB_OK;
+    dfree(w->dl);
+    w->cap_dl = 0;
+    if (dalloc(&w->dl, (size_t)(2 * n)) == hipSuccess) {
+      w->cap_dl = n;
+      return STB_OK;
+    }
+    if (!ctx->kept.empty()) {
+      ctx_drop_free(ctx);
+      continue;
+    }
+    if (w->cap_combo <= 4096) return stb_fail(ctx, STB_E_NO_MEMORY, "double-layer piece sums do not fit");
+    want_cand = std::min(want_cand, std::max<int64_t>(w->cap_cand / 2, 1024));
+    want_combo = std::min(want_combo, w->cap_combo / 2);
+    want_piece = std::min(want_piece, w->cap_piece / 2);
+    stb_free_workspace(ctx);
+    const stb_status s = ensure_workspace(ctx, want_cand, want_combo, want_piece);
+    if (s) return s;
+  }
+}
+
 stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long work[4]) {
   for (int k = 0; k < 4; ++k) work[k] = 0;
   if (job.nnz <= 0) return STB_OK;
@@ -1594,28 +1625,13 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
   const bool dl = job.dl_coef != nullptr;
   stb_status s = ensure_workspace(ctx, want_cand, want_combo, want_piece);
   if (s) return s;
-  // the double layer's other two sums per piece: a block lent by the context;
-  // where it does not fit beside the workspace, that makes room
-  struct Lent {
-    stb_ctx* ctx;
-    double* p;
-    ~Lent() { ctx_keep(ctx, p); }
-  } dl_sums{ctx, nullptr};
-  while (dl) {
-    const PairWorkspace* w = ctx->ws;
-    if (kalloc(ctx, &dl_sums.p, (size_t)(2 * w->cap_piece)) == hipSuccess) break;
-    if (w->cap_combo <= 4096) return stb_fail(ctx, STB_E_NO_MEMORY, "double-layer piece sums do not fit");
-    want_cand = std::min(want_cand, std::max<int64_t>(w->cap_cand / 2, 1024));
-    want_combo = std::min(want_combo, w->cap_combo / 2);
-    want_piece = std::min(want_piece, w->cap_piece / 2);
-    stb_free_workspace(ctx);
-    if ((s = ensure_workspace(ctx, want_cand, want_combo, want_piece))) return s;
-  }
+  if (dl && (s = ensure_dl_sums(ctx, want_cand, want_combo, want_piece))) return s;
   PairWorkspace* w = ctx->ws;
   Lists L = w->L;
   if (dl) {
-    L.pv2 = dl_sums.p;
-    L.pv3 = dl_sums.p + w->cap_piece;
+    L.cap_piece = std::min(L.cap_piece, w->cap_dl);
+    L.pv2 = w->dl;
+    L.pv3 = w->dl + w->cap_dl;
   }
   // the lists' lengths in use: the workspace's, within the caller's limits
   // (the combo fields' stride follows cap_combo, so a shorter length only
