@@ -308,14 +308,19 @@ __global__ __launch_bounds__(T) void k_gj_panel(int64_t K, int64_t k0, double* _
         bi = k > best ? s_idx[w] : bi;
         best = k > best ? k : best;
       }
+      // a pivot in frcp's range, by its key: 2^-1000 <= |pivot| < 2^1000
+      const bool plain = best - 0x01700001u < 0x7d000000u;
       // the pivot row's owner scales it and passes it on
 #pragma unroll
       for (int r = 0; r < RPT; ++r)
         if (threadIdx.x + r * T == (unsigned)bi) {
-          double inv = 1.0 / A[r][c];
-          if (!(fabs(A[r][c]) > 0.0 && fabs(A[r][c]) < HUGE_VAL && fabs(inv) < HUGE_VAL)) {
-            *singular = 1;
-            inv = 0.0;
+          double inv = stb::frcp(A[r][c]);
+          if (!plain) {
+            inv = 1.0 / A[r][c];
+            if (!(fabs(A[r][c]) < HUGE_VAL && fabs(inv) < HUGE_VAL)) {
+              *singular = 1;
+              inv = 0.0;
+            }
           }
 #pragma unroll
           for (int j = 0; j < NB; ++j) {
@@ -478,18 +483,14 @@ stb_status stb_gj_invert(stb_ctx* ctx, int64_t K, double* D, double* out) {
   if (K < 1 || K > kMotMaxPanels)
     return stb_fail(ctx, STB_E_INVALID_ARG, "inverse of order %lld (1 to %lld)", (long long)K, (long long)kMotMaxPanels);
   hipStream_t st = ctx->stream;
-  int32_t* piv = nullptr;
-  uint8_t* used = nullptr;
+  // one block lent by the context: the pivot rows' columns, pivots, flag, used rows
   double* rbuf = nullptr;
-  int* d_sing = nullptr;
-  auto cleanup = [&]() { dfree(piv); dfree(used); dfree(rbuf); dfree(d_sing); };
-  if (dalloc(&piv, (size_t)K) != hipSuccess || dalloc(&used, (size_t)K) != hipSuccess ||
-      dalloc(&rbuf, (size_t)(16 * K)) != hipSuccess || dalloc(&d_sing, 1) != hipSuccess) {
-    cleanup();
+  if (kalloc(ctx, &rbuf, (size_t)(16 * K + K + 1)) != hipSuccess)
     return stb_fail(ctx, STB_E_NO_MEMORY, "inverse of order %lld", (long long)K);
-  }
-  hipError_t e = hipMemsetAsync(used, 0, K, st);
-  if (e == hipSuccess) e = hipMemsetAsync(d_sing, 0, sizeof(int), st);
+  int32_t* piv = reinterpret_cast<int32_t*>(rbuf + 16 * K);
+  int* d_sing = piv + K;
+  uint8_t* used = reinterpret_cast<uint8_t*>(d_sing + 1);
+  hipError_t e = hipMemsetAsync(d_sing, 0, sizeof(int) + K, st);
   if (e == hipSuccess)
     e = K <= 1024   ? gj_steps<256, 4, 16>(K, D, piv, used, rbuf, d_sing, st)
         : K <= 2048 ? gj_steps<512, 4, 16>(K, D, piv, used, rbuf, d_sing, st)
@@ -504,7 +505,7 @@ stb_status stb_gj_invert(stb_ctx* ctx, int64_t K, double* D, double* out) {
   if (e == hipSuccess) e = hipMemcpyAsync(&sing, d_sing, sizeof(int), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   else (void)hipStreamSynchronize(st);
-  cleanup();
+  ctx_keep(ctx, rbuf);
   if (e != hipSuccess) return stb_fail(ctx, STB_E_DEVICE, "inverse: %s", hipGetErrorString(e));
   return sing ? stb_fail(ctx, STB_E_INTERNAL, "the diagonal block is singular") : STB_OK;
 }
