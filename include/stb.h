@@ -154,7 +154,10 @@ stb_status stb_mat_export(const stb_mat* mat, int64_t* rowptr, int32_t* cols, do
 /* y = A w for nrhs right-hand sides; w: n x nrhs row-major, y: n x nrhs.
  * nrhs == 1: FP64 sparse product.  nrhs == 16: FP32 matrix-core product
  * (A and W rounded to FP32, FP32 accumulation).  Other nrhs: FP64, one
- * column at a time. */
+ * column at a time.  An FP64 row sum runs in an order fixed by the store as a
+ * whole (from 2^24 entries on by parts of its columns), so the same row in a
+ * store of another size may differ in its last bits; repeated products agree
+ * bit for bit. */
 stb_status stb_apply(stb_ctx* ctx, const stb_mat* mat, int32_t nrhs, const double* w, double* y);
 stb_status stb_apply_dev(stb_ctx* ctx, const stb_mat* mat, int32_t nrhs, const double* w_dev,
                          double* y_dev, void* stream);

@@ -252,3 +252,30 @@ def test_every_entry_of_the_matrix_core_copy(stb, ctx, level, ntri, slabs):
         assert np.array_equal(A.apply(E)[:, :len(k)], D[:, k]), c
     A.close()
     M.close()
+
+
+# the stores of test_product_with_column_parts are on the sides of the limit that it
+# means: 2^24 entries; parts of at most 19,200 columns.  A large store's sums run by
+# parts, so the order of its rows' sums is the store's own: each part's entries as
+# they are summed in a row of 64 lanes, then the parts
+@pytest.mark.parametrize("level,slabs,parts", [(1, 48, 0), (2, 16, 1), (2, 32, 2), (2, 42, 3)])
+def test_column_part_stores_pass_the_limit(stb, ctx, level, slabs, parts):
+    mesh = inputs.icosphere_mesh(level, slabs)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    A = stb.assemble_V(ctx, M, stb.default_params(m_q=1, n_g=2))
+    assert (A.n_stored >= 2 ** 24) == (parts > 0)
+    w = np.random.default_rng(1).standard_normal(A.n)
+    y = A.apply(w)
+    if parts:
+        width = -(-A.n // parts)
+        assert -(-A.n // 19200) == parts
+        row = A.n - 1
+        v = A.get(np.full(A.n, row, dtype=np.int32), np.arange(A.n, dtype=np.int32))
+        c = np.nonzero(v)[0]
+        y_parts = A.apply(np.where(np.arange(A.n) < width, w, 0.0))[row]
+        for p in range(1, parts):
+            y_parts += A.apply(np.where(np.arange(A.n) // width == p, w, 0.0))[row]
+        # a part alone gives that part's sum and exact zeros elsewhere
+        assert y[row] == y_parts and len(c) > 64
+    A.close()
+    M.close()
