@@ -191,10 +191,6 @@ STB_HD __forceinline__ bool w_range(const TrialRec& T, const Apex& A, double& wl
   return true;
 }
 
-STB_HD __forceinline__ double r_of_w(double w, double d2) {
-  return d2 > 0.0 ? 0.5 * (w + d2 / w) : 0.5 * w;
-}
-
 // 1/x to within an ulp for normal, finite, non-zero x: the hardware
 // reciprocal estimate refined by two Newton steps (e = 1 - x r, r += r e).
 // Much shorter than an IEEE division; every use below has |x| well inside
@@ -1057,15 +1053,6 @@ STB_HD __forceinline__ double L_combo(const ComboL& cb, double cs, double sn) {
 // pieces have one gap, the rest two.
 constexpr int kRecipeGaps = 2;
 
-STB_HD __forceinline__ void order2i(double& s0, double& e0, int& i0, int& j0, double& s1, double& e1,
-                                    int& i1, int& j1) {
-  bool sw = s1 < s0;
-  double ts = s0, te = e0;
-  int ti = i0, tj = j0;
-  s0 = sw ? s1 : s0; e0 = sw ? e1 : e0; i0 = sw ? i1 : i0; j0 = sw ? j1 : j0;
-  s1 = sw ? ts : s1; e1 = sw ? te : e1; i1 = sw ? ti : i1; j1 = sw ? tj : j1;
-}
-
 // L(phi) as L_eval, also returning the recipe of its gap structure.  The
 // admissible set is found from values alone (as L_eval does); the endpoint
 // formula of each end of the (at most two) kept gaps is then identified by
@@ -1233,33 +1220,6 @@ struct Endpoint {
   bool cst, isb;    // constant end; root -d^2 f / q (else q / e)
 };
 
-STB_HD __forceinline__ double endpoint_value(const Endpoint& E, double d2, double wlo, double whi,
-                                             double cs, double sn) {
-  double B = fma(E.fb, cs, E.fc * sn);
-  double e = B - E.a, f = B + E.a;
-  double D = fma(E.C, E.C, d2 * (e * f));
-  double q = E.C + copysign(sqrt_disc(D), E.C);
-  double num = E.isb ? -d2 * f : q;
-  double den = E.isb ? q : e;
-  double v = num * frcp(den);
-  v = E.cst ? E.cval : v;
-  // the admissible set lies in [wlo, whi]; a formula evaluated just past
-  // the structure it was chosen for (rounding at a piece's end) stays there
-  return fmin(fmax(v, wlo), whi);
-}
-
-// endpoint_value for a q / e root (not a constant, not the -d^2 f / q root):
-// the same operations without the selects.
-STB_HD __forceinline__ double endpoint_value_qe(const Endpoint& E, double d2, double wlo, double whi,
-                                                double cs, double sn) {
-  double B = fma(E.fb, cs, E.fc * sn);
-  double e = B - E.a, f = B + E.a;
-  double D = fma(E.C, E.C, d2 * (e * f));
-  double q = E.C + copysign(sqrt_disc(D), E.C);
-  double v = q * frcp(e);
-  return fmin(fmax(v, wlo), whi);
-}
-
 // The Gauss-node stage's arithmetic: the same formulas with one refinement
 // step fewer.  Measured on the device over 2^22 seeded values spanning 2^-100
 // to 2^100: the reciprocal estimate is within 4.6e-8, so one Newton step
@@ -1362,28 +1322,6 @@ STB_HD __forceinline__ void dl_gap_node(double w0, double w1, double d2, double&
   sh += fma(-(d2 * sw), t, ln);
 }
 
-STB_HD __forceinline__ double endpoint_value_node(const Endpoint& E, double d2, double wlo, double whi,
-                                                  double cs, double sn) {
-  const double B = fma(E.fb, cs, E.fc * sn);
-  const double e = B - E.a, f = B + E.a;
-  const double D = fma(E.C, E.C, d2 * (e * f));
-  const double q = E.C + copysign(sqrt_disc_node(D), E.C);
-  const double num = E.isb ? -d2 * f : q;
-  const double den = E.isb ? q : e;
-  double v = num * frcp_node(den);
-  v = E.cst ? E.cval : v;
-  return fmin(fmax(v, wlo), whi);
-}
-
-STB_HD __forceinline__ double endpoint_value_qe_node(const Endpoint& E, double d2, double wlo,
-                                                     double whi, double cs, double sn) {
-  const double B = fma(E.fb, cs, E.fc * sn);
-  const double e = B - E.a, f = B + E.a;
-  const double D = fma(E.C, E.C, d2 * (e * f));
-  const double q = E.C + copysign(sqrt_disc_node(D), E.C);
-  return fmin(fmax(q * frcp_node(e), wlo), whi);
-}
-
 // One endpoint formula at the mirror nodes m -+ delta of a piece, from the
 // per-piece P = B(m), Q = b sin m - c cos m of its face, CC = C^2 and
 // SG = copysign(1, C): B(m -+ delta) = P cos delta +- Q sin delta, and
@@ -1410,23 +1348,12 @@ STB_HD __forceinline__ void endpoint_pair_node(const Endpoint& E, double P, doub
       w = num * (kUlp ? frcp_ulp(den) : frcp_node(den));
       w = E.cst ? E.cval : w;
     }
+    // the admissible set lies in [wlo, whi]; a formula evaluated just past the
+    // structure it was chosen for (rounding at a piece's end) stays there
     v[h] = fmin(fmax(w, wlo), whi);
   }
   vm = v[0];
   vp = v[1];
-}
-
-// L by a recipe: the r-measure of its gaps, each between two endpoint
-// formulas (E[2g], E[2g + 1]).
-STB_HD __forceinline__ double L_by_recipe(const Endpoint* E, int ng, double d2, double wlo,
-                                          double whi, double cs, double sn) {
-  double len = 0.0;
-  for (int g = 0; g < ng; ++g) {
-    double v0 = endpoint_value(E[2 * g], d2, wlo, whi, cs, sn);
-    double v1 = endpoint_value(E[2 * g + 1], d2, wlo, whi, cs, sn);
-    len += v1 > v0 ? rdiff(v0, v1, d2) : 0.0;
-  }
-  return len;
 }
 
 // ------------------------------------------------------------ mixed precision
