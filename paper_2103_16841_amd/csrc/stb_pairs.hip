@@ -1023,112 +1023,139 @@ __global__ __launch_bounds__(kBlk, 4) void k_nodes(Lists L, const int32_t* __res
   }
 }
 
-// The double layer's nodes of a piece by its recipe: as k_nodes_rec, with the
+// The double layer's nodes of a piece by its recipe: as in k_nodes_rec, with the
 // three sums of wt sa, wt sh cos phi and wt sh sin phi.  For the mirror nodes m
 // -+ delta the last two follow from cos m, sin m and the sums of sh cos delta and
-// of its difference times sin delta.  Bound by instruction issue: 4.2e7 pieces of
-// 1.4e5 surface points on 15,360 panels took 87 ms with one kernel for the
-// test and four endpoint formulas indexed in private memory, a library
-// logarithm and two quotients per gap and node; the node kernels take 24 ms and
-// the tests 11 ms here.
+// of its difference times sin delta.
 template <int NG, bool QE>
-__global__ __launch_bounds__(kBlk, 4) void k_nodes_dl(Lists L, const int32_t* __restrict__ jobs_arg,
-                                                      int64_t njob_arg, const double* __restrict__ gl, int ng) {
-  const int B = (int)blockDim.x;
-  const int64_t njob = list_count(L, njob_arg, L.cap_piece, 3);
-  const int32_t* __restrict__ jobs = jobs_arg ? jobs_arg : L.job + (L.cap_piece - njob);
-  for (int64_t base = (int64_t)blockIdx.x * B; base < njob; base += (int64_t)gridDim.x * B) {
-    const int64_t k = base + threadIdx.x;
-    if (k >= njob) continue;
-    const int32_t p = jobs[k];
-    const double H = L.ph[p], a = L.pa[p];
-    const uint32_t rec = L.prec[p];
-    const int64_t c = L.pc[p];
-    const int64_t cap = L.cap_combo;
-    const double d2 = L.cb[kCbD2 * cap + c], wlo = L.cb[kCbWlo * cap + c],
-                 whi = L.cb[kCbWhi * cap + c];
-    Endpoint E[2 * NG];
+__device__ __forceinline__ void dl_piece(const Lists& L, int32_t p, const double* __restrict__ gl, int ng) {
+  const double H = L.ph[p], a = L.pa[p];
+  const uint32_t rec = L.prec[p];
+  const int64_t c = L.pc[p];
+  const int64_t cap = L.cap_combo;
+  const double d2 = L.cb[kCbD2 * cap + c], wlo = L.cb[kCbWlo * cap + c],
+               whi = L.cb[kCbWhi * cap + c];
+  Endpoint E[2 * NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    E[2 * g] = endpoint_load(L, c, (rec >> (8 * g + 4)) & 15u, wlo, whi);
+    E[2 * g + 1] = endpoint_load(L, c, (rec >> (8 * g)) & 15u, wlo, whi);
+  }
+  // m = fl(a + H / 2) + lo: the nodes are mirrored about the true midpoint
+  const double m = a + 0.5 * H, mh = m - a, lo = (a - (m - mh)) + fma(0.5, H, -mh);
+  double s0, c0;
+  sincos_small(m, &s0, &c0);
+  const double sm = fma(lo, c0, s0), cm = fma(-lo, s0, c0);
+  double P[2 * NG], Q[2 * NG], CC[2 * NG], SG[2 * NG];
+#pragma unroll
+  for (int e = 0; e < 2 * NG; ++e) {
+    P[e] = fma(E[e].fb, cm, E[e].fc * sm);
+    Q[e] = fma(E[e].fb, sm, -(E[e].fc * cm));
+    CC[e] = E[e].C * E[e].C;
+    SG[e] = copysign(1.0, E[e].C);
+  }
+  double ia = 0.0, s1 = 0.0, s2 = 0.0;
+  // one mirror pair with weight factor wf (the midpoint itself: half of it)
+  auto pair = [&](double cd, double sd, double wf) {
+    double am = 0.0, hm = 0.0, ap = 0.0, hp = 0.0;
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
-      E[2 * g] = endpoint_load(L, c, (rec >> (8 * g + 4)) & 15u, wlo, whi);
-      E[2 * g + 1] = endpoint_load(L, c, (rec >> (8 * g)) & 15u, wlo, whi);
-    }
-    // m = fl(a + H / 2) + lo: the nodes are mirrored about the true midpoint
-    const double m = a + 0.5 * H, mh = m - a, lo = (a - (m - mh)) + fma(0.5, H, -mh);
-    double s0, c0;
-    sincos_small(m, &s0, &c0);
-    const double sm = fma(lo, c0, s0), cm = fma(-lo, s0, c0);
-    double P[2 * NG], Q[2 * NG], CC[2 * NG], SG[2 * NG];
+      double vm[2], vp[2];
 #pragma unroll
-    for (int e = 0; e < 2 * NG; ++e) {
-      P[e] = fma(E[e].fb, cm, E[e].fc * sm);
-      Q[e] = fma(E[e].fb, sm, -(E[e].fc * cm));
-      CC[e] = E[e].C * E[e].C;
-      SG[e] = copysign(1.0, E[e].C);
-    }
-    double ia = 0.0, s1 = 0.0, s2 = 0.0;
-    // one mirror pair with weight factor wf (the midpoint itself: half of it)
-    auto pair = [&](double cd, double sd, double wf) {
-      double am = 0.0, hm = 0.0, ap = 0.0, hp = 0.0;
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        double vm[2], vp[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const int e = 2 * g + t;
-          endpoint_pair_node<QE, true>(E[e], P[e], Q[e], CC[e], SG[e], d2, wlo, whi, cd, sd, vm[t], vp[t]);
-        }
-        dl_gap_node(vm[0], fmax(vm[1], vm[0]), d2, am, hm);
-        dl_gap_node(vp[0], fmax(vp[1], vp[0]), d2, ap, hp);
+      for (int t = 0; t < 2; ++t) {
+        const int e = 2 * g + t;
+        endpoint_pair_node<QE, true>(E[e], P[e], Q[e], CC[e], SG[e], d2, wlo, whi, cd, sd, vm[t], vp[t]);
       }
-      ia = fma(wf, am + ap, ia);
-      s1 = fma(wf * cd, hm + hp, s1);
-      s2 = fma(wf * sd, hm - hp, s2);
-    };
-    const bool short_piece = H <= kPi;
-    for (int gi = 0; gi < (ng >> 1); ++gi) {
-      double sd, cd;
-      if (short_piece) sincos_half_pi(H * gl[2 * kMaxNg + gi], &sd, &cd);
-      else sincos_small(H * gl[2 * kMaxNg + gi], &sd, &cd);
-      pair(cd, sd, gl[3 * kMaxNg + gi]);
+      dl_gap_node(vm[0], fmax(vm[1], vm[0]), d2, am, hm);
+      dl_gap_node(vp[0], fmax(vp[1], vp[0]), d2, ap, hp);
     }
-    if (ng & 1) pair(1.0, 0.0, 0.5 * (1.5 * gl[kMaxNg + (ng >> 1)]));
-    // phi = m - delta: cos phi = cm cd + sm sd, sin phi = sm cd - cm sd
-    L.pv[p] = H * ia;
-    L.pv2[p] = H * fma(cm, s1, sm * s2);
-    L.pv3[p] = H * fma(sm, s1, -(cm * s2));
+    ia = fma(wf, am + ap, ia);
+    s1 = fma(wf * cd, hm + hp, s1);
+    s2 = fma(wf * sd, hm - hp, s2);
+  };
+  const bool short_piece = H <= kPi;
+  for (int gi = 0; gi < (ng >> 1); ++gi) {
+    double sd, cd;
+    if (short_piece) sincos_half_pi(H * gl[2 * kMaxNg + gi], &sd, &cd);
+    else sincos_small(H * gl[2 * kMaxNg + gi], &sd, &cd);
+    pair(cd, sd, gl[3 * kMaxNg + gi]);
   }
+  if (ng & 1) pair(1.0, 0.0, 0.5 * (1.5 * gl[kMaxNg + (ng >> 1)]));
+  // phi = m - delta: cos phi = cm cd + sm sd, sin phi = sm cd - cm sd
+  L.pv[p] = H * ia;
+  L.pv2[p] = H * fma(cm, s1, sm * s2);
+  L.pv3[p] = H * fma(sm, s1, -(cm * s2));
 }
 
-// The double layer's nodes of the other pieces: full evaluation.
-__global__ __launch_bounds__(kBlk, 4) void k_nodes_dl_full(Lists L, const int32_t* __restrict__ jobs,
-                                                           int64_t njob_arg, const double* __restrict__ gl, int ng) {
-  const int B = (int)blockDim.x;
-  const int64_t njob = list_count(L, njob_arg, L.cap_piece, 3);
+// The same by the full evaluation, kNodeLanes lanes per piece, a node each in turn.
+__device__ __forceinline__ void dl_piece_full(const Lists& L, int32_t p, const double* __restrict__ gl, int ng) {
   const double ht = kTwoPi / (2 * ng);
-  for (int64_t k = (int64_t)blockIdx.x * B + threadIdx.x; k < njob; k += (int64_t)gridDim.x * B) {
-    const int32_t p = jobs[k];
-    const double H = L.ph[p], a = L.pa[p];
-    const ComboL cb = load_combo(L, L.pc[p]);
-    FaceSet F;
+  const int lane = threadIdx.x & (kNodeLanes - 1);
+  const double H = L.ph[p], a = L.pa[p];
+  const ComboL cb = load_combo(L, L.pc[p]);
+  FaceSet F;
 #pragma unroll
-    for (int f = 0; f < 4; ++f) { F.fa[f] = cb.fa[f]; F.fb[f] = cb.fb[f]; F.fc[f] = cb.fc[f]; }
-    const bool trap = H < 0.0;
-    double ia = 0.0, ic = 0.0, is = 0.0;
-    for (int gi = 0; gi < ng; ++gi) {
-      const double u = gl[gi];
-      const double phi = trap ? (a * ng + gi) * ht : a + H * (u * u * (3.0 - 2.0 * u));
-      const double wt = trap ? ht : (H * (6.0 * u * (1.0 - u))) * gl[kMaxNg + gi];
-      double sn, cs, sa, sh;
-      sincos_small(phi, &sn, &cs);
-      dl_eval(F, cb.C, cb.d2, cb.wlo, cb.whi, cs, sn, sa, sh);
-      ia += wt * sa;
-      ic += (wt * sh) * cs;
-      is += (wt * sh) * sn;
-    }
+  for (int f = 0; f < 4; ++f) { F.fa[f] = cb.fa[f]; F.fb[f] = cb.fb[f]; F.fc[f] = cb.fc[f]; }
+  const bool trap = H < 0.0;
+  double ia = 0.0, ic = 0.0, is = 0.0;
+  for (int gi = lane; gi < ng; gi += kNodeLanes) {
+    const double u = gl[gi];
+    const double phi = trap ? (a * ng + gi) * ht : a + H * (u * u * (3.0 - 2.0 * u));
+    const double wt = trap ? ht : (H * (6.0 * u * (1.0 - u))) * gl[kMaxNg + gi];
+    double sn, cs, sa, sh;
+    sincos_small(phi, &sn, &cs);
+    dl_eval(F, cb.C, cb.d2, cb.wlo, cb.whi, cs, sn, sa, sh);
+    ia += wt * sa;
+    ic += (wt * sh) * cs;
+    is += (wt * sh) * sn;
+  }
+#pragma unroll
+  for (int d = kNodeLanes / 2; d > 0; d >>= 1) {
+    ia += __shfl_xor(ia, d, kNodeLanes);
+    ic += __shfl_xor(ic, d, kNodeLanes);
+    is += __shfl_xor(is, d, kNodeLanes);
+  }
+  if (lane == 0) {
     L.pv[p] = ia;
     L.pv2[p] = ic;
     L.pv3[p] = is;
+  }
+}
+
+// The double layer's nodes of the one-gap q / e pieces (nearly all of them).  Bound
+// by instruction issue: 4.2e7 pieces of 1.4e5 surface points on 15,360 panels
+// took 87 ms with one kernel for the test and four endpoint formulas indexed in
+// private memory, a library logarithm and two quotients per gap and node; the
+// nodes take 25 ms and the tests 11 ms here.
+__global__ __launch_bounds__(kBlk, 4) void k_nodes_dl(Lists L, const double* __restrict__ gl, int ng) {
+  const int B = (int)blockDim.x;
+  const int64_t n = list_count(L, -(int64_t)CNT_JOB - 1, L.cap_piece, 3);
+  for (int64_t k = (int64_t)blockIdx.x * B + threadIdx.x; k < n; k += (int64_t)gridDim.x * B)
+    dl_piece<1, true>(L, L.job[k], gl, ng);
+}
+
+// Those of the other three lists, in one launch: a workgroup's share is one list's,
+// a piece per lane (kNodeLanes lanes where the recipe does not serve), and the
+// lists' shares follow each other.  6 points on 3,120 panels: 14 us, 12 + 15 + 32 us
+// with a launch per list and one lane per piece in the last.  In one launch with
+// the kernel above all of it spills (30,000 points: 13.7 instead of 13.0 ms).
+__global__ __launch_bounds__(kBlk, 3) void k_nodes_dl_rest(Lists L, const double* __restrict__ gl, int ng) {
+  const int B = (int)blockDim.x, F = B / kNodeLanes;
+  auto count = [&](int k) { return list_count(L, -(int64_t)k - 1, L.cap_piece, 3); };
+  const int64_t nx = count(CNT_JOB1X), n2 = count(CNT_JOB2), nf = count(CNT_JOBF);
+  const int64_t sx = (nx + B - 1) / B, s2 = sx + (n2 + B - 1) / B, sf = s2 + (nf + F - 1) / F;
+  for (int64_t s = blockIdx.x; s < sf; s += gridDim.x) {
+    if (s < sx) {
+      const int64_t k = s * B + threadIdx.x;
+      if (k < nx) dl_piece<1, false>(L, L.job[L.cap_piece - nx + k], gl, ng);
+    } else if (s < s2) {
+      const int64_t k = (s - sx) * B + threadIdx.x;
+      if (k < n2) dl_piece<2, false>(L, L.job2[k], gl, ng);
+    } else {
+      // a piece's lanes are of one wavefront and go together
+      const int64_t k = (s - s2) * F + threadIdx.x / kNodeLanes;
+      if (k < nf) dl_piece_full(L, L.jobf[k], gl, ng);
+    }
   }
 }
 
@@ -1664,14 +1691,18 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
     if (!e) HIPCHK(ctx, hipEventCreate(&e));
   bool used[8] = {false, false, false, false, false, false, false, false};
   // brackets a launch of kernel kind k with events (per chunk, read after
-  // the chunk's synchronisation)
-  auto t0 = [&](int k) { used[k] = true; return hipEventRecord(ctx->kev[2 * k], st); };
+  // the chunk's synchronisation); the double layer's times are not reported
+  auto t0 = [&](int k) {
+    if (dl) return hipSuccess;
+    used[k] = true;
+    return hipEventRecord(ctx->kev[2 * k], st);
+  };
   // grid of stage k: enough blocks for n items (per items per thread), at
   // most the stage's blocks per CU times the CU count
   auto gfor = [&](int k, unsigned long long n, int per = 1) {
     return grid_for((int64_t)n, per, ctx->tune_block[k], (int64_t)ctx->tune_per_cu[k] * ctx->ncu);
   };
-  auto t1 = [&](int k) { return hipEventRecord(ctx->kev[2 * k + 1], st); };
+  auto t1 = [&](int k) { return dl ? hipSuccess : hipEventRecord(ctx->kev[2 * k + 1], st); };
   while (c0 < job.nnz) {
     const int64_t nc = std::min<int64_t>(chunk, job.nnz - c0);
     for (auto& u : used) u = false;
@@ -1708,14 +1739,9 @@ stb_status stb_run_pairs(stb_ctx* ctx, const PairJob& job, unsigned long long wo
     // two-gap recipes, full evaluations
     HIPCHK(ctx, t0(4));
     if (dl) {
-      hipLaunchKernelGGL((k_nodes_dl<1, true>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L,
-                         L.job, dev(CNT_JOB), job.gl, job.ng);
-      hipLaunchKernelGGL((k_nodes_dl<1, false>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st,
-                         L, nullptr, dev(CNT_JOB1X), job.gl, job.ng);
-      hipLaunchKernelGGL((k_nodes_dl<2, false>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st,
-                         L, L.job2, dev(CNT_JOB2), job.gl, job.ng);
-      hipLaunchKernelGGL(k_nodes_dl_full, dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L, L.jobf,
-                         dev(CNT_JOBF), job.gl, job.ng);
+      hipLaunchKernelGGL(k_nodes_dl, dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L, job.gl, job.ng);
+      hipLaunchKernelGGL(k_nodes_dl_rest, dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L, job.gl,
+                         job.ng);
     } else {
       hipLaunchKernelGGL((k_nodes_rec<1, true>), dim3(gfor(4, ub_piece)), dim3(ctx->tune_block[4]), 0, st, L,
                          L.job, dev(CNT_JOB), job.gl, job.ng);

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_sums(T* __restrict__ sums
 }
 
 // Pass 3: each tile scanned with its offset; out[i + 1] = sum_{k <= i} in[k],
-// out[0] = 0.
+// out[0] = 0.  sums NULL: a single tile, the only pass then.
 template <typename T>
 __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const T* __restrict__ in, int64_t n,
                                                              const T* __restrict__ sums,
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const T* __restrict
     s += v[k];
   }
   T tot;
-  T run = sums[blockIdx.x] + block_exclusive(s, &tot);
+  T run = (sums ? sums[blockIdx.x] : T(0)) + block_exclusive(s, &tot);
 #pragma unroll
   for (int k = 0; k < kScanPer; ++k) {
     run += v[k];
@@ -146,9 +146,11 @@ hipError_t stb_scan(const T* in, T* out, int64_t n, T* tmp, hipStream_t st) {
   if (n < 0) return hipErrorInvalidValue;
   const int64_t nb = stb_scan_tmp_elems<T>(n);
   if (nb > (int64_t)0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_scan_tile_sums<T>, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, tmp);
-  hipLaunchKernelGGL(k_scan_sums<T>, dim3(1), dim3(kScanThreads), 0, st, tmp, nb);
-  hipLaunchKernelGGL(k_scan_tiles<T>, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, tmp, out);
+  if (nb > 1) {
+    hipLaunchKernelGGL(k_scan_tile_sums<T>, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, tmp);
+    hipLaunchKernelGGL(k_scan_sums<T>, dim3(1), dim3(kScanThreads), 0, st, tmp, nb);
+  }
+  hipLaunchKernelGGL(k_scan_tiles<T>, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, nb > 1 ? tmp : nullptr, out);
   return hipGetLastError();
 }
 

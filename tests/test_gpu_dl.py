@@ -371,3 +371,23 @@ def test_pairs_to_rounding(stb, ctx, panel, n_g):
     assert k.sum() > 3000
     assert np.quantile(np.abs(u[k] - ref[k]) / np.abs(ref[k]), 0.7) <= 24 * 2.0 ** -53
     M.close()
+
+
+# fewer nodes than a piece's lanes, one more, and two rounds of them; points whose
+# cones meet a panel's plane in whole circles (no breakpoints) and in short pieces;
+# one workgroup's share of every job list and several
+@pytest.mark.parametrize("n_g", [2, 15, 17, 33])
+@pytest.mark.parametrize("slabs", [1, 4])
+def test_full_evaluation_nodes(stb, ctx, n_g, slabs):
+    mesh = inputs.icosphere_mesh(0, slabs, T=float(slabs))
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    M.set_normals(mesh.outward_normals())
+    v = np.random.default_rng(4).standard_normal(mesh.nv)
+    cen = mesh.tet_coords().mean(axis=1)
+    off = np.concatenate([np.full((len(cen), 1), 0.05), 1e-3 * mesh.outward_normals()], axis=1)
+    pts = np.concatenate([cen + off, cen + [0.2, 1e-3, 0, 0], inputs.shell_points(40, mesh.T, seed=9)])
+    u = stb.potential_D(ctx, M, v, pts, params=stb.default_params(n_g=n_g))
+    ref = oracle.potential_dl(mesh.vtx, mesh.tets, mesh.outward_normals(), v, pts, n_g=n_g)
+    # the double layer's parity bound
+    assert np.all(np.abs(u - ref) <= 1e-10 * np.maximum(np.abs(ref), 1e-5 * np.abs(ref).max()))
+    M.close()
