@@ -260,10 +260,11 @@ __global__ void k_cull_rowptr(int64_t nrows, int64_t nseg, const int64_t* __rest
 
 // Fill the candidate columns of each row in ascending order, and the row of
 // each: a wavefront starts where its segment of the row does and ranks its
-// lanes by a ballot.
+// lanes by a ballot.  The first segment's also write the rows' starts.
 __global__ __launch_bounds__(256) void k_cull_fill(int64_t nrows, const ApexBox* __restrict__ rows, int64_t nt,
                                                    const TrialRec* __restrict__ T, const int64_t* __restrict__ start,
-                                                   int32_t* __restrict__ cols, int32_t* __restrict__ rowof) {
+                                                   int64_t* __restrict__ rowptr, int32_t* __restrict__ cols,
+                                                   int32_t* __restrict__ rowof) {
   __shared__ RowCull s_r[kCullBlkRows];
   const int64_t b0 = (int64_t)blockIdx.x * kCullBlkRows;
   for (int r = threadIdx.x; r < kCullBlkRows; r += 256) s_r[r] = row_cull(rows[b0 + r < nrows ? b0 + r : nrows - 1]);
@@ -277,6 +278,10 @@ __global__ __launch_bounds__(256) void k_cull_fill(int64_t nrows, const ApexBox*
   int64_t base[kCullRows];
 #pragma unroll
   for (int r = 0; r < kCullRows; ++r) base[r] = r < nr ? start[(i0 + r) * gridDim.y + blockIdx.y] : 0;
+  if (blockIdx.y == 0) {
+    if (lane < nr) rowptr[i0 + lane] = start[(i0 + lane) * gridDim.y];
+    if (blockIdx.x == 0 && threadIdx.x == 0) rowptr[nrows] = start[nrows * gridDim.y];
+  }
   for (; j0 < j1; j0 += 64) {
     const bool in = j0 + lane < j1;
     const TrialRec* const Tj = T + (in ? j0 + lane : j1 - 1);
@@ -605,10 +610,6 @@ stb_status stb_exclusive_scan(stb_ctx* ctx, const int64_t* in, int64_t* out, int
   return STB_OK;
 }
 
-static stb_status device_exclusive_scan(stb_ctx* ctx, const int64_t* in, int64_t* out, int64_t n) {
-  return stb_exclusive_scan(ctx, in, out, n, ctx->stream);
-}
-
 // Apex boxes of evaluation points (enqueued on ctx's stream).
 void stb_point_boxes(stb_ctx* ctx, int64_t np, const double* d_pts, ApexBox* d_box) {
   if (np > 0)
@@ -617,13 +618,15 @@ void stb_point_boxes(stb_ctx* ctx, int64_t np, const double* d_pts, ApexBox* d_b
 }
 
 // The start of every row's and segment's candidates (nrows * nseg + 1, kept
-// block): the count pass and its scan, enqueued on ctx's stream.
+// block): the count pass and its scan, enqueued on ctx's stream and not waited
+// for (the caller waits once, for the total).
 static stb_status cull_starts(stb_ctx* ctx, int64_t nrows, const ApexBox* d_rows, const stb_mesh* m, int64_t nseg,
                               int64_t** start) {
   int64_t* d_cnt = nullptr;
   *start = nullptr;
-  if (kalloc(ctx, &d_cnt, (size_t)(nrows * nseg)) != hipSuccess ||
-      kalloc(ctx, start, (size_t)(nrows * nseg) + 1) != hipSuccess) {
+  const int64_t m_cnt = nrows * nseg;
+  if (kalloc(ctx, &d_cnt, (size_t)(m_cnt + stb_scan_tmp_elems<int64_t>(m_cnt))) != hipSuccess ||
+      kalloc(ctx, start, (size_t)m_cnt + 1) != hipSuccess) {
     ctx_keep(ctx, d_cnt);
     return fail(ctx, STB_E_NO_MEMORY, "cull counts");
   }
@@ -631,11 +634,12 @@ static stb_status cull_starts(stb_ctx* ctx, int64_t nrows, const ApexBox* d_rows
     hipLaunchKernelGGL(k_cull_count, dim3((unsigned)((nrows + kCullBlkRows - 1) / kCullBlkRows), (unsigned)nseg),
                        dim3(256), 0, ctx->stream, nrows, d_rows, m->nt, m->d_trial, d_cnt);
   hipError_t e = hipGetLastError();
-  stb_status s = e == hipSuccess ? device_exclusive_scan(ctx, d_cnt, *start, nrows * nseg)
-                                 : fail(ctx, STB_E_DEVICE, "cull count: %s", hipGetErrorString(e));
+  if (e == hipSuccess) e = stb_scan<int64_t>(d_cnt, *start, m_cnt, d_cnt + m_cnt, ctx->stream);
   ctx_keep(ctx, d_cnt);
-  if (s) { ctx_keep(ctx, *start); *start = nullptr; }
-  return s;
+  if (e == hipSuccess) return STB_OK;
+  ctx_keep(ctx, *start);
+  *start = nullptr;
+  return fail(ctx, STB_E_DEVICE, "cull count: %s", hipGetErrorString(e));
 }
 
 // Device bytes of the cull's temporaries: counts, starts and the scan's scratch.
@@ -695,17 +699,19 @@ stb_status stb_cull(stb_ctx* ctx, int64_t nrows, const ApexBox* d_rows, const st
   if (s) return s;
   auto run = [&]() -> stb_status {
     HIPCHK(ctx, dalloc(d_rowptr, (size_t)nrows + 1));
-    hipLaunchKernelGGL(k_cull_rowptr, dim3((unsigned)(nrows / 256 + 1)), dim3(256), 0, ctx->stream, nrows, nseg,
-                       d_start, *d_rowptr);
-    HIPCHK(ctx, hipGetLastError());
-    HIPCHK(ctx, hipMemcpy(nnz, d_start + nrows * nseg, sizeof(int64_t), hipMemcpyDeviceToHost));
+    // (on the context's stream: a copy on the null stream would not wait for it)
+    HIPCHK(ctx, hipMemcpyAsync(nnz, d_start + nrows * nseg, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     HIPCHK(ctx, lend ? kalloc(ctx, d_cols, (size_t)*nnz) : dalloc(d_cols, (size_t)*nnz));
     HIPCHK(ctx, lend ? kalloc(ctx, d_rowof, (size_t)*nnz) : dalloc(d_rowof, (size_t)*nnz));
     if (nrows > 0) {
       hipLaunchKernelGGL(k_cull_fill, dim3((unsigned)((nrows + kCullBlkRows - 1) / kCullBlkRows), (unsigned)nseg),
-                         dim3(256), 0, ctx->stream, nrows, d_rows, m->nt, m->d_trial, d_start, *d_cols, *d_rowof);
-      HIPCHK(ctx, hipGetLastError());
+                         dim3(256), 0, ctx->stream, nrows, d_rows, m->nt, m->d_trial, d_start, *d_rowptr, *d_cols,
+                         *d_rowof);
+    } else {
+      hipLaunchKernelGGL(k_cull_rowptr, dim3(1), dim3(256), 0, ctx->stream, nrows, nseg, d_start, *d_rowptr);
     }
+    HIPCHK(ctx, hipGetLastError());
     return STB_OK;
   };
   s = run();

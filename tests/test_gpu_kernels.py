@@ -279,3 +279,31 @@ def test_column_part_stores_pass_the_limit(stb, ctx, level, slabs, parts):
         assert y[row] == y_parts and len(c) > 64
     A.close()
     M.close()
+
+
+# few candidates (their combos listed in one launch), both sides of its 4,096, and
+# chunks of few candidates by short lists, which overflow: a point's value is the
+# same in every call
+@pytest.mark.parametrize("layer", ["S", "D"])
+def test_potentials_do_not_depend_on_the_call(stb, layer):
+    mesh = inputs.icosphere_mesh(1, 13)
+    rng = np.random.default_rng(7)
+    pts = inputs.shell_points(60, mesh.T, seed=8)
+    w = rng.standard_normal(mesh.nv if layer == "D" else mesh.nt)
+    call = stb.potential_D if layer == "D" else stb.potential_S
+    c = stb.Context(0)
+    M = stb.Mesh(c, mesh.vtx, mesh.tets)
+    M.set_normals(mesh.outward_normals())
+    ref = call(c, M, w, pts)
+    assert c.lit_search()["candidates"] > 4096 > 0
+    sizes = set()
+    for k in (1, 2, 5, 9, 20):
+        u = np.concatenate([call(c, M, w, pts[i:i + k]) for i in range(0, 60, k)])
+        sizes.add(c.lit_search()["candidates"] > 4096)
+        assert np.array_equal(u, ref), k
+    for limits in ((64, 64, 64), (5000, 0, 0), (0, 100, 0), (0, 0, 300)):
+        stb.set_pair_lists(c, *limits)
+        assert np.array_equal(call(c, M, w, pts), ref), limits
+    assert sizes == {False, True}
+    M.close()
+    c.close()
