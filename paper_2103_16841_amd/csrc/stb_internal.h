@@ -235,6 +235,10 @@ stb_status stb_face_assemble(stb_ctx* ctx, const stb_quad_params& p, FaceUnit* u
 // st.
 stb_status stb_keep_causal(stb_ctx* ctx, stb_mat* M, const uint8_t* d_flag, hipStream_t st);
 
+// The plan of M's FP64 product by column parts (stb_lib.hip): made with every store
+// large enough for it, unless its memory is refused.  Synchronises st.
+stb_status stb_spmv_plan(stb_ctx* ctx, stb_mat* M, hipStream_t st);
+
 // Lit search of evaluation points by the cluster tree (stb_tree.hip): the
 // tree for leaves of at most nmin panels is built on first use; candidates
 // as by stb_cull (CSR per point, row of each candidate), nleaves (optional)

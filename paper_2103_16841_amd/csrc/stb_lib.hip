@@ -763,8 +763,9 @@ stb_status stb_cull_points(stb_ctx* ctx, stb_mesh* m, const stb_quad_params& p, 
 constexpr int64_t kSpmvLdsMin = (int64_t)1 << 24;
 
 // The column parts of a large store and where each row crosses them, made with
-// the store so that a product allocates nothing.
-static stb_status spmv_plan(stb_ctx* ctx, stb_mat* M, hipStream_t st) {
+// the store so that a product allocates nothing.  A store whose plan does not fit
+// beside it keeps the product without one (k_spmv).
+stb_status stb_spmv_plan(stb_ctx* ctx, stb_mat* M, hipStream_t st) {
   dfree(M->d_split);
   M->d_split = nullptr;
   M->nparts = 0;
@@ -774,7 +775,7 @@ static stb_status spmv_plan(stb_ctx* ctx, stb_mat* M, hipStream_t st) {
   const int P = (int)((nc + np - 1) / np);
   if (np > 1) {
     const int64_t m = M->n * (np - 1);
-    if (dalloc(&M->d_split, (size_t)m) != hipSuccess) return fail(ctx, STB_E_NO_MEMORY, "product plan");
+    if (dalloc(&M->d_split, (size_t)m) != hipSuccess) return STB_OK;
     hipLaunchKernelGGL(k_spmv_split, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, M->n, np, P, M->d_rowptr,
                        M->d_cols, M->d_split);
     HIPCHK(ctx, hipGetLastError());
@@ -825,7 +826,7 @@ stb_status stb_keep_causal(stb_ctx* ctx, stb_mat* M, const uint8_t* d_flag, hipS
   M->d_vals = vals;
   M->nnz = nk;
   M->host_valid = false;
-  return spmv_plan(ctx, M, st);
+  return stb_spmv_plan(ctx, M, st);
 }
 
 // Host copy of a matrix store (for stb_mat_get / stb_mat_to_dense).

@@ -171,3 +171,31 @@ def test_server_counts_the_cull(stb):
         S.close()
     M.close()
     ctx.close()
+
+
+def test_store_without_a_product_plan(stb):
+    """A large store whose product plan (where its rows cross the column parts) is
+    refused keeps the product without one: the same sums in another order."""
+    mesh = inputs.icosphere_mesh(2, 32)
+    ctx = stb.Context(0)
+    M = stb.Mesh(ctx, mesh.vtx, mesh.tets)
+    A = stb.assemble_V(ctx, M, stb.default_params(m_q=1, n_g=2))
+    plan = stb.load()._Z13stb_spmv_planP7stb_ctxP7stb_matP12ihipStream_t
+    plan.argtypes = [ctypes.c_void_p] * 3
+    w = np.random.default_rng(2).standard_normal(A.n)
+    y = A.apply(w)
+    with allowance(stb, 0):
+        assert plan(ctx.h, A.h, None) == 0
+    z = A.apply(w)
+    rowptr, cols, vals = A.export()
+    from scipy.sparse import csr_matrix
+    scale = csr_matrix((np.abs(vals), cols, rowptr), shape=(A.n, A.n)) @ np.abs(w)
+    terms = np.diff(rowptr)
+    assert not np.array_equal(y, z)
+    # either order: at most (terms) eps of the terms' size
+    assert np.all(np.abs(y - z) <= 2 * terms * 2.0 ** -53 * scale)
+    assert plan(ctx.h, A.h, None) == 0
+    assert np.array_equal(A.apply(w), y)
+    A.close()
+    M.close()
+    ctx.close()
