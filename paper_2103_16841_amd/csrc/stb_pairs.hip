@@ -580,13 +580,15 @@ __device__ __forceinline__ FaceAng face_ang(const FaceAng* __restrict__ p) {
   return F;
 }
 
-// Bound by instruction issue (about 2,240 vector instructions per wave and
-// pass, the vector pipes busy 68%); three waves per SIMD by its LDS slots and
-// registers.  30,720-panel assembly, 3.77e8 combos: 41.2 ms with every panel
-// field behind one reference, both signs of each tangency and the sorted
-// breakpoints written back; 35.5 ms with the record read in parts, the
-// tangencies' one reachable root, and the pieces taken from the sorted
-// registers.  Four waves per SIMD (19 slots, 128 registers): 43.2 ms, spills.
+// Bound by latency and instruction issue (about 2,240 vector instructions per wave
+// and pass, at 4 cycles each 59% of its time); three waves per SIMD by its LDS
+// slots and registers (168, and 20 spilled: the sorted breakpoints live across the
+// list allocation).  30,720-panel assembly, 3.77e8 combos: 41.2 ms with every
+// panel field behind one reference, both signs of each tangency and the sorted
+// breakpoints written back (152 registers, none spilled); 36.0 ms with the record
+// read in parts, the tangencies' one reachable root, and the pieces taken from the
+// sorted registers, although the spills write 2.4 GB more per chunk than its lists
+// hold.  Four waves per SIMD (19 slots, 128 registers): 43.2 ms.
 __global__ __launch_bounds__(kBlk, 3) void k_bp(Geo g, Lists L, int64_t c0, int64_t ncombo_arg) {
   const int B = (int)blockDim.x;
   const int64_t ncombo = list_count(L, ncombo_arg, L.cap_combo, 2);
