@@ -1543,10 +1543,14 @@ STB_HD __forceinline__ float far_end_value(const FarEnd& F, double B, double wc,
 }
 
 // A combo is far when the apex's spatial distance from the trial panel's
-// bounding ball exceeds eta times the ball's radius.
+// bounding ball exceeds eta times the ball's radius.  Not with the smallest
+// panels: the discriminants in delta are of the order of the panel's size
+// squared, and in FP32 they, and with them the nodes' error bounds, lose their
+// bits below 2^-126 (wrong entries from sizes of 1e-15 down).
+constexpr double kFarMinDiam = 0x1p-40;
 STB_HD __forceinline__ bool apex_far(const TrialRec& T, const double* x4, double eta) {
   double dx = x4[1] - T.cx, dy = x4[2] - T.cy, dz = x4[3] - T.cz;
-  return sqrt(dx * dx + dy * dy + dz * dz) - T.rad > eta * T.rad;
+  return T.diam >= kFarMinDiam && sqrt(dx * dx + dy * dy + dz * dz) - T.rad > eta * T.rad;
 }
 
 STB_HD __forceinline__ double L_at(const ComboL& cb, double phi) {

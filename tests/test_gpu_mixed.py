@@ -131,3 +131,22 @@ def test_mixed_against_fp64_through_the_same_points(stb, ctx):
     assert redone > 0
     assert np.count_nonzero(vm == vp) >= redone
     assert err.max() <= MTOL
+
+
+@pytest.mark.parametrize("eta", [0.0, 0.5])
+def test_scaled_meshes(stb, eta):
+    """The entries' bound holds at every size of the panels: where FP32 cannot
+    represent what the far nodes need, they are FP64 (or recomputed)."""
+    mesh = inputs.icosphere_mesh(level=0, S=4, T=3.0, jitter=0.15, seed=4)
+    ctx = stb.Context(0)
+    for k in (-150, -130, -110, -90, -70, -60, -52, -46, -41, -39, -30, 0, 30, 60, 70, 90, 110, 130):
+        M = stb.Mesh(ctx, mesh.vtx * 2.0 ** k, mesh.tets)
+        A = stb.assemble_V(ctx, M, stb.default_params(prec=stb.STB_MIXED, eta_far=eta))
+        B = stb.assemble_V(ctx, M, stb.default_params(prec=stb.STB_MIXED, eta_far=1e300))   # FP64, same points
+        (ra, ca, va), (rb, cb, vb) = A.export(), B.export()
+        assert np.array_equal(ra, rb) and np.array_equal(ca, cb)
+        assert np.all(np.abs(va - vb) <= 1e-6 * np.abs(vb)), k
+        A.close()
+        B.close()
+        M.close()
+    ctx.close()
