@@ -74,8 +74,9 @@ typedef enum { STB_LIT_TREE = 0, STB_LIT_FLAT = 1 } stb_lit_search;
  * Mixed (stb_assemble_V only; the potential is always FP64): the phi nodes
  * of "far" (outer point, trial panel) pairs -- the point farther than
  * eta_far times the radius of the panel's spatial bounding ball from that
- * ball (default 0.5), the panel at least 2^-40 in diameter -- solve the face quadratics and measure the r-gaps in
- * FP32 about the middle of the pair's admissible range, with Kahan-summed
+ * ball (default 0.5), the panel at least 2^-40 in diameter -- solve the face
+ * quadratics and measure the r-gaps in FP32 about the middle of the pair's
+ * admissible range, with Kahan-summed
  * FP32 node sums; lit test, breakpoints, empty-piece tests, angles and the
  * quadratics' coefficients stay FP64.  Every entry carries a first-order
  * bound of its FP32 error; entries whose bound exceeds 3e-6 of their size
